@@ -413,10 +413,9 @@ const char *grte_status_string(grte_status s);
 
 /* ------------------------------------------------------------------------
  * Batched slabs: many independent 1-D problems of the kind above, each with
- * its own N, P, opacity law, eps and dt, advanced together by one persistent
- * kernel per step (one tile of 256 or 64 threads per instance, instances
- * taken from a device work queue in longest-first order).  Each instance
- * computes exactly the step of grte_step (Algorithm 2).
+ * its own N, P, opacity law, eps and dt, advanced together (in the solves one
+ * tile of eight wavefronts or one wavefront per instance, in longest-first
+ * order).  Each instance computes exactly the step of grte_step (Algorithm 2).
  *
  * Packed layouts: instances are concatenated in the order given at creation.
  * For instance i with N_i cells and P_i pairs, its block starts at
@@ -448,8 +447,9 @@ typedef struct grte_batch_info {   /* per instance, as grte_step_info         */
 
 typedef struct grte_batch_tuning {
     int wave_max_n;    /* instances with N <= wave_max_n (<= 256) run on one
-                          wavefront, the others on a 256-thread work-group    */
-    int grid;          /* work-groups of the persistent launch                 */
+                          wavefront, the others on an eight-wavefront work-group */
+    int grid;          /* work-groups the device holds at once (kept and returned;
+                          a launch has one work-group per instance whatever it is) */
     double step_ms;    /* filled by grte_batch_tune: time of one step          */
 } grte_batch_tuning;
 
@@ -496,7 +496,7 @@ grte_status grte_batch_step(grte_batch *b, grte_batch_info *info);
  * enqueue steps or graph replays without `info`.  Synchronises the stream. */
 grte_status grte_batch_get_error_flags(grte_batch *b, int *flags, int clear);
 /* Autotuner: times `trials` steps for each candidate (wavefront threshold
- * 0/128/256 x grid of 1, 2, ... work-groups per compute unit) from the
+ * 0/128/256) from the
  * current state without changing it (each candidate step also starts its
  * prediction from the same iterate as the next real step will), orders the
  * instances by the measured work (iterations x N x P, largest first) and

@@ -3,30 +3,23 @@
 // graph of eight launches per step (the grte_batch_* calls of include/grte.h):
 // the per-cell phases (coefficients and right-hand sides, moments and Newton,
 // the correction's right-hand sides, the projection) as flat kernels over all
-// cells, the two per-slab solves (prediction, correction) as persistent tile
-// kernels.
+// cells, the two per-slab solves (prediction, correction) as one tile per slab.
 //
-// In the solve kernels every instance is advanced by one "tile": a whole
-// work-group (W = 256 threads) or, for small slabs, one wavefront (W = 64; four
-// independent instances per work-group).  In a work-group tile the per-pair
-// tridiagonal solves are split over its four wavefronts (pairs p = w, w + 4,
-// ... on wavefront w), each solving its pair alone with 4 M rows per lane:
-// four independent elimination chains in flight per work-group.  The step is
-// the algebra of the
+// In the solve kernels every instance is advanced by one "tile": a work-group of
+// NWB wavefronts or, for small slabs, one wavefront (NWB independent instances per
+// work-group).  The pairs of a slab are dealt to the tile's wavefronts, each
+// solving its pair alone (slab_tile.hpp).  The step is the algebra of the
 // single-instance path (Algorithm 2 and Section 5 of Tang, Wang & Zhang):
 // the per-pair tridiagonal operators T_p = Lam + mu_p^2 L + mu_p B with U*
 // eliminated through (4.5c), the angular coupling of the prediction solved by
 // the DSA-preconditioned residual-form iteration with adaptive Chebyshev
 // updates (warm-started from the previous step's rho*),
 // Newton on (4.13)/(5.5), the per-pair correction (4.11) and the projection
-// (4.14).  One tile owns all parity pairs of its instance, so the angular sum
-// is accumulated in registers (and, across the wavefronts of a work-group,
-// summed through LDS in a fixed order) and no grid-wide synchronisation
-// exists.
-// Instances are taken from two work queues -- work-group tiles first, then
-// wavefront tiles -- in an order chosen by the host (longest expected work
-// first), so that work-groups that finish their large slabs early drain the
-// small ones.
+// (4.14).  One tile owns all parity pairs of its instance, so no grid-wide
+// synchronisation exists.
+// The work-groups of a launch are the instances in an order chosen by the host
+// (longest expected work first, work-group tiles before wavefront tiles), which
+// the device hands to its compute units as they come free.
 
 #include <hip/hip_runtime.h>
 
@@ -38,13 +31,14 @@
 #include <vector>
 
 #include "../../include/grte.h"
-#include "solver_common.hpp"
+#include "slab_tile.hpp"
 
 namespace {
 
-constexpr int BNT = 256;              // threads per work-group
+constexpr int NWB = 8;                // wavefronts per work-group tile
+constexpr int BNT = 64 * NWB;         // threads per work-group of the solves
 constexpr int WAVE = 64;
-constexpr int BMAX_N = 2048;          // largest slab of the batched path (8 rows per thread)
+constexpr int BMAX_N = 2048;          // largest slab of the batched path (32 rows per lane)
 constexpr int BMAX_P = 64;
 constexpr int WAVE_MAX_N = 256;       // largest slab a wavefront tile can take (4 rows per lane)
 
@@ -55,15 +49,16 @@ enum {
     NCA
 };
 
-// LDS of one tile (doubles).  A work-group tile (NP = 256 M padded rows, in
-// the layout of the wavefront solver: 64 lanes of 4 M rows) holds rho, Ll, Lu,
-// Lam and Lam - G, the angular sums of its four wavefronts (4 NP), the last
-// Chebyshev update of every row (NP binary32) and a 32-double reduction area;
-// a wavefront tile holds rho, Ll, Lu in its position order and its solver's
-// scratch.
-constexpr int LDS_WG = 9 * BMAX_N + BMAX_N / 2 + 32;
-constexpr int LDS_WAVE = 3 * WAVE_MAX_N + tile_scratch<WAVE>();
-static_assert(4 * LDS_WAVE <= LDS_WG, "four wavefront tiles fit in the work-group LDS");
+// LDS of the solves (doubles): the largest work-group tile, or a wavefront tile per wavefront
+constexpr int LDS_WAVE = tile_lds<1, 4>();
+template <int M = 4>
+constexpr int lds_wg()
+{
+    if constexpr (M + 2 > BMAX_N / 64) return tile_lds<NWB, M>();
+    else return std::max(tile_lds<NWB, M>(), lds_wg<M + 2>());
+}
+constexpr int LDS_WG = std::max(lds_wg(), NWB * LDS_WAVE);
+static_assert(LDS_WG * sizeof(double) + 64 <= 160 * 1024, "the tile fits the LDS of a CU");
 
 struct BInst {
     int N, P, m, W, M;                 // tile of W threads, M rows each
@@ -72,14 +67,13 @@ struct BInst {
     double dx, a, c, cv, eps, dt;
     double one_minus_W, mu1, mu2;      // 1 - sum omega (exact), sum omega mu, sum omega mu^2
     long long oE, oO, oT, oP;          // offsets of E (N P), O ((N+1) P), cells (N), pairs (P)
-    long long oC, oR, NPa;             // cell scratch, pair scratch (2 P NPa), padded rows allocated
+    long long oC, oR, oF, NPa;         // cell scratch, pair scratch (2 P NPa), factorisations, padded rows allocated
 };
 
 struct BatchArgs {
     int n_wg, n_wave;
     const BInst *inst;
     const int *order;                  // n_wg work-group instances, then n_wave wavefront instances
-    int *queue;                        // per solve kernel: [0] work-group queue head, [1] wavefront queue head
     const int2 *cblk;                  // blocks of the per-cell kernels: (instance, first cell)
     double *epart;                     // 2 per block of the projection: the energy partial sums
     int n_inst;
@@ -91,7 +85,7 @@ struct BatchArgs {
     float *E32o, *O32o;
     int f32;                    // (the kernel variant is chosen by the host)
     const double *mu, *omega, *bL, *bR;
-    double *cells, *pairs;
+    double *cells, *pairs, *fac;
     int *istat;                        // 8 per instance
     double tol;
     int maxit, newton_maxit;
@@ -101,27 +95,6 @@ struct BatchArgs {
     double *ienergy;            // per instance: E_tot^n, E_tot^{n+1}, outflow dt, defect
     int *sticky;                // error flags OR-ed over steps (GRTE_ERRF_*), not cleared by a step
 };
-
-// make the tile's LDS and global writes visible to the whole tile
-template <int W>
-__device__ __forceinline__ void tsync()
-{
-    if constexpr (W == BNT) {
-        __syncthreads();
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    }
-}
-
-// v through an empty asm: the compiler cannot hoist what is derived from the
-// result out of the enclosing loop (keeps per-row addresses out of registers)
-__device__ __forceinline__ int opaque(int v)
-{
-    __asm__ volatile("" : "+v"(v));
-    return v;
-}
 
 // interior node i (1..N-1): harmonic-mean sigma, arithmetic-mean K
 __device__ __forceinline__ void b_node(const BInst &I, const double *Tk, const double *sg, int i,
@@ -520,460 +493,99 @@ __device__ __forceinline__ void cell_project(const BatchArgs &A, const IView<F32
     ea = I.dx * (r1 / I.c + I.cv * t1);
 }
 
-// W = BNT: a work-group tile of LMW rows per lane (NP = 64 LMW; M = LMW / 4 rows per
-// thread of the work-group-wide diffusion solve where LMW is a multiple of 4 and at
-// least 8); W = 64: a wavefront tile of M rows per lane
-template <int W, int M, bool F32, int LMW = 4 * M>
+// the prediction of instance i by a tile of NW wavefronts, M rows per lane: E* into
+// the pair scratch, rho* into rprev (the next step's starting iterate)
+template <int NW, int M>
 __device__ __forceinline__ void pred_solve(const BatchArgs &A, int i, double *sm)
 {
-    constexpr int NP = 64 * (W == BNT ? LMW : M);
     const BInst I = A.inst[i];
-    const int N = I.N, P = I.P, N1 = N + 1;
-    const int k = opaque(tile_lane<W>());   // opaque: per-thread addresses are formed per instance, not held across the queue loop
-    const int j0 = k * M;
-    const double *Tn = A.T + I.oT;
-    BState<F32> S;
-    S.P = I.P;
+    const int N1 = I.N + 1;
+    const double *C = A.cells + I.oC;
+    TileSys S;
     S.N = I.N;
-    S.ac = I.a * I.c;
-    S.Tn = Tn;
-    S.E = F32 ? nullptr : A.E + I.oE;
-    S.O = F32 ? nullptr : A.O + I.oO;
-    S.E32 = F32 ? A.E32 + I.oE : nullptr;
-    S.O32 = F32 ? A.O32 + I.oO : nullptr;
-    const double *mu = A.mu + I.oP, *om = A.omega + I.oP;
-    double *C = A.cells + I.oC;
-    // Per-pair global arrays are pair-major in cell order: thread k's rows
-    // j0 .. j0+M-1 are contiguous, so its loads and stores are wide and the
-    // later per-cell phases read along cells.
-    double *Rt = A.pairs + I.oR;                  // right-hand sides
-    double *Et = Rt + (size_t)P * I.NPa;          // E* (prediction), then E^{n+1} (correction)
-    int *st = A.istat + 8 * i;
-    // Work-group tiles keep the per-row arrays in the layout of the wavefront
-    // solver (LM = 4 M rows per lane, row j at LDS position (j % LM) 64 + j / LM);
-    // wavefront tiles in their own position order (LM = M, the same formula).
-    constexpr bool WG = (W == BNT);
-    constexpr int LM = WG ? LMW : M;
-    auto lpos = [](int j) { return (j % LM) * 64 + j / LM; };
-    double *rho = sm, *sLl = sm + NP, *sLu = sm + 2 * NP, *sh = sm + 3 * NP;
-    double *slam = nullptr, *slmg = nullptr, *accw = nullptr, *red = nullptr;
-    float *sdch = nullptr;
-    if constexpr (WG) {
-        slam = sm + 3 * NP;
-        slmg = sm + 4 * NP;
-        accw = sm + 5 * NP;
-        sdch = reinterpret_cast<float *>(sm + 9 * NP);
-        red = sm + 9 * NP + NP / 2;
-    }
-
-    double *rp = A.rprev + I.oT;
-    for (int j = k; j < NP; j += W) {
-        const int t = lpos(j);
-        const bool in = j < N;
-        rho[t] = in ? (A.warm ? rp[j] : C[C_RHON * N1 + j]) : 0.0;
-        sLl[t] = in ? C[C_LL * N1 + j] : 0.0;
-        sLu[t] = in ? C[C_LU * N1 + j] : 0.0;
-        if constexpr (WG) {
-            slam[t] = in ? C[C_LAM * N1 + j] : 1.0;   // padding rows: T_p = D = 1, no coupling
-            slmg[t] = in ? C[C_LMG * N1 + j] : 1.0;
-            sdch[t] = 0.0f;
-        }
-    }
-    tsync<W>();
-    const double bd0 = C[C_BD * N1 + 0], bdN = C[C_BD * N1 + N - 1];
-
-    // ---------------- prediction: DSA-preconditioned iteration (plain or Chebyshev updates)
-    int it = 0, converged = 0, ph = 0;
-    ChebState Cs;
-    if constexpr (WG) {
-        const int w = threadIdx.x >> 6;
-        // Per lane: jq = first row, nv = rows inside the slab, rl1 = lane row of
-        // the slab's last row.  The lane index is re-derived through opaque() in
-        // every pair step, so each array costs one base register there and the
-        // rows are immediate offsets r * 64 doubles.
-        // Padding rows (j >= N) need no tests: their right-hand sides are zero,
-        // Lam = Lam - G = 1 and Ll = Lu = 0 there, so every solve and update
-        // below yields exact zeros in them.
-        auto load_r = [&](int p, double (&v)[LM]) {
-            const double *src = Rt + (size_t)p * NP + opaque(threadIdx.x & 63) * LM;
+    S.P = I.P;
+    S.mu = A.mu + I.oP;
+    S.om = A.omega + I.oP;
+    S.Ll = C + C_LL * N1;
+    S.Lu = C + C_LU * N1;
+    S.Lam = C + C_LAM * N1;
+    S.LmG = C + C_LMG * N1;
+    S.bd0 = C[C_BD * N1];
+    S.bdN = C[C_BD * N1 + I.N - 1];
+    S.mu1 = I.mu1;
+    S.mu2 = I.mu2;
+    S.omw = I.one_minus_W;
+    S.rhs = A.pairs + I.oR;
+    S.rhs_stride = 64 * M;
+    S.rho0 = A.warm ? A.rprev + I.oT : C + C_RHON * N1;
+    S.rho_out = A.rprev + I.oT;
+    S.fac = A.fac + I.oF;
+    S.accel = A.accel;
+    S.maxit = A.maxit;
+    S.tol = A.tol;
+    S.hist = nullptr;
+    double *Et = A.pairs + I.oR + (size_t)I.P * I.NPa;
+    int converged = 0;
+    const int it = pred_tile<NW, M>(S, sm, converged, [&](int p, int j0, const double (&x)[M]) {
+        double *ep = Et + (size_t)p * (64 * M) + j0;
 #pragma unroll
-            for (int r = 0; r < LM; ++r) v[r] = src[r];
-        };
-        // One sweep of this wavefront's pairs from the current rho: v_p = T_p^{-1}
-        // [r_p - (Lam - G + mu^2 L + mu B) rho], summed as omega_p v_p into the
-        // wavefront's LDS row sums, or (final) E*_p = rho + v_p written.  rnext
-        // holds pair w's right-hand side on entry and again on return (loaded
-        // while the tile waits).
-        double rnext[LM];
-        if (w < P) load_r(w, rnext);
-        auto sweep = [&](bool final_sweep) {
-            if (!final_sweep) {
-                double *acc = accw + w * NP + opaque(threadIdx.x & 63);
-#pragma unroll
-                for (int r = 0; r < LM; ++r) acc[r * 64] = 0.0;
-            }
-            for (int p = w; p < P; p += 4) {
-                const double m1 = mu[p], m2 = m1 * m1, wp = om[p];
-                double x[LM];
-#pragma unroll
-                for (int r = 0; r < LM; ++r) x[r] = rnext[r];
-                load_r(p + 4 < P ? p + 4 : w, rnext);
-                const int lq = opaque(threadIdx.x & 63), jq = lq * LM, rl1 = N - 1 - jq;
-                const double *rh = rho + lq, *ll = sLl + lq, *lu = sLu + lq, *la = slam + lq, *lg = slmg + lq;
-                const double b0 = jq == 0 ? bd0 : 0.0;
-                auto bdr = [&](int r) { return (r == 0 ? b0 : 0.0) + (r == rl1 ? bdN : 0.0); };
-#pragma unroll
-                for (int r = 0; r < LM; ++r) {
-                    // the neighbours' rho (an in-bounds dummy where there is none: its
-                    // coefficient ll or lu is 0 there)
-                    const double rj = rh[r * 64];
-                    const double rl = (r > 0) ? rh[(r - 1) * 64] : (jq > 0 ? rh[(LM - 1) * 64 - 1] : rj);
-                    const double rn = (r < LM - 1) ? rh[(r + 1) * 64] : (lq < 63 ? rh[1] : rj);
-                    const double q = ll[r * 64] * (rl - rj) + lu[r * 64] * (rn - rj);   // difference form
-                    x[r] = x[r] - lg[r * 64] * rj - m2 * q - m1 * bdr(r) * rj;
-                }
-                lane_chunk_solve<LM>(
-                    [&](int r) { return m2 * ll[r * 64]; },
-                    [&](int r) { return la[r * 64] + m2 * (-(ll[r * 64] + lu[r * 64])) + m1 * bdr(r); },
-                    [&](int r) { return m2 * lu[r * 64]; }, x);
-                if (final_sweep) {
-                    double *ep = Et + (size_t)p * NP + jq;
-#pragma unroll
-                    for (int r = 0; r < LM; ++r) ep[r] = rh[r * 64] + x[r];
-                } else {
-                    double *acc = accw + w * NP + lq;
-#pragma unroll
-                    for (int r = 0; r < LM; ++r) acc[r * 64] += wp * x[r];
-                }
-            }
-        };
-        while (true) {
-            {
-                sweep(false);
-                __syncthreads();
-                double alpha, beta;
-                cheb_coeffs(Cs, A.accel, A.tol, alpha, beta);   // every wavefront: the same state
-                if constexpr (LM % 4 == 0 && LM >= 8) {
-                    // res = sum_p omega_p v_p - (1 - W) rho (the four wavefronts' sums in
-                    // a fixed order);  rho += res + D^{-1} (G res), G = Lam - (Lam - G),
-                    // D = Lam - G + <mu^2> L + <mu> B (the diffusion operator of the DSA),
-                    // solved by the whole work-group (tri_factor_solve): thread k takes the
-                    // M rows j = k M + r, which lie in lane k / 4 of the wavefront layout
-                    // at rows (k % 4) M + r, i.e. at LDS position base + 64 r
-                    const int kk = opaque((int)threadIdx.x);
-                    const int base = (kk & 3) * M * 64 + (kk >> 2), jk = kk * M;
-                    double rl[M], d[M], bb[M], f[M];
-#pragma unroll
-                    for (int r = 0; r < M; ++r) {
-                        const int t = base + r * 64, j = jk + r;
-                        const double tot = ((accw[t] + accw[NP + t]) + accw[2 * NP + t]) + accw[3 * NP + t];
-                        rl[r] = tot - I.one_minus_W * rho[t];
-                        d[r] = (slam[t] - slmg[t]) * rl[r];
-                        const double bdj = (j == 0 ? bd0 : 0.0) + (j == N - 1 ? bdN : 0.0);
-                        bb[r] = slmg[t] + I.mu2 * (-(sLl[t] + sLu[t])) + I.mu1 * bdj;
-                    }
-                    __syncthreads();                  // every angular sum read: accw is the solver's scratch now
-                    int ph0 = 0;
-                    tri_factor_solve<BNT, M>(I.mu2, sLl, sLu, bb, d, f, accw, ph0, base, 64);
-                    double md = 0.0, mr = 0.0;
-#pragma unroll
-                    for (int r = 0; r < M; ++r) {
-                        const int t = base + r * 64;
-                        const double z = rl[r] + f[r];
-                        const double upd = alpha * (double)sdch[t] + beta * z;
-                        sdch[t] = (float)upd;
-                        const double nw = rho[t] + upd;
-                        rho[t] = nw;
-                        md = fmax(md, fabs(z));
-                        mr = fmax(mr, fabs(nw));
-                    }
-                    // maxima over the tile: a butterfly per wavefront, then the four in order
-#pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) {
-                        md = fmax(md, __shfl_xor(md, o, 64));
-                        mr = fmax(mr, __shfl_xor(mr, o, 64));
-                    }
-                    if ((threadIdx.x & 63) == 0) {
-                        red[w] = md;
-                        red[8 + w] = mr;
-                    }
-                } else {
-                    // the same correction where the tile's rows per lane are not 4 M
-                    // (M >= 2): every wavefront solves the whole diffusion system in the
-                    // wavefront layout (lane_chunk_solve, LM rows per lane), the same in
-                    // all four; wavefront w then updates the rows r = w (mod 4) of its lanes
-                    const int lq = opaque(threadIdx.x & 63), jq = lq * LM, rl1 = N - 1 - jq;
-                    const double *ll = sLl + lq, *lu = sLu + lq, *lg = slmg + lq;
-                    auto res_at = [&](int r) {
-                        const int t = r * 64 + lq;
-                        const double tot = ((accw[t] + accw[NP + t]) + accw[2 * NP + t]) + accw[3 * NP + t];
-                        return tot - I.one_minus_W * rho[t];
-                    };
-                    double f[LM];
-#pragma unroll
-                    for (int r = 0; r < LM; ++r) f[r] = (slam[r * 64 + lq] - slmg[r * 64 + lq]) * res_at(r);
-                    __syncthreads();                  // every wavefront has read rho before any update
-                    const double b0 = jq == 0 ? bd0 : 0.0;
-                    auto bdr = [&](int r) { return (r == 0 ? b0 : 0.0) + (r == rl1 ? bdN : 0.0); };
-                    lane_chunk_solve<LM>(
-                        [&](int r) { return I.mu2 * ll[r * 64]; },
-                        [&](int r) { return lg[r * 64] + I.mu2 * (-(ll[r * 64] + lu[r * 64])) + I.mu1 * bdr(r); },
-                        [&](int r) { return I.mu2 * lu[r * 64]; }, f);
-                    double md = 0.0, mr = 0.0;
-#pragma unroll
-                    for (int r = 0; r < LM; ++r) {
-                        if ((r & 3) != w) continue;
-                        const int t = r * 64 + lq;
-                        const double z = res_at(r) + f[r];
-                        const double upd = alpha * (double)sdch[t] + beta * z;
-                        sdch[t] = (float)upd;
-                        const double nw = rho[t] + upd;
-                        rho[t] = nw;
-                        md = fmax(md, fabs(z));
-                        mr = fmax(mr, fabs(nw));
-                    }
-#pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) {
-                        md = fmax(md, __shfl_xor(md, o, 64));
-                        mr = fmax(mr, __shfl_xor(mr, o, 64));
-                    }
-                    if ((threadIdx.x & 63) == 0) {
-                        red[w] = md;
-                        red[8 + w] = mr;
-                    }
-                }
-                __syncthreads();                      // the rho update and its norms visible to the tile
-            }
-            const double md = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-            const double mr = fmax(fmax(red[8], red[9]), fmax(red[10], red[11]));
-            ++it;
-            const float qprev = Cs.q1, qprev2 = Cs.q2, qprev3 = Cs.q3;
-            const float q = (float)(mr > 0.0 ? md / mr : md);
-            cheb_record(Cs, q);
-            converged = pred_stop(md, mr, q, qprev, qprev2, qprev3, it, A.tol);
-            if (converged || it >= A.maxit) break;
-        }
-        sweep(true);                                  // E* of the final iterate
-    } else {
-        double lam[M], lmg[M];
-#pragma unroll
-        for (int r = 0; r < M; ++r) {
-            const int j = j0 + r;
-            const bool in = j < N;
-            lam[r] = in ? C[C_LAM * N1 + j] : 1.0;
-            lmg[r] = in ? C[C_LMG * N1 + j] : 0.0;
-        }
-        float dch[M];                             // previous update (steers the next one only)
-#pragma unroll
-        for (int r = 0; r < M; ++r) dch[r] = 0.0f;
-        // One sweep over the pairs from the current rho, v_p = T_p^{-1} [r_p -
-        // (Lam - G + mu^2 L + mu B) rho]: accumulates sum_p omega_p v_p into acc,
-        // or (final) writes E*_p = rho + v_p of the final iterate.
-        auto sweep = [&](double (&acc)[M], bool final_sweep) {
-            double rnext[M];
-#pragma unroll
-            for (int r = 0; r < M; ++r) {
-                acc[r] = 0.0;
-                rnext[r] = Rt[j0 + r];              // right-hand side of pair 0
-            }
-            for (int p = 0; p < P; ++p) {
-                const double m1 = mu[p], m2 = m1 * m1, wp = om[p];
-                double rcur[M];
-#pragma unroll
-                for (int r = 0; r < M; ++r) {       // this pair's right-hand side; fetch the next one
-                    rcur[r] = rnext[r];
-                    if (p + 1 < P) rnext[r] = Rt[(size_t)(p + 1) * NP + j0 + r];
-                }
-                double b[M], y[M], v[M];
-#pragma unroll
-                for (int r = 0; r < M; ++r) {
-                    const int j = j0 + r;
-                    const int t = r * W + k;
-                    if (j < N) {
-                        const double ll = sLl[t], lu = sLu[t];
-                        const double bdj = (j == 0 ? bd0 : 0.0) + (j == N - 1 ? bdN : 0.0);
-                        b[r] = lam[r] + m2 * (-(ll + lu)) + m1 * bdj;
-                        const double rj = rho[t];
-                        double rl = rj, rn = rj;   // boundary rows: ll or lu is 0
-                        if (j > 0) rl = (r > 0) ? rho[t - W] : rho[(M - 1) * W + k - 1];
-                        if (j < N - 1) rn = (r < M - 1) ? rho[t + W] : rho[k + 1];
-                        const double q = ll * (rl - rj) + lu * (rn - rj);   // difference form (low rounding floor)
-                        y[r] = rcur[r] - lmg[r] * rj - m2 * q - m1 * bdj * rj;
-                    } else {
-                        b[r] = 1.0;
-                        y[r] = 0.0;
-                    }
-                }
-                tri_factor_solve<W, M>(m2, sLl, sLu, b, y, v, sh, ph);
-                if (final_sweep) {
-                    double *ep = Et + (size_t)p * NP;
-#pragma unroll
-                    for (int r = 0; r < M; ++r) ep[j0 + r] = rho[r * W + k] + v[r];
-                } else {
-#pragma unroll
-                    for (int r = 0; r < M; ++r) acc[r] += wp * v[r];
-                }
-            }
-        };
-        while (true) {
-            double acc[M];
-            sweep(acc, false);
-            // res = sum_p omega_p v_p - (1 - W) rho;  rho += res + D^{-1} (G res).
-            // Every operator is factored and solved in one call (one barrier); the
-            // diffusion operator is factored again each iteration rather than held
-            // in registers across the pair loop (one factorisation per P solves).
-            double rl[M], d[M], f[M];
-            {
-                double b[M];
-#pragma unroll
-                for (int r = 0; r < M; ++r) {
-                    const int j = j0 + r;
-                    const bool in = j < N;
-                    rl[r] = in ? acc[r] - I.one_minus_W * rho[r * W + k] : 0.0;
-                    const int t = r * W + k;
-                    const double bdj = (j == 0 ? bd0 : 0.0) + (j == N - 1 ? bdN : 0.0);
-                    d[r] = in ? (lam[r] - lmg[r]) * rl[r] : 0.0;                 // G res
-                    b[r] = in ? lmg[r] + I.mu2 * (-(sLl[t] + sLu[t])) + I.mu1 * bdj : 1.0;
-                }
-                tri_factor_solve<W, M>(I.mu2, sLl, sLu, b, d, f, sh, ph);
-            }
-            double alpha, beta;
-            cheb_coeffs(Cs, A.accel, A.tol, alpha, beta);
-            double md = 0.0, mr = 0.0;
-#pragma unroll
-            for (int r = 0; r < M; ++r) {
-                if (j0 + r < N) {
-                    const int t = r * W + k;
-                    const double z = rl[r] + f[r];
-                    const double upd = alpha * (double)dch[r] + beta * z;
-                    dch[r] = (float)upd;
-                    const double nw = rho[t] + upd;
-                    rho[t] = nw;
-                    md = fmax(md, fabs(z));
-                    mr = fmax(mr, fabs(nw));
-                }
-            }
-            tile_max2<W>(md, mr, sh);
-            tsync<W>();                               // rho update visible to the tile
-            ++it;
-            const float qprev = Cs.q1, qprev2 = Cs.q2, qprev3 = Cs.q3;
-            const float q = (float)(mr > 0.0 ? md / mr : md);
-            cheb_record(Cs, q);
-            converged = pred_stop(md, mr, q, qprev, qprev2, qprev3, it, A.tol);
-            if (converged || it >= A.maxit) break;
-        }
-        {
-            double acc[M];
-            sweep(acc, true);                         // E* of the final iterate
-        }
-    }
-    for (int j = k; j < N; j += W) rp[j] = rho[lpos(j)];   // next step's starting iterate
-    tsync<W>();                                   // E* visible to the tile
-    if (k == 0) {
+        for (int r = 0; r < M; ++r) ep[r] = x[r];
+    });
+    if ((NW == 1 ? (threadIdx.x & 63) : threadIdx.x) == 0) {
+        int *st = A.istat + 8 * i;
         st[0] = it;
         st[1] = converged;
+        if (!converged) atomicOr(A.sticky, GRTE_ERRF_PRED_NOCONV);
     }
-
-    if (k == 0 && !converged) atomicOr(A.sticky, GRTE_ERRF_PRED_NOCONV);
 }
 
-template <int W, int M, bool F32, int LMW = 4 * M>
+// the correction's systems of instance i, one pair per wavefront at a time;
+// E^{n+1} replaces E* in the pair scratch
+template <int NW, int M>
 __device__ __forceinline__ void corr_solve(const BatchArgs &A, int i, double *sm)
 {
-    constexpr int NP = 64 * (W == BNT ? LMW : M);
+    constexpr int NP = 64 * M;
     const BInst I = A.inst[i];
     const int N = I.N, P = I.P, N1 = N + 1;
-    const int k = opaque(tile_lane<W>());   // opaque: per-thread addresses are formed per instance, not held across the queue loop
-    const int j0 = k * M;
-    const double *Tn = A.T + I.oT;
-    BState<F32> S;
-    S.P = I.P;
-    S.N = I.N;
-    S.ac = I.a * I.c;
-    S.Tn = Tn;
-    S.E = F32 ? nullptr : A.E + I.oE;
-    S.O = F32 ? nullptr : A.O + I.oO;
-    S.E32 = F32 ? A.E32 + I.oE : nullptr;
-    S.O32 = F32 ? A.O32 + I.oO : nullptr;
+    const int tid = NW == 1 ? (threadIdx.x & 63) : threadIdx.x;
+    const int w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const double *mu = A.mu + I.oP;
-    double *C = A.cells + I.oC;
-    // Per-pair global arrays are pair-major in cell order: thread k's rows
-    // j0 .. j0+M-1 are contiguous, so its loads and stores are wide and the
-    // later per-cell phases read along cells.
-    double *Rt = A.pairs + I.oR;                  // right-hand sides
-    double *Et = Rt + (size_t)P * I.NPa;          // E* (prediction), then E^{n+1} (correction)
-    constexpr bool WG = (W == BNT);
-    constexpr int LM = WG ? LMW : M;
-    auto lpos = [](int j) { return (j % LM) * 64 + j / LM; };
-    double *sLl = sm + NP, *sLu = sm + 2 * NP, *sh = sm + 3 * NP;
-    double *slam = WG ? sm + 3 * NP : nullptr;
-    int ph = 0;
-    for (int j = k; j < NP; j += W) {
-        const int t = lpos(j);
+    const double *C = A.cells + I.oC;
+    const double *Rt = A.pairs + I.oR;
+    double *Et = A.pairs + I.oR + (size_t)P * I.NPa;
+    double *sLl = sm, *sLu = sm + NP, *slam = sm + 2 * NP;
+    for (int j = tid; j < NP; j += 64 * NW) {
+        const int t = (j % M) * 64 + j / M;
         const bool in = j < N;
         sLl[t] = in ? C[C_LL * N1 + j] : 0.0;
         sLu[t] = in ? C[C_LU * N1 + j] : 0.0;
-        if constexpr (WG) slam[t] = in ? C[C_LAM * N1 + j] : 1.0;
+        slam[t] = in ? C[C_LAM * N1 + j] : 1.0;
     }
-    tsync<W>();
-    const double cb0 = C[C_BD * N1 + 0], cbN = C[C_BD * N1 + N - 1];
-    if constexpr (WG) {
-        // wavefront w solves pairs w, w + 4, ... alone; E*, no longer needed, takes E^{n+1}
-        const int w = threadIdx.x >> 6;
-        auto load_r = [&](int p, double (&v)[LM]) {   // padding rows hold zeros
-            const double *src = Rt + (size_t)p * NP + opaque(threadIdx.x & 63) * LM;
+    tile_sync<NW>();
+    const double bd0 = C[C_BD * N1 + 0], bdN = C[C_BD * N1 + N - 1];
+    for (int p = w; p < P; p += NW) {
+        const double m1 = mu[p], m2 = m1 * m1;
+        const int l = opaque(threadIdx.x & 63), j0 = l * M, rl1 = N - 1 - j0;
+        const double *ll = sLl + l, *lu = sLu + l, *la = slam + l;
+        const double *src = Rt + (size_t)p * NP + j0;      // padding rows hold zeros
+        double x[M], inv[M - 1];
+        LaneRed F;
 #pragma unroll
-            for (int r = 0; r < LM; ++r) v[r] = src[r];
-        };
-        double rnext[LM];
-        if (w < P) load_r(w, rnext);
-        for (int p = w; p < P; p += 4) {
-            const double m1 = mu[p], m2 = m1 * m1;
-            double x[LM];
+        for (int r = 0; r < M; ++r) x[r] = src[r];
+        const double b0 = l == 0 ? bd0 : 0.0;
+        lane_factor<M>([&](int q) { return m2 * ll[q * 64]; },
+                       [&](int q) {
+                           const double bd = (q == 0 ? b0 : 0.0) + (q == rl1 ? bdN : 0.0);
+                           return la[q * 64] + m2 * (-(ll[q * 64] + lu[q * 64])) + m1 * bd;
+                       },
+                       [&](int q) { return m2 * lu[q * 64]; }, inv, F);
+        lane_solve<M>(m2, [&](int q) { return ll[q * 64]; }, [&](int q) { return lu[q * 64]; }, inv, F, x,
+                      [](int) {});
+        double *ep = Et + (size_t)p * NP + j0;
 #pragma unroll
-            for (int r = 0; r < LM; ++r) x[r] = rnext[r];
-            if (p + 4 < P) load_r(p + 4, rnext);
-            const int lq = opaque(threadIdx.x & 63), jq = lq * LM, rl1 = N - 1 - jq;
-            const double *ll = sLl + lq, *lu = sLu + lq, *la = slam + lq;
-            const double c0 = jq == 0 ? cb0 : 0.0;
-            auto bdc = [&](int r) { return (r == 0 ? c0 : 0.0) + (r == rl1 ? cbN : 0.0); };
-            lane_chunk_solve<LM>(
-                [&](int r) { return m2 * ll[r * 64]; },
-                [&](int r) { return la[r * 64] + m2 * (-(ll[r * 64] + lu[r * 64])) + m1 * bdc(r); },
-                [&](int r) { return m2 * lu[r * 64]; }, x);
-            double *ep = Et + (size_t)p * NP + jq;
-#pragma unroll
-            for (int r = 0; r < LM; ++r) ep[r] = x[r];
-        }
-    } else {
-        double lam[M];
-#pragma unroll
-        for (int r = 0; r < M; ++r) lam[r] = (j0 + r < N) ? C[C_LAM * N1 + j0 + r] : 1.0;
-        for (int p = 0; p < P; ++p) {
-            const double m1 = mu[p], m2 = m1 * m1;
-            const double *rp = Rt + (size_t)p * NP;
-            double b[M], d[M], x[M];
-#pragma unroll
-            for (int r = 0; r < M; ++r) {
-                const int j = j0 + r;
-                const int t = r * W + k;
-                if (j < N) {
-                    const double bdj = (j == 0 ? cb0 : 0.0) + (j == N - 1 ? cbN : 0.0);
-                    b[r] = lam[r] + m2 * (-(sLl[t] + sLu[t])) + m1 * bdj;
-                    d[r] = rp[j];
-                } else {
-                    b[r] = 1.0;
-                    d[r] = 0.0;
-                }
-            }
-            tri_factor_solve<W, M>(m2, sLl, sLu, b, d, x, sh, ph);
-            double *ep = Et + (size_t)p * NP;   // E*, no longer needed, takes E^{n+1}
-#pragma unroll
-            for (int r = 0; r < M; ++r) ep[j0 + r] = x[r];
-        }
+        for (int r = 0; r < M; ++r) ep[r] = x[r];
     }
-    tsync<W>();
-
+    tile_sync<NW>();
 }
 
 // binary64 state <-> binary32 storage of every instance (one block per
@@ -1073,74 +685,38 @@ __global__ void __launch_bounds__(CB) cells_kernel(BatchArgs A)
 }
 static_assert(CB % 64 == 0 && CB <= 512, "per-cell blocks: whole wavefronts, at most eight");
 
-// the two per-slab solves: work-group tiles first (largest work first), then
-// wavefront tiles; PH 0: the prediction, 1: the correction
-template <int PH, bool F32>
+// the two per-slab solves, one work-group per work-group tile (largest work first),
+// then NWB wavefront tiles per work-group; PH 0: the prediction, 1: the correction
+template <int PH, int NW, int M>
+__device__ __forceinline__ void slab_solve(const BatchArgs &A, int i, double *sm)
+{
+    if constexpr (PH == 0) pred_solve<NW, M>(A, i, sm);
+    else corr_solve<NW, M>(A, i, sm);
+}
+
+template <int PH, int M = 4>
+__device__ __forceinline__ void slab_rows(const BatchArgs &A, int i, int rows, double *sm)
+{
+    if (rows == M) slab_solve<PH, NWB, M>(A, i, sm);
+    else if constexpr (M + 2 <= BMAX_N / 64) slab_rows<PH, M + 2>(A, i, rows, sm);
+}
+
+template <int PH>
 __global__ void __launch_bounds__(BNT) solve_kernel(BatchArgs A)
 {
     extern __shared__ double smem[];
-    __shared__ int s_q;
-    int *queue = A.queue + 2 * PH;
-    while (true) {
-        if (threadIdx.x == 0) s_q = atomicAdd(&queue[0], 1);
-        __syncthreads();
-        const int q = __builtin_amdgcn_readfirstlane(s_q);   // uniform: instance data in SGPRs
-        __syncthreads();
-        if (q >= A.n_wg) break;
+    const int q = blockIdx.x;
+    if (q < A.n_wg) {
         const int i = A.order[q];
-        if constexpr (PH == 0) {
-            switch (A.inst[i].M) {   // rows per lane
-            case 4: pred_solve<BNT, 1, F32, 4>(A, i, smem); break;
-            case 6: pred_solve<BNT, 1, F32, 6>(A, i, smem); break;
-            case 8: pred_solve<BNT, 2, F32, 8>(A, i, smem); break;
-            case 10: pred_solve<BNT, 1, F32, 10>(A, i, smem); break;
-            case 12: pred_solve<BNT, 3, F32, 12>(A, i, smem); break;
-            case 14: pred_solve<BNT, 1, F32, 14>(A, i, smem); break;
-            case 16: pred_solve<BNT, 4, F32, 16>(A, i, smem); break;
-            case 18: pred_solve<BNT, 1, F32, 18>(A, i, smem); break;
-            case 20: pred_solve<BNT, 5, F32, 20>(A, i, smem); break;
-            case 22: pred_solve<BNT, 1, F32, 22>(A, i, smem); break;
-            case 24: pred_solve<BNT, 6, F32, 24>(A, i, smem); break;
-            case 26: pred_solve<BNT, 1, F32, 26>(A, i, smem); break;
-            case 28: pred_solve<BNT, 7, F32, 28>(A, i, smem); break;
-            case 30: pred_solve<BNT, 1, F32, 30>(A, i, smem); break;
-            case 32: pred_solve<BNT, 8, F32, 32>(A, i, smem); break;
-            }
-        } else {
-            switch (A.inst[i].M) {
-            case 4: corr_solve<BNT, 1, F32, 4>(A, i, smem); break;
-            case 6: corr_solve<BNT, 1, F32, 6>(A, i, smem); break;
-            case 8: corr_solve<BNT, 2, F32, 8>(A, i, smem); break;
-            case 10: corr_solve<BNT, 1, F32, 10>(A, i, smem); break;
-            case 12: corr_solve<BNT, 3, F32, 12>(A, i, smem); break;
-            case 14: corr_solve<BNT, 1, F32, 14>(A, i, smem); break;
-            case 16: corr_solve<BNT, 4, F32, 16>(A, i, smem); break;
-            case 18: corr_solve<BNT, 1, F32, 18>(A, i, smem); break;
-            case 20: corr_solve<BNT, 5, F32, 20>(A, i, smem); break;
-            case 22: corr_solve<BNT, 1, F32, 22>(A, i, smem); break;
-            case 24: corr_solve<BNT, 6, F32, 24>(A, i, smem); break;
-            case 26: corr_solve<BNT, 1, F32, 26>(A, i, smem); break;
-            case 28: corr_solve<BNT, 7, F32, 28>(A, i, smem); break;
-            case 30: corr_solve<BNT, 1, F32, 30>(A, i, smem); break;
-            case 32: corr_solve<BNT, 8, F32, 32>(A, i, smem); break;
-            }
-        }
+        slab_rows<PH>(A, i, A.inst[i].M, smem);
+        return;
     }
-    double *wsm = smem + (threadIdx.x >> 6) * LDS_WAVE;
-    while (true) {
-        int q = 0;
-        if ((threadIdx.x & 63) == 0) q = atomicAdd(&queue[1], 1);
-        q = __builtin_amdgcn_readfirstlane(q);
-        if (q >= A.n_wave) break;
-        const int i = A.order[A.n_wg + q];
-        if constexpr (PH == 0) {
-            if (A.inst[i].M == 2) pred_solve<WAVE, 2, F32>(A, i, wsm);
-            else pred_solve<WAVE, 4, F32>(A, i, wsm);
-        } else {
-            if (A.inst[i].M == 2) corr_solve<WAVE, 2, F32>(A, i, wsm);
-            else corr_solve<WAVE, 4, F32>(A, i, wsm);
-        }
-    }
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), v = (q - A.n_wg) * NWB + w;
+    if (v >= A.n_wave) return;
+    const int i = A.order[A.n_wg + v];
+    double *wsm = smem + w * LDS_WAVE;
+    if (A.inst[i].M == 2) slab_solve<PH, 1, 2>(A, i, wsm);
+    else slab_solve<PH, 1, 4>(A, i, wsm);
 }
 
 // the energy balance of every slab: its blocks' partial sums in block order,
@@ -1165,11 +741,10 @@ __global__ void __launch_bounds__(256) batch_energy(BatchArgs A)
     en[3] = (ea - eb) + fdt;
 }
 
-// queue heads and per-instance counters cleared by a kernel (not a memset node)
-__global__ void batch_reset(int *queue, int *istat, int n8)
+// per-instance counters cleared by a kernel (not a memset node)
+__global__ void batch_reset(int *istat, int n8)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < 4) queue[t] = 0;
     if (t < n8) istat[t] = 0;
 }
 
@@ -1224,7 +799,7 @@ struct grte_batch {
     hipStream_t stream = nullptr;
     std::vector<void *> allocs;
     BInst *d_inst = nullptr;
-    int *d_order = nullptr, *d_queue = nullptr, *d_istat = nullptr;
+    int *d_order = nullptr, *d_istat = nullptr;
     int2 *d_cblk = nullptr;                    // blocks of the per-cell kernels
     double *d_epart = nullptr;                 // their energy partial sums (2 per block)
     int n_cblk = 0;
@@ -1236,6 +811,7 @@ struct grte_batch {
     int f32 = 0;
     double *sigma0 = nullptr, *mu = nullptr, *omega = nullptr, *bL = nullptr, *bR = nullptr;
     double *cells = nullptr, *pairs = nullptr;
+    double *fac = nullptr;                     // the prediction's factorisations (P + 1 per instance)
     long long pairs_doubles = 0;               // size of the pair scratch
     double *rprev = nullptr;                   // per cell: the last prediction's rho*
     double *d_energy = nullptr;                // per instance: energy balance of the last step (4)
@@ -1326,14 +902,13 @@ BatchArgs make_args(const grte_batch *b, int src)
     A.n_wave = b->n_wave;
     A.inst = b->d_inst;
     A.order = b->d_order;
-    A.queue = b->d_queue;
     A.cblk = b->d_cblk;
     A.epart = b->d_epart;
     A.n_inst = b->n;
     A.E = b->E[src]; A.O = b->O[src]; A.T = b->T[src];
     A.E2 = b->E[1 - src]; A.O2 = b->O[1 - src]; A.T2 = b->T[1 - src];
     A.sigma0 = b->sigma0; A.mu = b->mu; A.omega = b->omega; A.bL = b->bL; A.bR = b->bR;
-    A.cells = b->cells; A.pairs = b->pairs; A.istat = b->d_istat;
+    A.cells = b->cells; A.pairs = b->pairs; A.fac = b->fac; A.istat = b->d_istat;
     A.tol = b->tol; A.maxit = b->maxit; A.newton_maxit = b->newton_maxit; A.accel = b->accel;
     A.f32 = b->f32;
     A.rprev = b->rprev;
@@ -1352,27 +927,26 @@ grte_status enqueue_step(grte_batch *b, hipStream_t s, int src, const hipEvent_t
 {
     BatchArgs A = make_args(b, src);
     const int n8 = 8 * b->n;
-    hipLaunchKernelGGL(batch_reset, dim3((unsigned)((std::max(n8, 4) + 255) / 256)), dim3(256), 0, s,
-                       b->d_queue, b->d_istat, n8);
+    hipLaunchKernelGGL(batch_reset, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, b->d_istat, n8);
     BCHK(hipGetLastError());
-    const dim3 cg((unsigned)b->n_cblk), sg((unsigned)b->grid), eg((unsigned)((b->n + 255) / 256));
+    const dim3 cg((unsigned)b->n_cblk), sg((unsigned)(b->n_wg + (b->n_wave + NWB - 1) / NWB)), eg((unsigned)((b->n + 255) / 256));
     if (b->f32) {
         hipLaunchKernelGGL((cells_kernel<CP_PRED, true>), cg, dim3(CB), 0, s, A);
         if (kev) BCHK(hipEventRecord(kev[0], s));
-        hipLaunchKernelGGL((solve_kernel<0, true>), sg, dim3(BNT), BATCH_LDS, s, A);
+        hipLaunchKernelGGL(solve_kernel<0>, sg, dim3(BNT), BATCH_LDS, s, A);
         if (kev) BCHK(hipEventRecord(kev[1], s));
         hipLaunchKernelGGL((cells_kernel<CP_NEWTON, true>), cg, dim3(CB), 0, s, A);
         hipLaunchKernelGGL((cells_kernel<CP_CORR, true>), cg, dim3(CB), 0, s, A);
-        hipLaunchKernelGGL((solve_kernel<1, true>), sg, dim3(BNT), BATCH_LDS, s, A);
+        hipLaunchKernelGGL(solve_kernel<1>, sg, dim3(BNT), BATCH_LDS, s, A);
         hipLaunchKernelGGL((cells_kernel<CP_PROJECT, true>), cg, dim3(CB), 0, s, A);
     } else {
         hipLaunchKernelGGL((cells_kernel<CP_PRED, false>), cg, dim3(CB), 0, s, A);
         if (kev) BCHK(hipEventRecord(kev[0], s));
-        hipLaunchKernelGGL((solve_kernel<0, false>), sg, dim3(BNT), BATCH_LDS, s, A);
+        hipLaunchKernelGGL(solve_kernel<0>, sg, dim3(BNT), BATCH_LDS, s, A);
         if (kev) BCHK(hipEventRecord(kev[1], s));
         hipLaunchKernelGGL((cells_kernel<CP_NEWTON, false>), cg, dim3(CB), 0, s, A);
         hipLaunchKernelGGL((cells_kernel<CP_CORR, false>), cg, dim3(CB), 0, s, A);
-        hipLaunchKernelGGL((solve_kernel<1, false>), sg, dim3(BNT), BATCH_LDS, s, A);
+        hipLaunchKernelGGL(solve_kernel<1>, sg, dim3(BNT), BATCH_LDS, s, A);
         hipLaunchKernelGGL((cells_kernel<CP_PROJECT, false>), cg, dim3(CB), 0, s, A);
     }
     BCHK(hipGetLastError());
@@ -1481,7 +1055,7 @@ grte_status grte_batch_create(int n, const grte_instance *inst, const double *mu
     }
     b->h_inst.resize(n);
     b->cost.resize(n);
-    long long oE = 0, oO = 0, oT = 0, oP = 0, oC = 0, oR = 0;
+    long long oE = 0, oO = 0, oT = 0, oP = 0, oC = 0, oR = 0, oF = 0;
     for (int i = 0; i < n; ++i) {
         const grte_instance &d = inst[i];
         BInst &I = b->h_inst[i];
@@ -1501,7 +1075,7 @@ grte_status grte_batch_create(int n, const grte_instance *inst, const double *mu
         I.one_minus_W = (1.0 - s) - e;
         I.mu1 = m1;
         I.mu2 = m2;
-        I.oE = oE; I.oO = oO; I.oT = oT; I.oP = oP; I.oC = oC; I.oR = oR;
+        I.oE = oE; I.oO = oO; I.oT = oT; I.oP = oP; I.oC = oC; I.oR = oR; I.oF = oF;
         I.NPa = 64LL * tile_rows(I.N, BNT);   // also covers every wavefront tile (N <= 256)
         oE += (long long)I.N * I.P;
         oO += (long long)(I.N + 1) * I.P;
@@ -1509,6 +1083,7 @@ grte_status grte_batch_create(int n, const grte_instance *inst, const double *mu
         oP += I.P;
         oC += (long long)NCA * (I.N + 1);
         oR += 2LL * I.P * I.NPa;
+        oF += (I.P + 1LL) * fac_doubles(tile_rows(I.N, BNT));
         b->cost[i] = (double)I.N * I.P;
     }
     b->tot_E = oE; b->tot_O = oO; b->tot_cells = oT; b->tot_pairs = oP;
@@ -1530,7 +1105,6 @@ grte_status grte_batch_create(int n, const grte_instance *inst, const double *mu
         st = GRTE_E_HIP;
     if (st == GRTE_OK) st = balloc(b, &b->d_inst, n);
     if (st == GRTE_OK) st = balloc(b, &b->d_order, n);
-    if (st == GRTE_OK) st = balloc(b, &b->d_queue, 4);
     if (st == GRTE_OK) st = balloc(b, &b->d_istat, (size_t)8 * n);
     for (int q = 0; q < 2 && st == GRTE_OK; ++q) {
         st = balloc(b, &b->E[q], oE);
@@ -1544,6 +1118,7 @@ grte_status grte_batch_create(int n, const grte_instance *inst, const double *mu
     if (st == GRTE_OK) st = balloc(b, &b->bR, oP);
     if (st == GRTE_OK) st = balloc(b, &b->cells, oC);
     if (st == GRTE_OK) st = balloc(b, &b->pairs, oR);
+    if (st == GRTE_OK) st = balloc(b, &b->fac, oF);
     b->pairs_doubles = oR;
     if (st == GRTE_OK) st = balloc(b, &b->rprev, oT);
     if (st == GRTE_OK) st = balloc(b, &b->d_energy, (size_t)4 * n);
@@ -1552,8 +1127,7 @@ grte_status grte_batch_create(int n, const grte_instance *inst, const double *mu
                           hipMemset(b->d_energy, 0, (size_t)4 * n * sizeof(double)) != hipSuccess))
         st = GRTE_E_HIP;
     if (st != GRTE_OK) { grte_batch_destroy(b); return st; }
-    const void *solvers[] = {(const void *)solve_kernel<0, false>, (const void *)solve_kernel<1, false>,
-                             (const void *)solve_kernel<0, true>, (const void *)solve_kernel<1, true>};
+    const void *solvers[] = {(const void *)solve_kernel<0>, (const void *)solve_kernel<1>};
     int nbmin = 1 << 30;
     for (const void *f : solvers) {
         int nb = 0;
@@ -1838,7 +1412,7 @@ grte_status grte_batch_tune(grte_batch *b, int trials, grte_batch_tuning *best)
     }
     update_cost(b, h);
     int nb = 0;
-    const void *kfn = b->f32 ? (const void *)solve_kernel<0, true> : (const void *)solve_kernel<0, false>;
+    const void *kfn = (const void *)solve_kernel<0>;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kfn, BNT, BATCH_LDS) != hipSuccess) nb = 1;
     const int waves[] = {0, 128, 256};
     std::vector<int> grids;
