@@ -4,13 +4,10 @@
 // Training data are rows of six binary32 values, (f_0..f_4, log(T^{n+1}/T^n)),
 // written by grte_log_pairs from converged steps of the solver itself.  One
 // training step on a minibatch of B rows is two kernels:
-//   mlp_grad_kernel  one wavefront per 64 rows: forward and backward pass of
-//                    every row in registers (binary32), the per-row vectors
-//                    (h1, h2, dL/dz1, dL/dz2, x) in LDS, then each lane forms
-//                    whole gradient entries as fixed-order sums over the 64
-//                    rows -> per-block partial gradient (deterministic, no
-//                    atomics);
-//   mlp_adam_kernel  sums the partials in block order, applies Adam with bias
+//   mlp_grad_kernel  forward and backward pass of 16 rows at a time, the three
+//                    64 x 64 products on the binary32 matrix instructions ->
+//                    per-block partial gradient (deterministic, no atomics);
+//   mlp_adam_kernel  sums the partials in a fixed order, applies Adam with bias
 //                    correction to the binary32 master parameters and writes
 //                    their bfloat16 copy (round to nearest even).
 // The loss is the mean squared error of the standardised target.
@@ -28,7 +25,8 @@
 #include "mlp_common.hpp"
 
 namespace {
-constexpr int GB = 64;                 // rows per training block (one wavefront)
+constexpr int GROWS = 16;              // rows of one pass of a gradient block
+constexpr int GRAD_BLOCKS = 256;       // most gradient blocks of one minibatch (each takes rows until none is left)
 }
 
 // Workspace of grte_mlp_train_noalloc: per-block partial gradients, partial
@@ -37,7 +35,7 @@ constexpr int GB = 64;                 // rows per training block (one wavefront
 // for it: its address on a device comes from hipGetSymbolAddress, taken once
 // per device with that device current, and kept.
 constexpr int NOALLOC_MAX_BATCH = 16384;                      // rows per minibatch
-constexpr int NOALLOC_MAX_BLOCKS = NOALLOC_MAX_BATCH / GB;    // 256 gradient blocks
+constexpr int NOALLOC_MAX_BLOCKS = GRAD_BLOCKS;
 constexpr int NOALLOC_MAX_STEPS = 65536;                      // loss-history entries
 constexpr size_t NOALLOC_FLOATS =
     (size_t)NOALLOC_MAX_BLOCKS * MLP_NPARAM + NOALLOC_MAX_BLOCKS + NOALLOC_MAX_STEPS;   // 4.98 MB
@@ -46,114 +44,180 @@ static __device__ __align__(256) float scratch[NOALLOC_FLOATS];
 
 namespace {
 
-constexpr int HS = MLP_H + 1;          // padded LDS row stride (conflict-free)
-constexpr int NPAD = 4612;             // parameters in LDS, padded
+using f32x4 = __attribute__((ext_vector_type(4))) float;
+using f32x16 = __attribute__((ext_vector_type(16))) float;
+using bf16x8 = __attribute__((ext_vector_type(8))) __bf16;
 
-constexpr size_t grad_lds_bytes() { return (size_t)(NPAD + 4 * GB * HS + GB * 8 + 2 * GB) * sizeof(float); }
+int grad_blocks(int B) { return std::min((B + GROWS - 1) / GROWS, GRAD_BLOCKS); }
 
-__global__ void __launch_bounds__(GB) mlp_grad_kernel(const float *theta, const float *norm, const float *data,
-                                                      long long n, long long start, int B, float *gpart,
-                                                      float *lpart)
+// One gradient block: four wavefronts, GROWS rows at a time.  Lane l = 16 q + u of
+// wavefront w holds hidden unit 16 w + u of the rows 4 q .. 4 q + 3, in both layers and
+// both passes -- the result layout of the 16 x 16 x 4 matrix instruction, so activations,
+// their derivatives and the sums over rows stay in registers and only h1 and dL/dz2
+// pass through LDS, as operands.  The weights of the products are read once per block.
+//   z2 = h1 W2^T, dL/dh1 = dL/dz2 W2     (16 x 64 per wavefront's 16 columns)
+//   dL/dW2 = dL/dz2^T h1                 (16 rows of W2 per wavefront, sums kept over all rows)
+// Bound: the chain of one pass (weights and rows from memory, 32 dependent matrix
+// instructions, four barriers), hence the least rows per block that the instruction
+// takes and as many blocks as compute units.  4096 rows on an MI355X: 9.3 us; one
+// wavefront per 64 rows with each row's 64-unit vectors in one lane took 138 us.
+constexpr int GS = MLP_H + 4;          // LDS row stride
+
+__global__ void __launch_bounds__(256) mlp_grad_kernel(const float *theta, const float *norm, const float *data,
+                                                       long long n, long long start, int B, float *gpart,
+                                                       float *lpart)
 {
-    extern __shared__ float sm[];
-    float *sW = sm;
-    float *sH1 = sW + NPAD, *sH2 = sH1 + GB * HS, *sD2 = sH2 + GB * HS, *sD1 = sD2 + GB * HS;
-    float *sX = sD1 + GB * HS, *sDy = sX + GB * 8, *sL = sDy + GB;
-    const int t = threadIdx.x;
-    for (int e = t; e < MLP_NPARAM; e += GB) sW[e] = theta[e];
-    __syncthreads();
-    const int s = blockIdx.x * GB + t;
-    const bool valid = s < B;
-    float x[MLP_IN], tg = 0.0f;
-    {
-        const long long row = valid ? (start + s) % n : 0;
+    __shared__ __align__(16) float sH[GROWS * GS], sD[GROWS * GS], sY[4][GROWS], sX[GROWS][8];
+    const int t = threadIdx.x, w = t >> 6, u = t & 15, q = (t & 63) >> 4, unit = 16 * w + u;
+    // W2 as operands, k-slot (g, q, e) = input 16 g + 4 q + e
+    float wf[16], wb[16], w1[MLP_IN];
 #pragma unroll
-        for (int q = 0; q < MLP_IN; ++q) x[q] = valid ? (data[row * 6 + q] - norm[q]) / norm[MLP_IN + q] : 0.0f;
-        if (valid) tg = (data[row * 6 + 5] - norm[2 * MLP_IN]) / norm[2 * MLP_IN + 1];
-    }
-    // forward
-    float z1[MLP_H], h1[MLP_H], z2[MLP_H];
+    for (int g = 0; g < 4; ++g)
 #pragma unroll
-    for (int i = 0; i < MLP_H; ++i) {
-        float z = sW[MLP_OB1 + i];
-#pragma unroll
-        for (int q = 0; q < MLP_IN; ++q) z += sW[MLP_OW1 + MLP_IN * i + q] * x[q];
-        z1[i] = z;
-        h1[i] = gelu_f(z);
-        sH1[t * HS + i] = h1[i];
-    }
-    float y = sW[MLP_OB3];
-    for (int i = 0; i < MLP_H; ++i) {
-        float z = sW[MLP_OB2 + i];
-#pragma unroll
-        for (int j = 0; j < MLP_H; ++j) z += sW[MLP_OW2 + MLP_H * i + j] * h1[j];
-        z2[i] = z;
-        const float h2 = gelu_f(z);
-        sH2[t * HS + i] = h2;
-        y += sW[MLP_OW3 + i] * h2;
-    }
-    // backward: dL/dy, dL/dz2, dL/dz1
-    const float dy = valid ? 2.0f * (y - tg) / (float)B : 0.0f;
-    sDy[t] = dy;
-    sL[t] = valid ? (y - tg) * (y - tg) : 0.0f;
-#pragma unroll
-    for (int i = 0; i < MLP_H; ++i) {
-        const float d2 = dy * sW[MLP_OW3 + i] * gelu_prime_f(z2[i]);
-        z2[i] = d2;
-        sD2[t * HS + i] = d2;
-    }
-    for (int j = 0; j < MLP_H; ++j) {
-        float dh = 0.0f;
-#pragma unroll
-        for (int i = 0; i < MLP_H; ++i) dh += sW[MLP_OW2 + MLP_H * i + j] * z2[i];
-        sD1[t * HS + j] = dh * gelu_prime_f(z1[j]);
-    }
-#pragma unroll
-    for (int q = 0; q < MLP_IN; ++q) sX[t * 8 + q] = x[q];
-    __syncthreads();
-    // gradient entries of this block: fixed-order sums over its rows
-    float *g = gpart + (size_t)blockIdx.x * MLP_NPARAM;
-    for (int e = t; e < MLP_NPARAM; e += GB) {
-        float acc = 0.0f;
-        if (e < MLP_OB1) {                 // W1[i, q]
-            const int i = e / MLP_IN, q = e - (e / MLP_IN) * MLP_IN;
-            for (int r = 0; r < GB; ++r) acc += sD1[r * HS + i] * sX[r * 8 + q];
-        } else if (e < MLP_OW2) {          // b1[i]
-            const int i = e - MLP_OB1;
-            for (int r = 0; r < GB; ++r) acc += sD1[r * HS + i];
-        } else if (e < MLP_OB2) {          // W2[i, j]
-            const int i = (e - MLP_OW2) / MLP_H, j = (e - MLP_OW2) - ((e - MLP_OW2) / MLP_H) * MLP_H;
-            for (int r = 0; r < GB; ++r) acc += sD2[r * HS + i] * sH1[r * HS + j];
-        } else if (e < MLP_OW3) {          // b2[i]
-            const int i = e - MLP_OB2;
-            for (int r = 0; r < GB; ++r) acc += sD2[r * HS + i];
-        } else if (e < MLP_OB3) {          // W3[i]
-            const int i = e - MLP_OW3;
-            for (int r = 0; r < GB; ++r) acc += sDy[r] * sH2[r * HS + i];
-        } else {                           // b3
-            for (int r = 0; r < GB; ++r) acc += sDy[r];
+        for (int e = 0; e < 4; ++e) {
+            wf[4 * g + e] = theta[MLP_OW2 + MLP_H * unit + 16 * g + 4 * q + e];
+            wb[4 * g + e] = theta[MLP_OW2 + MLP_H * (16 * g + 4 * q + e) + unit];
         }
-        g[e] = acc;
+#pragma unroll
+    for (int c = 0; c < MLP_IN; ++c) w1[c] = theta[MLP_OW1 + MLP_IN * unit + c];
+    const float b1 = theta[MLP_OB1 + unit], b2 = theta[MLP_OB2 + unit], w3 = theta[MLP_OW3 + unit], b3 = theta[MLP_OB3];
+    f32x4 gW2[4] = {};
+    float gW1[MLP_IN] = {}, gb1 = 0.0f, gb2 = 0.0f, gW3 = 0.0f, gb3 = 0.0f, loss = 0.0f;
+    for (int r0 = blockIdx.x * GROWS; r0 < B; r0 += gridDim.x * GROWS) {
+        if (t < GROWS * 6) {                           // standardised inputs and target
+            const int r = t / 6, c = t - 6 * r, k = c < MLP_IN ? c : 2 * MLP_IN;
+            float v = 0.0f;
+            if (r0 + r < B) v = (data[(start + r0 + r) % n * 6 + c] - norm[k]) / norm[c < MLP_IN ? k + MLP_IN : k + 1];
+            sX[r][c] = v;
+        }
+        __syncthreads();
+        float x[4][MLP_IN], d1[4], d2[4], h2[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float z = b1;
+#pragma unroll
+            for (int c = 0; c < MLP_IN; ++c) {
+                x[r][c] = sX[4 * q + r][c];
+                z = fmaf(w1[c], x[r][c], z);
+            }
+            sH[(4 * q + r) * GS + unit] = gelu_both(z, d1[r]);
+        }
+        __syncthreads();
+        f32x4 z2 = {b2, b2, b2, b2};
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 h = *reinterpret_cast<const float4 *>(&sH[u * GS + 16 * g + 4 * q]);
+            z2 = __builtin_amdgcn_mfma_f32_16x16x4f32(h.x, wf[4 * g], z2, 0, 0, 0);
+            z2 = __builtin_amdgcn_mfma_f32_16x16x4f32(h.y, wf[4 * g + 1], z2, 0, 0, 0);
+            z2 = __builtin_amdgcn_mfma_f32_16x16x4f32(h.z, wf[4 * g + 2], z2, 0, 0, 0);
+            z2 = __builtin_amdgcn_mfma_f32_16x16x4f32(h.w, wf[4 * g + 3], z2, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            h2[r] = gelu_both(z2[r], d2[r]);
+            float y = w3 * h2[r];                      // over the wavefront's 16 units
+            y += __shfl_xor(y, 1);
+            y += __shfl_xor(y, 2);
+            y += __shfl_xor(y, 4);
+            y += __shfl_xor(y, 8);
+            if (u == 0) sY[w][4 * q + r] = y;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 4 * q + r;
+            const float e = b3 + ((sY[0][row] + sY[1][row]) + (sY[2][row] + sY[3][row])) - sX[row][MLP_IN];
+            const bool in = r0 + row < B;
+            const float dy = in ? 2.0f * e / (float)B : 0.0f;
+            loss += in ? e * e : 0.0f;
+            gb3 += dy;
+            gW3 = fmaf(dy, h2[r], gW3);
+            d2[r] *= dy * w3;
+            gb2 += d2[r];
+            sD[row * GS + unit] = d2[r];
+        }
+        __syncthreads();
+        f32x4 dh = {};
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 d = *reinterpret_cast<const float4 *>(&sD[u * GS + 16 * g + 4 * q]);
+            dh = __builtin_amdgcn_mfma_f32_16x16x4f32(d.x, wb[4 * g], dh, 0, 0, 0);
+            dh = __builtin_amdgcn_mfma_f32_16x16x4f32(d.y, wb[4 * g + 1], dh, 0, 0, 0);
+            dh = __builtin_amdgcn_mfma_f32_16x16x4f32(d.z, wb[4 * g + 2], dh, 0, 0, 0);
+            dh = __builtin_amdgcn_mfma_f32_16x16x4f32(d.w, wb[4 * g + 3], dh, 0, 0, 0);
+        }
+#pragma unroll
+        for (int c = 0; c < GROWS / 4; ++c) {
+            const float d = sD[(4 * c + q) * GS + unit];
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                gW2[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(d, sH[(4 * c + q) * GS + 16 * g + u], gW2[g], 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float d = dh[r] * d1[r];
+            gb1 += d;
+#pragma unroll
+            for (int c = 0; c < MLP_IN; ++c) gW1[c] = fmaf(d, x[r][c], gW1[c]);
+        }
+        // (no barrier here: each array is written again only behind one that follows its last reads)
+    }
+    // the sums over the four lanes of a unit, then this block's gradient
+    auto rows = [](float v) {
+        v += __shfl_xor(v, 16);
+        return v + __shfl_xor(v, 32);
+    };
+    float *g = gpart + (size_t)blockIdx.x * MLP_NPARAM;
+#pragma unroll
+    for (int c = 0; c < MLP_IN; ++c) gW1[c] = rows(gW1[c]);
+    gb1 = rows(gb1);
+    gb2 = rows(gb2);
+    gW3 = rows(gW3);
+    gb3 = rows(gb3);
+    loss = rows(loss);
+    if (q == 0) {
+#pragma unroll
+        for (int c = 0; c < MLP_IN; ++c) g[MLP_OW1 + MLP_IN * unit + c] = gW1[c];
+        g[MLP_OB1 + unit] = gb1;
+        g[MLP_OB2 + unit] = gb2;
+        g[MLP_OW3 + unit] = gW3;
     }
     if (t == 0) {
-        float l = 0.0f;
-        for (int r = 0; r < GB; ++r) l += sL[r];
-        lpart[blockIdx.x] = l;
+        g[MLP_OB3] = gb3;
+        lpart[blockIdx.x] = loss;
     }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) g[MLP_OW2 + MLP_H * (16 * w + 4 * q + r) + 16 * k + u] = gW2[k][r];
 }
 
-__global__ void mlp_adam_kernel(float *theta, float *am, float *av, uint16_t *wbf, const float *gpart, int nblk,
-                                const float *lpart, int B, float *lhist, int hidx, float lr, float c1, float c2)
+// Adam on AE parameters per block: thread (a, s) sums the partials s, s + AS, .. of
+// parameter a, then the AS sums are joined in order.  Bound by the latency of the
+// partials' loads: 16 per thread in flight.  256 partials: 6.6 us (64 partials by one
+// thread per parameter: 20 us).
+constexpr int AE = 16, AS = 16;
+
+__global__ void __launch_bounds__(AE *AS) mlp_adam_kernel(float *theta, float *am, float *av, uint16_t *wbf,
+                                                          const float *gpart, int nblk, const float *lpart, int B,
+                                                          float *lhist, int hidx, float lr, float c1, float c2)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e == 0 && lhist) {
-        float l = 0.0f;
-        for (int b = 0; b < nblk; ++b) l += lpart[b];
-        lhist[hidx] = l / (float)B;
-    }
-    if (e >= MLP_NPARAM) return;
+    __shared__ float part[AS][AE + 1];
+    const int a = threadIdx.x % AE, s = threadIdx.x / AE, e = blockIdx.x * AE + a;
     float g = 0.0f;
-    for (int b = 0; b < nblk; ++b) g += gpart[(size_t)b * MLP_NPARAM + e];
+    if (e < MLP_NPARAM) {
+#pragma unroll 16
+        for (int b = s; b < nblk; b += AS) g += gpart[(size_t)b * MLP_NPARAM + e];
+    } else if (lhist && e == MLP_NPARAM) {             // the spare column of the last block: the loss
+        for (int b = s; b < nblk; b += AS) g += lpart[b];
+    }
+    part[s][a] = g;
+    __syncthreads();
+    if (s > 0) return;
+#pragma unroll
+    for (int k = 1; k < AS; ++k) g += part[k][a];
+    if (lhist && e == MLP_NPARAM) lhist[hidx] = g / (float)B;
+    if (e >= MLP_NPARAM) return;
     const float beta1 = 0.9f, beta2 = 0.999f;
     const float m = beta1 * am[e] + (1.0f - beta1) * g;
     const float v = beta2 * av[e] + (1.0f - beta2) * g * g;
@@ -164,6 +228,7 @@ __global__ void mlp_adam_kernel(float *theta, float *am, float *av, uint16_t *wb
     theta[e] = th;
     wbf[e] = f_to_bf16(th);
 }
+constexpr int ADAM_GRID = (MLP_NPARAM + AE) / AE;      // covers MLP_NPARAM + 1 columns
 
 __global__ void mlp_round_kernel(const float *theta, uint16_t *wbf)
 {
@@ -251,33 +316,19 @@ grte_status ensure_gpart(grte_mlp *m, int nblk)
     return GRTE_OK;
 }
 
-grte_status grad_lds_attribute()
-{
-    static bool lds_set = false;
-    if (!lds_set) {
-        MCHK(hipFuncSetAttribute((const void *)mlp_grad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)grad_lds_bytes()));
-        lds_set = true;
-    }
-    return GRTE_OK;
-}
-
-// per-block partial gradients and losses into gpart/lpart (nblk = ceil(B / GB) blocks)
+// per-block partial gradients and losses into gpart/lpart (grad_blocks(B) blocks)
 grte_status launch_grad_into(grte_mlp *m, const float *data, long long n, long long start, int B, float *gpart,
                              float *lpart)
 {
-    grte_status st = grad_lds_attribute();
-    if (st != GRTE_OK) return st;
-    const int nblk = (B + GB - 1) / GB;
-    hipLaunchKernelGGL(mlp_grad_kernel, dim3(nblk), dim3(GB), grad_lds_bytes(), m->stream, m->theta, m->norm, data,
-                       n, start, B, gpart, lpart);
+    hipLaunchKernelGGL(mlp_grad_kernel, dim3(grad_blocks(B)), dim3(256), 0, m->stream, m->theta, m->norm, data, n,
+                       start, B, gpart, lpart);
     MCHK(hipGetLastError());
     return GRTE_OK;
 }
 
 grte_status launch_grad(grte_mlp *m, const float *data, long long n, long long start, int B)
 {
-    const int nblk = (B + GB - 1) / GB;
+    const int nblk = grad_blocks(B);
     grte_status st = ensure_gpart(m, nblk);
     if (st != GRTE_OK) return st;
     return launch_grad_into(m, data, n, start, B, m->gpart, m->lpart);
@@ -289,7 +340,7 @@ grte_status launch_grad(grte_mlp *m, const float *data, long long n, long long s
 grte_status train_steps(grte_mlp *m, const float *data, long long n, int steps, int B, float lr, float *gpart,
                         float *lpart, float *lhist)
 {
-    const int nblk = (B + GB - 1) / GB;
+    const int nblk = grad_blocks(B);
     long long start = 0;
     for (int k = 0; k < steps; ++k) {
         grte_status st = launch_grad_into(m, data, n, start, B, gpart, lpart);
@@ -297,7 +348,7 @@ grte_status train_steps(grte_mlp *m, const float *data, long long n, int steps, 
         start = (start + B) % n;
         const int kk = ++m->adam_k;
         const float c1 = (float)(1.0 - std::pow(0.9, kk)), c2 = (float)(1.0 - std::pow(0.999, kk));
-        hipLaunchKernelGGL(mlp_adam_kernel, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, m->stream, m->theta,
+        hipLaunchKernelGGL(mlp_adam_kernel, dim3(ADAM_GRID), dim3(AE * AS), 0, m->stream, m->theta,
                            m->am, m->av, m->wbf, gpart, nblk, lpart, B, lhist, k, lr, c1, c2);
         MCHK(hipGetLastError());
     }
@@ -440,7 +491,7 @@ grte_status grte_mlp_grad(grte_mlp *m, const float *data, long long n, float *gr
     const int B = (int)n;
     grte_status st = launch_grad(m, data, n, 0, B);
     if (st != GRTE_OK) return st;
-    const int nblk = (B + GB - 1) / GB;
+    const int nblk = grad_blocks(B);
     std::vector<float> gp((size_t)nblk * MLP_NPARAM), lp(nblk);
     MCHK(hipMemcpyAsync(gp.data(), m->gpart, gp.size() * sizeof(float), hipMemcpyDeviceToHost, m->stream));
     MCHK(hipMemcpyAsync(lp.data(), m->lpart, lp.size() * sizeof(float), hipMemcpyDeviceToHost, m->stream));
@@ -463,7 +514,7 @@ grte_status grte_mlp_train(grte_mlp *m, const float *data, long long n, int step
 {
     if (!m || !data || n < 1 || steps < 1 || batch < 1 || batch > (1 << 20) || !(lr > 0)) return GRTE_E_INVAL;
     const int B = (int)std::min<long long>(batch, n);
-    const int nblk = (B + GB - 1) / GB;
+    const int nblk = grad_blocks(B);
     if (loss_hist && steps > m->hcap) {
         if (m->lhist) (void)hipFree(m->lhist);
         m->lhist = nullptr;
