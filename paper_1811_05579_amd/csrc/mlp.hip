@@ -272,21 +272,131 @@ __global__ void __launch_bounds__(256) mlp_norm_kernel(const float *data, long l
     }
 }
 
+// Inference: a wavefront takes 32 rows at a time through both layers on the 32 x 32 x 16
+// bfloat16 matrix instruction, units by rows, binary32 sums.  The weights are bfloat16;
+// each binary32 input is split into three bfloat16 terms whose sum it is (8 + 8 + 8 of
+// its 24 bits), so every product is exact and the sums are those of binary32 arithmetic.
+// Layer 1 is one instruction per 32 units: 15 slots of the 16 hold the terms of the five
+// inputs, the last the bias.  Lane 32 h + c gets the units 8 (r / 4) + 4 h + r % 4 of row
+// c, which are the operand of layer 2 as they stand (W2's columns in the same order), so
+// nothing passes through LDS but b2 and W3.
+// Bound: the gelu evaluations (128 per row, 14 vector instructions each, one of them a
+// quarter-rate exp2); 2^20 rows on an MI355X: 85 us per call (213 us with one row per lane
+// and vector products); two or three wavefronts per SIMD make no difference.
+struct Split {
+    unsigned hi, mid, lo;              // bfloat16 terms in the upper halves
+};
+__device__ __forceinline__ Split split3(float v)
+{
+    Split s;
+    s.hi = __float_as_uint(v);
+    const float r = v - __uint_as_float(s.hi & 0xffff0000u);
+    s.mid = __float_as_uint(r);
+    s.lo = __float_as_uint(r - __uint_as_float(s.mid & 0xffff0000u));
+    return s;
+}
+// the upper halves of a and b as two bfloat16 values, a first
+__device__ __forceinline__ unsigned pack_hi(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
 __global__ void __launch_bounds__(256) mlp_predict_kernel(const uint16_t *wbf, const float *norm, const float *data,
                                                           long long n, float *y)
 {
-    __shared__ uint16_t sW[MLP_NPARAM + 3];
-    __shared__ float sN[MLP_NNORM];
-    for (int e = threadIdx.x; e < MLP_NPARAM; e += 256) sW[e] = wbf[e];
-    if (threadIdx.x < MLP_NNORM) sN[threadIdx.x] = norm[threadIdx.x];
-    __syncthreads();
-    const long long r = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (r >= n) return;
-    float f[MLP_IN];
+    __shared__ __align__(16) float sB2[MLP_H], sW3[MLP_H];
+    const int t = threadIdx.x, l = t & 63, c = l & 31, h = l >> 5;
+    if (t < MLP_H) {
+        sB2[t] = bf16_to_f(wbf[MLP_OB2 + t]);
+        sW3[t] = bf16_to_f(wbf[MLP_OW3 + t]);
+    }
+    float mean[MLP_IN], sd[MLP_IN];
 #pragma unroll
-    for (int q = 0; q < MLP_IN; ++q) f[q] = data[r * 6 + q];
-    y[r] = mlp_eval(sW, sN, f);
+    for (int k = 0; k < MLP_IN; ++k) {
+        mean[k] = norm[k];
+        sd[k] = norm[MLP_IN + k];
+    }
+    const float b3 = bf16_to_f(wbf[MLP_OB3]);
+    // layer 1, slots of the lower lanes: hi 0..4, mid 0..2; of the upper: mid 3, 4, lo 0..4, bias
+    uint4 w1[2], w2[2][4];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const uint16_t *r = wbf + MLP_OW1 + MLP_IN * (32 * m + c);
+        const unsigned bias = wbf[MLP_OB1 + 32 * m + c];
+        const unsigned a0 = r[0], a1 = r[1], a2 = r[2], a3 = r[3], a4 = r[4];
+        w1[m] = h == 0 ? make_uint4(a0 | a1 << 16, a2 | a3 << 16, a4 | a0 << 16, a1 | a2 << 16)
+                       : make_uint4(a3 | a4 << 16, a0 | a1 << 16, a2 | a3 << 16, a4 | bias << 16);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint2 *q = reinterpret_cast<const uint2 *>(wbf + MLP_OW2 + MLP_H * (32 * m + c) + 16 * k + 4 * h);
+            const uint2 lo = q[0], hi = q[2];
+            w2[m][k] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        }
+    }
+    __syncthreads();
+    auto mma = [](const uint4 &a, const uint4 &b, const f32x16 &acc) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc,
+                                                       0, 0, 0);
+    };
+    const long long tiles = (n + 31) / 32, stride = (long long)gridDim.x * 4;
+    for (long long tile = (long long)blockIdx.x * 4 + (t >> 6); tile < tiles; tile += stride) {
+        const long long row = tile * 32 + c;
+        const float *f = data + (row < n ? row : n - 1) * 6;
+        Split x[MLP_IN];
+#pragma unroll
+        for (int k = 0; k < MLP_IN; ++k) x[k] = split3((f[k] - mean[k]) / sd[k]);
+        const uint4 xb = h == 0 ? make_uint4(pack_hi(x[0].hi, x[1].hi), pack_hi(x[2].hi, x[3].hi),
+                                             pack_hi(x[4].hi, x[0].mid), pack_hi(x[1].mid, x[2].mid))
+                                : make_uint4(pack_hi(x[3].mid, x[4].mid), pack_hi(x[0].lo, x[1].lo),
+                                             pack_hi(x[2].lo, x[3].lo), pack_hi(x[4].lo, 0x3f800000u));
+        f32x16 z2[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 b = *reinterpret_cast<const float4 *>(&sB2[32 * m + 8 * g + 4 * h]);
+                z2[m][4 * g] = b.x;
+                z2[m][4 * g + 1] = b.y;
+                z2[m][4 * g + 2] = b.z;
+                z2[m][4 * g + 3] = b.w;
+            }
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const f32x16 zero = {};
+            const f32x16 z1 = mma(w1[m], xb, zero);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {              // eight of the lane's units: one slot group of layer 2
+                unsigned hi[4], mid[4], lo[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const Split a = split3(gelu_f(z1[8 * k + 2 * j])), b = split3(gelu_f(z1[8 * k + 2 * j + 1]));
+                    hi[j] = pack_hi(a.hi, b.hi);
+                    mid[j] = pack_hi(a.mid, b.mid);
+                    lo[j] = pack_hi(a.lo, b.lo);
+                }
+                const uint4 vl = make_uint4(lo[0], lo[1], lo[2], lo[3]), vm = make_uint4(mid[0], mid[1], mid[2], mid[3]),
+                            vh = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    z2[o] = mma(w2[o][2 * m + k], vl, z2[o]);
+                    z2[o] = mma(w2[o][2 * m + k], vm, z2[o]);
+                    z2[o] = mma(w2[o][2 * m + k], vh, z2[o]);
+                }
+            }
+        }
+        float s = 0.0f;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 w = *reinterpret_cast<const float4 *>(&sW3[32 * m + 8 * g + 4 * h]);
+                s = fmaf(w.x, gelu_f(z2[m][4 * g]), s);
+                s = fmaf(w.y, gelu_f(z2[m][4 * g + 1]), s);
+                s = fmaf(w.z, gelu_f(z2[m][4 * g + 2]), s);
+                s = fmaf(w.w, gelu_f(z2[m][4 * g + 3]), s);
+            }
+        s += __shfl_xor(s, 32);
+        if (h == 0 && row < n) y[row] = s + b3;
+    }
 }
+constexpr int PREDICT_BLOCKS = 1024;   // four per compute unit, each wavefront's weights loaded once
 
 grte_status mhip(hipError_t e, const char *what)
 {
@@ -559,8 +669,8 @@ grte_status grte_mlp_train_noalloc(grte_mlp *m, const float *data, long long n, 
 grte_status grte_mlp_predict(grte_mlp *m, const float *data, long long n, float *y)
 {
     if (!m || !data || !y || n < 1) return GRTE_E_INVAL;
-    hipLaunchKernelGGL(mlp_predict_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m->stream, m->wbf,
-                       m->norm, data, n, y);
+    const unsigned blocks = (unsigned)std::min<long long>((n + 127) / 128, PREDICT_BLOCKS);
+    hipLaunchKernelGGL(mlp_predict_kernel, dim3(blocks), dim3(256), 0, m->stream, m->wbf, m->norm, data, n, y);
     MCHK(hipGetLastError());
     MCHK(hipStreamSynchronize(m->stream));
     return GRTE_OK;
