@@ -111,16 +111,45 @@ __device__ __forceinline__ void cell_yx(const Sys &S, int j, int &iy, int &ix)
     }
 }
 
+// The tile that work-group b of nb takes: the work-groups go to the eight dies in turn,
+// each with an L2 of its own, so each die takes a run of consecutive tiles and finds the
+// halos that its neighbours read.  nb tiles for nb work-groups, a permutation.
+__device__ __forceinline__ int die_tile(int b, int nb)
+{
+    const int q = nb >> 3, rem = nb & 7, x = b & 7, i = b >> 3;
+    return x * q + min(x, rem) + i;
+}
+
+// sum over the P lanes of a cell, in every one of them (P the same in all lanes: each
+// test is a scalar branch).  Data-parallel moves: as lane shuffles through LDS these
+// sums were two thirds of the operator product's time.
 __device__ __forceinline__ double group_sum(double v, int P)
 {
-    for (int o = P >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (P >= 2) v += dpp_mov<quad(1, 0, 3, 2)>(v, v);
+    if (P >= 4) v += dpp_mov<quad(2, 3, 0, 1)>(v, v);
+    if (P >= 8) v += dpp_mov<DPP_HALF_MIRROR>(v, v);
+    if (P >= 16) v += dpp_mov<DPP_MIRROR>(v, v);
+    if (P >= 32) v = add_rows(v);
+    if (P >= 64) v = add_halves(v);
     return v;
 }
 
+// the value of a cell's first lane, in all P
 __device__ __forceinline__ double group_lane0(double v, int P)
 {
-    const int lane = __lane_id();
-    return __shfl(v, lane & ~(P - 1), 64);
+    if (P == 64) return lane_at(v, 0);
+    if (P == 32) {
+        const double lo = lane_at(v, 0), hi = lane_at(v, 32);
+        return __lane_id() < 32 ? lo : hi;
+    }
+    if (P == 16) return dpp_mov<DPP_ROW_BCAST>(v, v);
+    if (P == 8) {
+        const double lo = dpp_mov<DPP_ROW_BCAST, 0xf, 0x3>(v, v);
+        return dpp_mov<DPP_ROW_BCAST + 8, 0xf, 0xc>(lo, v);
+    }
+    if (P == 4) return dpp_mov<quad(0, 0, 0, 0)>(v, v);
+    if (P == 2) return dpp_mov<quad(0, 0, 2, 2)>(v, v);
+    return v;
 }
 
 // 3 x 3 neighbourhood of a cell field (indices clamped at the walls)
@@ -303,7 +332,7 @@ struct VecArgs {
     Sys S;
     size_t n;                  // N * P
     const double *En;          // E^n (rhs)
-    double *bv, *x;            // right-hand side, iterate (binary64)
+    double *x;                 // iterate (binary64)
     // the Krylov vectors and the block inverse's 1/d_p, stored in binary32 or
     // binary64 (the kernels' template type V; the arithmetic is binary64): a
     // pass of iterations ends when the recursion has reduced the residual by
@@ -335,8 +364,7 @@ __device__ __forceinline__ void block_sums(double *vals, int k, double *part)
     __shared__ double red[4][B2 / 64];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
     for (int q = 0; q < k; ++q) {
-        double v = vals[q];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        const double v = group_sum(vals[q], 64);
         if (lane == 0) red[q][w] = v;
     }
     __syncthreads();
@@ -347,30 +375,36 @@ __device__ __forceinline__ void block_sums(double *vals, int k, double *part)
     }
 }
 
-// the shadow vector of BiCGStab: a fixed pseudo-random value in [-1, 1) per
-// item (the splitmix64 output function of the item index), computed where used
+// the shadow vector of BiCGStab: a fixed pseudo-random value in [-1, 1) per item,
+// computed where used (two rounds of a multiplication by 2^32 / golden ratio and an
+// exclusive-or with the upper half: a 64-bit mix took as long as the vectors' traffic)
 __device__ __forceinline__ double shadow(int t)
 {
-    unsigned long long z = (unsigned long long)(unsigned)t + 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    z ^= z >> 31;
-    return (double)(z >> 11) * 0x1p-52 - 1.0;
+    unsigned z = (unsigned)t * 0x9E3779B9u;
+    z ^= z >> 16;
+    z *= 0x9E3779B9u;
+    z ^= z >> 15;
+    return (double)(int)z * 0x1p-31;
 }
 
-// rhs: rb1 E^n_p + rb0 - k div O(known)   (rb1 = K eps^2 prediction, K eps correction)
+// (b, b) of the right-hand side b = rb1 E^n_p + rb0 - k div O(known) (rb1 = K eps^2
+// prediction, K eps correction), partial sums; the residual is formed from the equations,
+// so b itself is not kept
 __global__ void __launch_bounds__(B2) rhs2d_kernel(VecArgs A)
 {
     const Sys &S = A.S;
     const int P = S.P;
+    double acc = 0.0;
     for (int t = blockIdx.x * B2 + threadIdx.x; t < (int)A.n; t += gridDim.x * B2) {
         const int j = t >> S.lgP, p = t & (P - 1);
         int iy, ix;
         cell_yx(S, j, iy, ix);
         Grad O;
         faces<true, false>(S, iy, ix, p, nullptr, O);
-        A.bv[t] = S.rb1[j] * A.En[t] + S.rb0[j] - S.kco[j] * divergence(S, O, p);
+        const double b = S.rb1[j] * A.En[t] + S.rb0[j] - S.kco[j] * divergence(S, O, p);
+        acc += b * b;
     }
+    block_sums(&acc, 1, A.part);
 }
 
 // b - A x evaluated from the full face values and differences of nearly equal
@@ -425,15 +459,14 @@ __device__ __forceinline__ double residual_at(const Sys &S, const double *En, co
 }
 
 // r = b - A x (the pass's starting residual, stored as V), partial (r, r)
-// of the binary64 residual, (b, b), the backward-error scale and (h, r)
-// (h: the shadow vector)
+// of the binary64 residual, the backward-error scale and (h, r) (h: the shadow vector)
 template <class V>
 __global__ void __launch_bounds__(B2) residual2d_kernel(VecArgs A)
 {
     const Sys &S = A.S;
     const int P = S.P;
     V *r = (V *)A.r;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    double acc[3] = {0.0, 0.0, 0.0};
     for (int t = blockIdx.x * B2 + threadIdx.x; t < (int)A.n; t += gridDim.x * B2) {
         const int j = t >> A.S.lgP, p = t & (P - 1);
         double mag;
@@ -445,15 +478,14 @@ __global__ void __launch_bounds__(B2) residual2d_kernel(VecArgs A)
             if (p == 0) A.mr[j] = m;
         }
         acc[0] += rr * rr;
-        acc[1] += A.bv[t] * A.bv[t];
-        acc[2] += mag * mag;
-        acc[3] += shadow(t) * (double)rf;
+        acc[1] += mag * mag;
+        acc[2] += shadow(t) * (double)rf;
     }
-    block_sums(acc, 4, A.part);
+    block_sums(acc, 3, A.part);
 }
 
 // The operator products of the iteration by columns: the grid is cut into tiles
-// of (B2 / P) cells across by OP_ROWS cells down; thread (cell c, pair p) of a
+// of (B2 / P) cells across by `rows` cells down (op_rows); thread (cell c, pair p) of a
 // tile walks down its column keeping the 3 x 3 neighbourhood of its pair in
 // registers, so that a row costs three new loads of x instead of nine and the
 // shared face coefficient of two rows one, and it loads the next row's values
@@ -465,15 +497,14 @@ __global__ void __launch_bounds__(B2) residual2d_kernel(VecArgs A)
 // part[k * KRYB + blockIdx.x].  The products are stored as V.
 // MODE 1: v = A ph, partial (h, v) and, with the isotropic correction, the moment
 // of v;  MODE 2: t = A sh, partial (t, s), (t, t)
-constexpr int OP_ROWS = 16;
+constexpr int OP_ROWS = 16, OP_ROWS_MIN = 2, OP_TILES = 1024;
 
 __device__ __forceinline__ void block_sums_at(double *vals, int k, double *part, int bid)
 {
     __shared__ double red[4][B2 / 64];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
     for (int q = 0; q < k; ++q) {
-        double v = vals[q];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        const double v = group_sum(vals[q], 64);
         if (lane == 0) red[q][w] = v;
     }
     __syncthreads();
@@ -485,7 +516,7 @@ __device__ __forceinline__ void block_sums_at(double *vals, int k, double *part,
 }
 
 template <int MODE, class V>
-__global__ void __launch_bounds__(B2, 5) apply2d_col_kernel(VecArgs A, int ncol, int ntile)
+__global__ void __launch_bounds__(B2, 5) apply2d_col_kernel(VecArgs A, int ncol, int ntile, int rows)
 {
     if (A.fl[F_STATE] != 0) return;
     const Sys &S = A.S;
@@ -502,7 +533,7 @@ __global__ void __launch_bounds__(B2, 5) apply2d_col_kernel(VecArgs A, int ncol,
         const int ty = tile / ncol, tx = tile - ty * ncol;
         const int ix = tx * cw + c;
         if (ix >= nx) continue;                 // whole cells: a cell's P lanes agree
-        const int iy0 = ty * OP_ROWS, iy1 = min(iy0 + OP_ROWS, ny);
+        const int iy0 = ty * rows, iy1 = min(iy0 + rows, ny);
         const int o0 = max(ix - 1, 0) * P + p, o1 = ix * P + p, o2 = min(ix + 1, nx - 1) * P + p;
         auto ldrow = [&](int row, double(&v)[3]) {
             const V *q = xv + row * rs;
@@ -758,16 +789,31 @@ __global__ void __launch_bounds__(B2) supd2d_kernel(VecArgs A)
     }
 }
 
-// the isotropic correction's inputs from the moments:
-// which 0: yP = mr + beta (yP - omega mv) (yP holds the last direction's moment);
-// which 1: yS = mr - alpha mv
+// the isotropic correction's inputs from the moments, for the direction (yP holds the
+// last direction's moment; mr alone in the first iteration of a pass) and for s
+// (explicit fused multiply-adds: every kernel that forms them rounds alike)
+struct MomScal {
+    double alpha, beta, omega;
+    int first;
+};
+__device__ __forceinline__ MomScal mom_scal(const double *sc, const int *fl)
+{
+    return MomScal{sc[S_ALPHA], sc[S_BETA], sc[S_OMEGA], fl[F_ITS] == 0};
+}
+__device__ __forceinline__ double mom_p(const MomScal &M, double mr, double yP, double mv)
+{
+    return M.first ? mr : fma(M.beta, fma(-M.omega, mv, yP), mr);
+}
+__device__ __forceinline__ double mom_s(const MomScal &M, double mr, double mv) { return fma(-M.alpha, mv, mr); }
+
+// which 0: yP of the next direction; which 1: yS
 __global__ void __launch_bounds__(B2) ymom2d_kernel(VecArgs A, int which, int n)
 {
     if (A.fl[F_STATE] != 0) return;
-    const double alpha = A.sc[S_ALPHA], beta = A.sc[S_BETA], omega = A.sc[S_OMEGA];
+    const MomScal M = mom_scal(A.sc, A.fl);
     for (int j = blockIdx.x * B2 + threadIdx.x; j < n; j += gridDim.x * B2) {
-        if (which == 0) A.yP[j] = A.mr[j] + beta * (A.yP[j] - omega * A.mv[j]);
-        else A.yS[j] = A.mr[j] - alpha * A.mv[j];
+        if (which == 0) A.yP[j] = mom_p(M, A.mr[j], A.yP[j], A.mv[j]);
+        else A.yS[j] = mom_s(M, A.mr[j], A.mv[j]);
     }
 }
 
@@ -841,7 +887,7 @@ struct IsoArgs {
     const double *y;
     const double *xin;
     double *xout, *d;
-    double c1, c2, th;
+    double c1, c2, ith;          // Chebyshev coefficients of a step; 1 / theta
     const int *fl;
 };
 
@@ -925,7 +971,7 @@ __global__ void __launch_bounds__(B2) iso_first_kernel(IsoArgs A)
     for (int j = blockIdx.x * B2 + threadIdx.x; j < n; j += gridDim.x * B2) {
         int iy, ix;
         const IsoRow R = iso_row_at(A, j, iy, ix);
-        const double d0 = A.y[j] / (R.diag * A.th);
+        const double d0 = A.y[j] * R.rdg * A.ith;
         A.d[j] = d0;
         A.xout[j] = d0;
     }
@@ -945,112 +991,128 @@ __global__ void __launch_bounds__(B2) iso_step_kernel(IsoArgs A)
         const double xl = ix > 0 ? x[j - 1] : 0.0, xr = ix < S.nx - 1 ? x[j + 1] : 0.0;
         const double xb = iy > 0 ? x[j - S.nx] : 0.0, xt = iy < S.ny - 1 ? x[j + S.nx] : 0.0;
         const double r = iso_jres(A.y[j] * R.rdg, R.wl, R.wr, R.wb, R.wt, xc, xl, xr, xb, xt);
-        const double dn = A.c1 * A.d[j] + A.c2 * r;
+        const double dn = fma(A.c1, A.d[j], A.c2 * r);
         A.d[j] = dn;
         A.xout[j] = xc + dn;
     }
 }
 
-// Up to ISO_HALO stencil steps of the Chebyshev map in one launch, preceded
-// by the local first step (first = 1) or continuing from a stored iterate and
-// direction.  A block owns a tile of ISO_T x ISO_T cells and works on the tile
-// plus a halo of as many cells as it takes stencil steps: the iterate sits in
-// LDS, each cell's own values (its Jacobi-scaled row, y / diag, the Chebyshev
-// direction) in registers.  Stencil step s updates the region cells
-// at least s + 1 cells inside its border (their neighbours hold step-s
-// values), so after the launch's steps the tile's cells are exact; cells
-// outside the grid are never read (their neighbours' weights are zero and
-// their values taken as 0, as in the per-step form).  The arithmetic is the
-// per-step kernels' own, term for term, so the result is the same to the bit.
-constexpr int ISO_T = 32, ISO_HALO = 9, ISO_RMAX = ISO_T + 2 * ISO_HALO, ISO_TB = 1024;
-constexpr int ISO_CPT = (ISO_RMAX * ISO_RMAX + ISO_TB - 1) / ISO_TB;
+// the cells' Jacobi-scaled rows, once per solve: w_l, w_r, w_b, w_t, 1 / diag, n of each
+__global__ void __launch_bounds__(B2) iso_rows_kernel(IsoArgs A, double *rows)
+{
+    const int n = A.S.nx * A.S.ny;
+    for (int j = blockIdx.x * B2 + threadIdx.x; j < n; j += gridDim.x * B2) {
+        int iy, ix;
+        const IsoRow R = iso_row_at(A, j, iy, ix);
+        rows[j] = R.wl;
+        rows[n + j] = R.wr;
+        rows[2 * n + j] = R.wb;
+        rows[3 * n + j] = R.wt;
+        rows[4 * n + j] = R.rdg;
+    }
+}
+
+// Several stencil steps of the Chebyshev map in one launch, preceded by the local first
+// step (first = 1) or continuing from a stored iterate and direction.  A block of 16
+// wavefronts works on a region of 64 cells across (a lane each) by 16 RPW down (RPW rows
+// per wavefront): the iterate, the direction and the rows' coefficients stay in registers,
+// the neighbours across are data-parallel moves, those down registers of the same lane but
+// for a wavefront's end rows, which go through LDS (two buffers, one barrier per step).
+// Every cell is updated in every step; those next to the region's border go wrong by one
+// cell per step, so the block owns the region less a halo of as many cells as it takes
+// steps -- none on a side where the region covers the grid.  Cells outside the grid have
+// zero rows and stay zero.  The arithmetic is the per-step kernels' own, term for term, so
+// the result is the same to the bit.  The correction's input is formed here too (ymode).
+// Bound: the reads of the region (8 words per cell in the first launch, 2.2 times the
+// grid's with the halo) and the vector instructions of a step (12 binary64, 4 moves per
+// cell).  One launch of nine steps on an MI355X: 512 x 512 cells 11.6 us, 1024 x 1024 33;
+// with the iterate in LDS (32 x 32 tiles, two barriers per step), every row formed in
+// every launch and the input by a launch of its own, 12.5 + 2.3 and 37 + 3.4.  47 x 33
+// cells: 18 steps in one launch 14 us (two of nine, 21).
+constexpr int ISO_W = 16, ISO_HALO = 9, ISO_STEPS = 24;   // wavefronts; steps of a launch with a halo, without
 
 struct IsoFused {
     IsoArgs A;                  // A.xin: the iterate to continue from (first = 0); A.xout: the result
-    int first;                  // 1: start with the local first step from A.y
-    int nsteps;                 // stencil steps of this launch, 0 .. ISO_HALO
+    int first;                  // 1: start with the local first step
+    int nsteps;                 // stencil steps of this launch
+    int hx, hy;                 // halo across, down
+    int ymode;                  // input: 0 A.y, 1 the direction's moment (yP, kept in ynew by the owner), 2 that of s
+    const double *rows, *mr, *mv, *yP, *sc;
+    double *ynew;
     const double *din;          // the direction to continue from (first = 0)
     double *dout;               // the direction after the launch (null: not kept)
-    double c1[ISO_HALO], c2[ISO_HALO];
+    double c1[ISO_STEPS], c2[ISO_STEPS];
 };
 
-__global__ void __launch_bounds__(ISO_TB, 8) iso_fused_kernel(IsoFused F)
+template <int RPW>
+__global__ void __launch_bounds__(64 * ISO_W) iso_tile_kernel(IsoFused F)
 {
     const IsoArgs &A = F.A;
     if (A.fl[F_STATE] != 0) return;
-    const Sys &S = A.S;
-    const int h = F.nsteps, R = ISO_T + 2 * h;
-    const int ox = blockIdx.x * ISO_T - h, oy = blockIdx.y * ISO_T - h;   // grid position of region cell (0, 0)
-    __shared__ double X[ISO_RMAX * ISO_RMAX];
-    const int t = threadIdx.x;
-    // per cell: its Jacobi-scaled row and y / diag in registers, and its region
-    // position packed as rx | ry << 8 | (depth + 1) << 16, depth = distance to
-    // the region's border (-1: outside the region or the grid), so that stencil
-    // step s updates the cells of depth > s and the tile is the cells of depth >= h
-    double yr[ISO_CPT], wl[ISO_CPT], wr[ISO_CPT], wb[ISO_CPT], wt[ISO_CPT], d[ISO_CPT], xn[ISO_CPT];
-    int pk[ISO_CPT];
+    const int nx = A.S.nx, ny = A.S.ny, n = nx * ny;
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ry0 = w * RPW;
+    const int tile = die_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    const int ty = tile / gridDim.x, tx = tile - ty * gridDim.x;
+    const int ix = tx * (64 - 2 * F.hx) - F.hx + l;
+    const int iy0 = ty * (ISO_W * RPW - 2 * F.hy) - F.hy + ry0;
+    __shared__ double sLo[2][ISO_W][64], sHi[2][ISO_W][64];   // the wavefronts' first and last rows
+    double yr[RPW], wl[RPW], wr[RPW], wb[RPW], wt[RPW], d[RPW], x[RPW];
+    const MomScal M = F.ymode ? mom_scal(F.sc, A.fl) : MomScal{};
 #pragma unroll
-    for (int i = 0; i < ISO_CPT; ++i) {
-        const int c = t + i * ISO_TB;
-        yr[i] = wl[i] = wr[i] = wb[i] = wt[i] = d[i] = xn[i] = 0.0;
-        pk[i] = 0;
-        if (c >= R * R) continue;
-        const int ry = c / R, rx = c - ry * R;
-        const int iy = oy + ry, ix = ox + rx;
-        if (iy < 0 || iy >= S.ny || ix < 0 || ix >= S.nx) continue;
-        const int dep = min(min(rx, R - 1 - rx), min(ry, R - 1 - ry));
-        pk[i] = rx | (ry << 8) | ((dep + 1) << 16);
-        const int j = iy * S.nx + ix, fl = iy * (S.nx + 1) + ix;
-        const IsoRow Rw = iso_row_coefs(A, iy, ix, j, S.gx[fl], S.gx[fl + 1], S.gy[j], S.gy[j + S.nx]);
-        wl[i] = Rw.wl;
-        wr[i] = Rw.wr;
-        wb[i] = Rw.wb;
-        wt[i] = Rw.wt;
-        const double y = A.y[j];
-        yr[i] = y * Rw.rdg;
-        if (F.first) {
-            d[i] = y / (Rw.diag * A.th);   // the first step: x1 = d0
-            xn[i] = d[i];
+    for (int r = 0; r < RPW; ++r) {
+        const int iy = iy0 + r;
+        yr[r] = wl[r] = wr[r] = wb[r] = wt[r] = d[r] = x[r] = 0.0;
+        if (ix < 0 || ix >= nx || iy < 0 || iy >= ny) continue;
+        const int j = iy * nx + ix;
+        wl[r] = F.rows[j];
+        wr[r] = F.rows[n + j];
+        wb[r] = F.rows[2 * n + j];
+        wt[r] = F.rows[3 * n + j];
+        const double rdg = F.rows[4 * n + j];
+        double y;
+        if (F.ymode == 0) {
+            y = A.y[j];
+        } else if (F.ymode == 1) {
+            y = mom_p(M, F.mr[j], F.yP[j], F.mv[j]);
+            if (l >= F.hx && l < 64 - F.hx && ry0 + r >= F.hy && ry0 + r < ISO_W * RPW - F.hy) F.ynew[j] = y;
         } else {
-            d[i] = F.din[j];
-            xn[i] = A.xin[j];
+            y = mom_s(M, F.mr[j], F.mv[j]);
+        }
+        yr[r] = y * rdg;
+        if (F.first) {
+            d[r] = yr[r] * A.ith;                      // the first step: x1 = d0
+            x[r] = d[r];
+        } else {
+            d[r] = F.din[j];
+            x[r] = A.xin[j];
         }
     }
-#pragma unroll
-    for (int i = 0; i < ISO_CPT; ++i) {
-        const int c = t + i * ISO_TB;
-        if (c < R * R) X[c] = xn[i];
-    }
-    __syncthreads();
-    for (int s = 0; s < h; ++s) {
+    for (int s = 0; s < F.nsteps; ++s) {
         const double c1 = F.c1[s], c2 = F.c2[s];
+        const int b = s & 1;
+        sLo[b][w][l] = x[0];
+        sHi[b][w][l] = x[RPW - 1];
+        __syncthreads();
+        double lo = w > 0 ? sHi[b][w > 0 ? w - 1 : 0][l] : 0.0;
+        const double hi = w < ISO_W - 1 ? sLo[b][w < ISO_W - 1 ? w + 1 : 0][l] : 0.0;
 #pragma unroll
-        for (int i = 0; i < ISO_CPT; ++i) {
-            if ((pk[i] >> 16) - 1 <= s) continue;
-            const int c = t + i * ISO_TB;
-            const int rx = pk[i] & 0xff, ry = (pk[i] >> 8) & 0xff;
-            const int iy = oy + ry, ix = ox + rx;
-            const double xc = X[c];
-            const double xl = ix > 0 ? X[c - 1] : 0.0, xr = ix < S.nx - 1 ? X[c + 1] : 0.0;
-            const double xb = iy > 0 ? X[c - R] : 0.0, xt = iy < S.ny - 1 ? X[c + R] : 0.0;
-            const double r = iso_jres(yr[i], wl[i], wr[i], wb[i], wt[i], xc, xl, xr, xb, xt);
-            const double dn = c1 * d[i] + c2 * r;
-            d[i] = dn;
-            xn[i] = xc + dn;
+        for (int r = 0; r < RPW; ++r) {
+            const double xc = x[r], xt = r < RPW - 1 ? x[r < RPW - 1 ? r + 1 : 0] : hi;
+            const double q = iso_jres(yr[r], wl[r], wr[r], wb[r], wt[r], xc, dpp_mov<DPP_PREV>(xc, xc),
+                                      dpp_mov<DPP_NEXT>(xc, xc), lo, xt);
+            d[r] = fma(c1, d[r], c2 * q);
+            lo = xc;
+            x[r] = xc + d[r];
         }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < ISO_CPT; ++i)
-            if ((pk[i] >> 16) - 1 > s) X[t + i * ISO_TB] = xn[i];
-        __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < ISO_CPT; ++i) {
-        if ((pk[i] >> 16) - 1 < h) continue;
-        const int rx = pk[i] & 0xff, ry = (pk[i] >> 8) & 0xff;
-        const int j = (oy + ry) * S.nx + ox + rx;
-        A.xout[j] = X[t + i * ISO_TB];
-        if (F.dout) F.dout[j] = d[i];
+    for (int r = 0; r < RPW; ++r) {
+        const int iy = iy0 + r, ry = ry0 + r;
+        if (l < F.hx || l >= 64 - F.hx || ry < F.hy || ry >= ISO_W * RPW - F.hy || ix >= nx || iy >= ny) continue;
+        const int j = iy * nx + ix;
+        A.xout[j] = x[r];
+        if (F.dout) F.dout[j] = d[r];
     }
 }
 
@@ -1205,7 +1267,7 @@ __device__ __forceinline__ double block_reduce(double v)
 // first reduction level: block b sums partials b*red_b .. of each of k sums
 __global__ void __launch_bounds__(B2) red2d_kernel(VecArgs A, int which, int k, int nb)
 {
-    if (which != 0 && A.fl[F_STATE] != 0) return;
+    if (which != 0 && which != 4 && A.fl[F_STATE] != 0) return;
     const int base = blockIdx.x * A.red_b, cnt = min(A.red_b, nb - base);
     for (int q = 0; q < k; ++q) {
         double v = 0.0;
@@ -1239,7 +1301,7 @@ __device__ __forceinline__ void fin_sums(const VecArgs &A, int nb, double (&s)[K
     const int lane = __lane_id(), w = threadIdx.x >> 6;
 #pragma unroll
     for (int q = 0; q < K; ++q) {
-        for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
+        v[q] = group_sum(v[q], 64);
         if (lane == 0) red[q][w] = v[q];
     }
     __syncthreads();
@@ -1251,20 +1313,24 @@ __device__ __forceinline__ void fin_sums(const VecArgs &A, int nb, double (&s)[K
     }
 }
 
-// which: 0 = start (rho = (h, r), rr = (r, r), bb, test), 1 = alpha, 2 = omega, 3 = rho/beta/test
+// which: 0 = start (rho = (h, r), rr = (r, r), test), 1 = alpha, 2 = omega, 3 = rho/beta/test,
+// 4 = bb of the solve
 __global__ void __launch_bounds__(FIN_T) fin2d_kernel(VecArgs A, int which, int nb)
 {
-    if (which != 0 && A.fl[F_STATE] != 0) return;
+    if (which != 0 && which != 4 && A.fl[F_STATE] != 0) return;
     double *sc = A.sc;
-    if (which == 0) {
-        double f[4];
-        fin_sums<4>(A, nb, f);
-        const double rr = f[0], bb = f[1], mm = f[2], hr = f[3];
+    if (which == 4) {
+        double f[1];
+        fin_sums<1>(A, nb, f);
+        if (threadIdx.x == 0) sc[S_BB] = f[0];
+    } else if (which == 0) {
+        double f[3];
+        fin_sums<3>(A, nb, f);
+        const double rr = f[0], bb = sc[S_BB], mm = f[1], hr = f[2];
         if (threadIdx.x == 0) {
             sc[S_RHO] = hr;
             sc[S_RR] = rr;
             sc[S_R0] = rr;
-            sc[S_BB] = bb;
             sc[S_MM] = mm;
             sc[S_ALPHA] = sc[S_OMEGA] = 1.0;
             sc[S_BETA] = 0.0;
@@ -1313,11 +1379,6 @@ __global__ void __launch_bounds__(FIN_T) fin2d_kernel(VecArgs A, int which, int 
             }
         }
     }
-}
-
-__global__ void __launch_bounds__(B2) zero2_kernel(double *a, double *b, size_t n)
-{
-    for (int t = blockIdx.x * B2 + threadIdx.x; t < (int)n; t += gridDim.x * B2) a[t] = b[t] = 0.0;
 }
 
 // x += dx at the end of a pass
@@ -1718,7 +1779,7 @@ struct grte2d_ctx {
     double *acU = nullptr, *beta = nullptr, *ustar = nullptr, *Dv = nullptr, *rhon = nullptr;
     double *sab = nullptr, *ue = nullptr;
     // Krylov
-    double *bv = nullptr, *x = nullptr, *Es = nullptr;
+    double *x = nullptr, *Es = nullptr;
     // the Krylov vectors: binary64 arrays, used as binary32 ones when the
     // solve's vectors are narrow
     double *r = nullptr, *p = nullptr, *ph = nullptr, *v = nullptr, *s = nullptr, *sh = nullptr, *t = nullptr;
@@ -1745,7 +1806,7 @@ struct grte2d_ctx {
     double last_eps = 0, last_dt = 0;
     // isotropic correction of the preconditioner
     int iso_kind = 1;                    // 0 none, 1 Chebyshev (tiled), 2 multigrid V-cycle, 3 Chebyshev per step
-    int iso_k = 19;                      // Chebyshev steps (two tiled launches)
+    int iso_k = 19;                      // Chebyshev steps
     // iterations of each pass of the last prediction / correction solve (-1: none yet)
     int last_its[2][KRY_RESTARTS + 1];
     int mg_nu = 2;                       // multigrid: Jacobi sweeps before and after the coarse correction
@@ -1768,6 +1829,7 @@ struct grte2d_ctx {
     float *idg32 = nullptr;              // the same in binary32
     double *opc = nullptr;               // the operator's packed per-cell coefficients (OPC_N per cell)
     double *mr = nullptr, *mv = nullptr;  // angular moments of r and v (isotropic correction)
+    double *irows = nullptr, *yP2 = nullptr;   // the isotropic operator's rows; second buffer of yP
     double *idir2 = nullptr;             // second Chebyshev direction buffer of the tiled launches
     // sampled timing of the operator kernel (first iteration of every chunk)
     int profiling = 0;
@@ -1808,6 +1870,18 @@ int kblocks(size_t n, int items)
 {
     const size_t b = (n + (size_t)B2 * items - 1) / ((size_t)B2 * items);
     return (int)std::max<size_t>(1, std::min<size_t>(b, KRYB));
+}
+
+// rows of the operator products' tiles: OP_ROWS (two of OP_ROWS + 2 rows read are halo),
+// halved down to OP_ROWS_MIN while the grid has fewer than OP_TILES tiles -- a row is a
+// chain of its own in a tile, so small grids are faster in many short tiles (47 x 33
+// cells of four pairs: 10.3 us in six tiles of 16 rows, 3.5 in 34 of two; at 512 x 512
+// cells of 32 pairs, 4096 tiles of 16 rows, the halo counts)
+int op_rows(int ncol, int ny)
+{
+    int rows = OP_ROWS;
+    while (rows > OP_ROWS_MIN && (long long)ncol * ((ny + rows - 1) / rows) < OP_TILES) rows /= 2;
+    return rows;
 }
 
 Sys make_sys(grte2d_ctx *c, int corr, double eps)
@@ -1876,7 +1950,7 @@ IsoArgs iso_args(grte2d_ctx *c, const Sys &S)
     I.xin = nullptr;
     I.xout = nullptr;
     I.d = c->idir;
-    I.c1 = I.c2 = I.th = 0.0;
+    I.c1 = I.c2 = I.ith = 0.0;
     return I;
 }
 
@@ -1928,8 +2002,57 @@ void mg_vcycle(grte2d_ctx *c, size_t l, const double *b, hipStream_t st)
     mg_sweeps(c, L, b, c->mg_nu, false, st);
 }
 
-// K Chebyshev steps for D z = y; the result lands in out (tmp is scratch)
-void iso_cheb(grte2d_ctx *c, const Sys &S, const double *y, double *out, hipStream_t st)
+// the tiled launches' shape: rows per wavefront and halos
+struct IsoShape {
+    int rpw, hx, hy, steps;            // steps: most stencil steps of a launch
+    dim3 grid;
+};
+
+// The region's height: with one block per compute unit at a time (1024 threads), the
+// number of rounds over the 256 of them times the rows per wavefront a round works on
+// (plus about one row's worth for the loads and barriers), least first.  A side that the
+// region covers needs no halo, and with none on either side all steps run in one launch.
+IsoShape iso_shape(int nx, int ny, int steps)
+{
+    IsoShape best{};
+    double cost = 0.0;
+    for (int rpw = 1; rpw <= 6; ++rpw) {
+        IsoShape s;
+        s.rpw = rpw;
+        const int rh = ISO_W * rpw;
+        const bool cx = nx <= 64, cy = ny <= rh;
+        s.steps = std::min(steps, cx && cy ? ISO_STEPS : ISO_HALO);
+        s.hx = cx ? 0 : s.steps;
+        s.hy = cy ? 0 : s.steps;
+        if (rh <= 2 * s.hy) continue;
+        s.grid = dim3((nx + 63 - 2 * s.hx) / (64 - 2 * s.hx), (ny + rh - 2 * s.hy - 1) / (rh - 2 * s.hy));
+        const int launches = s.steps > 0 ? (steps + s.steps - 1) / s.steps : 1;
+        const double c = (double)launches * ((s.grid.x * s.grid.y + 255) / 256) * (rpw + 1);
+        if (best.rpw == 0 || c < cost) {
+            best = s;
+            cost = c;
+        }
+    }
+    return best;
+}
+
+void launch_iso_tile(int rpw, dim3 grid, hipStream_t st, const IsoFused &F)
+{
+    const dim3 b(64 * ISO_W);
+    switch (rpw) {
+    case 1: hipLaunchKernelGGL(iso_tile_kernel<1>, grid, b, 0, st, F); break;
+    case 2: hipLaunchKernelGGL(iso_tile_kernel<2>, grid, b, 0, st, F); break;
+    case 3: hipLaunchKernelGGL(iso_tile_kernel<3>, grid, b, 0, st, F); break;
+    case 4: hipLaunchKernelGGL(iso_tile_kernel<4>, grid, b, 0, st, F); break;
+    case 5: hipLaunchKernelGGL(iso_tile_kernel<5>, grid, b, 0, st, F); break;
+    default: hipLaunchKernelGGL(iso_tile_kernel<6>, grid, b, 0, st, F); break;
+    }
+}
+
+// K Chebyshev steps for D z = y, y the moment of the direction (which 0) or of s (1); the
+// result lands in out (tmp is scratch).  The tiled launches form y themselves (yP in the
+// other of its two buffers), the per-step ones read it
+void iso_cheb(grte2d_ctx *c, const Sys &S, int which, double *out, hipStream_t st)
 {
     const int K = c->iso_k;
     const int nbc = nblocks(c->N);
@@ -1939,25 +2062,34 @@ void iso_cheb(grte2d_ctx *c, const Sys &S, const double *y, double *out, hipStre
     I.Myy = c->Myy;
     I.Sx = c->Sx;
     I.Sy = c->Sy;
-    I.y = y;
+    I.y = which == 0 ? c->yP : c->yS;
     I.d = c->idir;
     I.fl = c->fl;
     const double th = 0.5 * (CHEB2_B + CHEB2_A), de = 0.5 * (CHEB2_B - CHEB2_A), sg = th / de;
-    I.th = th;
+    I.ith = 1.0 / th;
     if (c->iso_kind == 1) {
-        // tiled launches of up to ISO_HALO stencil steps each (the first also
-        // takes the local first step); the iterate alternates between itmp and
-        // out so that the last launch writes out, the direction between idir
-        // and idir2
-        const int nl = K - 1 <= ISO_HALO ? 1 : 1 + (K - 1 - ISO_HALO + ISO_HALO - 1) / ISO_HALO;
-        const dim3 grid((S.nx + ISO_T - 1) / ISO_T, (S.ny + ISO_T - 1) / ISO_T);
+        // the first launch also takes the local first step; the iterate alternates
+        // between itmp and out so that the last launch writes out, the direction
+        // between idir and idir2
+        const IsoShape sh = iso_shape(S.nx, S.ny, K - 1);
+        const int nl = sh.steps > 0 ? (K - 1 + sh.steps - 1) / sh.steps : 1;
         double rho = 1.0 / sg;
         int k = 1;                          // global index of the next stencil step
         for (int l = 0; l < nl; ++l) {
             IsoFused F;
             F.A = I;
             F.first = l == 0;
-            F.nsteps = std::min(ISO_HALO, K - k);
+            F.nsteps = std::min(sh.steps, K - k);
+            F.hx = sh.hx;
+            F.hy = sh.hy;
+            F.rows = c->irows;
+            F.mr = c->mr;
+            F.mv = c->mv;
+            F.yP = c->yP;
+            F.ynew = c->yP2;
+            F.sc = c->sc;
+            F.ymode = which == 1 ? 2 : l == 0 ? 1 : 0;
+            if (which == 0 && l > 0) F.A.y = c->yP2;
             F.A.xin = l == 0 ? nullptr : (((nl - l) % 2 == 0) ? out : c->itmp);
             F.A.xout = ((nl - 1 - l) % 2 == 0) ? out : c->itmp;
             F.din = l == 0 ? nullptr : ((l % 2 == 1) ? c->idir : c->idir2);
@@ -1968,8 +2100,9 @@ void iso_cheb(grte2d_ctx *c, const Sys &S, const double *y, double *out, hipStre
                 F.c2[s] = 2.0 * rn / de;
                 rho = rn;
             }
-            hipLaunchKernelGGL(iso_fused_kernel, grid, dim3(ISO_TB), 0, st, F);
+            launch_iso_tile(sh.rpw, sh.grid, st, F);
         }
+        if (which == 0) std::swap(c->yP, c->yP2);
         return;
     }
     auto buf = [&](int k) { return ((K - k) % 2 == 0) ? out : c->itmp; };   // iterate k lands in buf(k)
@@ -1989,18 +2122,40 @@ void iso_cheb(grte2d_ctx *c, const Sys &S, const double *y, double *out, hipStre
     }
 }
 
-void iso_solve(grte2d_ctx *c, const Sys &S, const double *y, double *out, hipStream_t st)
+// the isotropic correction of the direction (which 0) or of s (1)
+void iso_solve(grte2d_ctx *c, const Sys &S, const VecArgs &A, int which, hipStream_t st)
 {
-    if (c->iso_kind == 1 || c->iso_kind == 3) {
-        iso_cheb(c, S, y, out, st);
+    double *out = which == 0 ? c->dP : c->dS;
+    if (c->iso_kind == 1) {
+        iso_cheb(c, S, which, out, st);
+        return;
+    }
+    hipLaunchKernelGGL(ymom2d_kernel, dim3(nblocks(c->N)), dim3(B2), 0, st, A, which, (int)c->N);
+    if (c->iso_kind == 3) {
+        iso_cheb(c, S, which, out, st);
         return;
     }
     // one V-cycle; level 0's result buffer is `out`
     grte2d_ctx::Lv &L0 = c->mg[0];
     double *keep = L0.z0;
     L0.z0 = out;
-    mg_vcycle(c, 0, y, st);
+    mg_vcycle(c, 0, which == 0 ? c->yP : c->yS, st);
     L0.z0 = keep;
+}
+
+// the square norm of the right-hand side of A.S, for the solve that follows
+void rhs_norm(grte2d_ctx *c, VecArgs &A)
+{
+    const int nb = nblocks(c->nE);
+    A.part = c->part;
+    A.part2 = c->part2;
+    A.red_b = c->red_b;
+    A.sc = c->sc;
+    A.fl = c->fl;
+    hipLaunchKernelGGL(rhs2d_kernel, dim3(nb), dim3(B2), 0, c->stream, A);
+    if (nb > c->red_b)
+        hipLaunchKernelGGL(red2d_kernel, dim3((nb + c->red_b - 1) / c->red_b), dim3(B2), 0, c->stream, A, 4, 1, nb);
+    hipLaunchKernelGGL(fin2d_kernel, dim3(1), dim3(FIN_T), 0, c->stream, A, 4, nb);
 }
 
 // BiCGStab on the system currently described by the coefficient arrays; x holds
@@ -2015,7 +2170,6 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
     A.S.opc = c->opc;
     A.n = c->nE;
     A.En = c->E;
-    A.bv = c->bv;
     A.x = c->x;
     A.r = c->r;
     A.p = c->p;
@@ -2046,19 +2200,21 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
     // the correction's systems have none
     const bool iso = c->iso_kind != 0 && !S.corr;
     if (iso && c->iso_kind == 2) mg_setup(c, S, c->stream);
+    if (iso && c->iso_kind == 1)
+        hipLaunchKernelGGL(iso_rows_kernel, dim3(nblocks(c->N)), dim3(B2), 0, c->stream, iso_args(c, S), c->irows);
     A.dP = iso ? c->dP : nullptr;
     A.dS = iso ? c->dS : nullptr;
     A.yP = iso ? c->yP : nullptr;
     A.yS = iso ? c->yS : nullptr;
     A.mr = iso ? c->mr : nullptr;
     A.mv = iso ? c->mv : nullptr;
-    const int nbc = nblocks(c->N);
     const int nb = kblocks(c->nE, c->kry_items);
     A.red_b = c->red_b;
     hipStream_t st = c->stream;
     // the scalar step `which` of the iteration after a kernel that left k partial sums per block
     // (the operator products of the iteration run on their own grid of column tiles)
-    const int ncol = (c->nx + (B2 / c->P) - 1) / (B2 / c->P), ntile = ncol * ((c->ny + OP_ROWS - 1) / OP_ROWS);
+    const int ncol = (c->nx + (B2 / c->P) - 1) / (B2 / c->P), rows = op_rows(ncol, c->ny);
+    const int ntile = ncol * ((c->ny + rows - 1) / rows);
     const int nbo = std::min(ntile, KRYB);
     auto fin = [&](int which, int k, int nbk) {
         if (nbk > c->red_b)
@@ -2077,11 +2233,9 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
     for (int restart = 0; restart <= KRY_RESTARTS; ++restart) {
         hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(64), 0, st, c->fl);
         hipLaunchKernelGGL(residual2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-        fin(0, 4, nb);
-        // the recurrence of the isotropic correction's input starts from zero
-        // moments (the pass's first iteration takes p = r and dx = alpha ph +
-        // omega sh, so p, v and dx need no clearing)
-        if (iso) hipLaunchKernelGGL(zero2_kernel, dim3(nbc), dim3(B2), 0, st, c->yP, c->mv, c->N);
+        fin(0, 3, nb);
+        // (the pass's first iteration takes p = r, its moment and dx = alpha ph +
+        // omega sh, so p, v, dx and the moments need no clearing)
         if (hipMemcpyAsync(c->h_fl, c->fl, F_NF * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess)
             return GRTE_E_HIP;
         if (hipMemcpyAsync(c->h_sc, c->sc, S_NS * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
@@ -2112,21 +2266,15 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
             const int batch = last < 0 ? CHUNK : (left >= 1 ? std::min(CHUNK, left) : 2);
             inpass += batch;
             for (int k = 0; k < batch; ++k) {
-                if (iso) {
-                    hipLaunchKernelGGL(ymom2d_kernel, dim3(nbc), dim3(B2), 0, st, A, 0, (int)c->N);
-                    iso_solve(c, S, c->yP, c->dP, st);
-                }
+                if (iso) iso_solve(c, S, A, 0, st);
                 hipLaunchKernelGGL(pupd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
                 if (timed && k == 0) (void)hipEventRecord(c->ev0, st);
-                hipLaunchKernelGGL((apply2d_col_kernel<1, V>), dim3(nbo), dim3(B2), 0, st, A, ncol, ntile);
+                hipLaunchKernelGGL((apply2d_col_kernel<1, V>), dim3(nbo), dim3(B2), 0, st, A, ncol, ntile, rows);
                 if (timed && k == 0) (void)hipEventRecord(c->ev1, st);
                 fin(1, 1, nbo);
-                if (iso) {
-                    hipLaunchKernelGGL(ymom2d_kernel, dim3(nbc), dim3(B2), 0, st, A, 1, (int)c->N);
-                    iso_solve(c, S, c->yS, c->dS, st);
-                }
+                if (iso) iso_solve(c, S, A, 1, st);
                 hipLaunchKernelGGL(supd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-                hipLaunchKernelGGL((apply2d_col_kernel<2, V>), dim3(nbo), dim3(B2), 0, st, A, ncol, ntile);
+                hipLaunchKernelGGL((apply2d_col_kernel<2, V>), dim3(nbo), dim3(B2), 0, st, A, ncol, ntile, rows);
                 fin(2, 2, nbo);
                 hipLaunchKernelGGL(xupd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
                 fin(3, 2, nb);
@@ -2153,7 +2301,7 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
             // one more true residual for the report
             hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(64), 0, st, c->fl);
             hipLaunchKernelGGL(residual2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-            fin(0, 4, nb);
+            fin(0, 3, nb);
             if (hipMemcpyAsync(c->h_sc, c->sc, S_NS * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
                 return GRTE_E_HIP;
             if (hipStreamSynchronize(st) != hipSuccess) return GRTE_E_HIP;
@@ -2273,7 +2421,7 @@ grte_status grte2d_create(const grte2d_problem *pb, const double *mu, const doub
               dalloc(c, c->lam, c->N) && dalloc(c, c->dmg, c->N) && dalloc(c, c->cg, c->N) &&
               dalloc(c, c->kco, c->N) && dalloc(c, c->rb0, c->N) && dalloc(c, c->rb1, c->N) &&
               dalloc(c, c->acU, c->N) && dalloc(c, c->beta, c->N) && dalloc(c, c->ustar, c->N) &&
-              dalloc(c, c->Dv, c->N) && dalloc(c, c->rhon, c->N) && dalloc(c, c->bv, c->nE) &&
+              dalloc(c, c->Dv, c->N) && dalloc(c, c->rhon, c->N) &&
               dalloc(c, c->sab, c->N) && dalloc(c, c->ue, c->N) &&
               dalloc(c, c->yP, c->N) && dalloc(c, c->yS, c->N) && dalloc(c, c->dP, c->N) &&
               dalloc(c, c->rstar, c->N) && dalloc(c, c->bflux, c->N) && dalloc(c, c->rho1, c->N) && dalloc(c, c->tguess, c->N) &&
@@ -2288,7 +2436,7 @@ grte_status grte2d_create(const grte2d_problem *pb, const double *mu, const doub
                   }
                   return true;
               }() &&
-              dalloc(c, c->dS, c->N) && dalloc(c, c->itmp, c->N) && dalloc(c, c->idir, c->N) && dalloc(c, c->idir2, c->N) && dalloc(c, c->pgc, c->N) && dalloc(c, c->idg, c->nE) && dalloc(c, c->idg32, c->nE) && dalloc(c, c->opc, OPC_N * c->N) && dalloc(c, c->dxv, c->nE) && dalloc(c, c->narrow, 1) && dalloc(c, c->mr, c->N) && dalloc(c, c->mv, c->N) &&
+              dalloc(c, c->dS, c->N) && dalloc(c, c->itmp, c->N) && dalloc(c, c->idir, c->N) && dalloc(c, c->idir2, c->N) && dalloc(c, c->irows, 5 * c->N) && dalloc(c, c->yP2, c->N) && dalloc(c, c->pgc, c->N) && dalloc(c, c->idg, c->nE) && dalloc(c, c->idg32, c->nE) && dalloc(c, c->opc, OPC_N * c->N) && dalloc(c, c->dxv, c->nE) && dalloc(c, c->narrow, 1) && dalloc(c, c->mr, c->N) && dalloc(c, c->mv, c->N) &&
               dalloc(c, c->x, c->nE) && dalloc(c, c->r, c->nE) &&
               dalloc(c, c->p, c->nE) && dalloc(c, c->ph, c->nE) && dalloc(c, c->v, c->nE) &&
               dalloc(c, c->s, c->nE) && dalloc(c, c->sh, c->nE) && dalloc(c, c->t, c->nE) &&
@@ -2581,8 +2729,7 @@ grte_status grte2d_step(grte2d_ctx *c, double dt, double eps, grte2d_step_info *
         A.S = Sp;
         A.n = c->nE;
         A.En = c->E;
-        A.bv = c->bv;
-        hipLaunchKernelGGL(rhs2d_kernel, dim3(nb), dim3(B2), 0, st, A);
+            rhs_norm(c, A);
     }
     if (hipMemcpyAsync(c->x, c->E, c->nE * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess)
         return GRTE_E_HIP;
@@ -2597,8 +2744,7 @@ grte_status grte2d_step(grte2d_ctx *c, double dt, double eps, grte2d_step_info *
     inf.pred_narrow = c->narrow_used[0];
     inf.pred_residual = res;
     inf.pred_floor_stop = floor;
-    if (hipMemcpyAsync(c->Es, c->x, c->nE * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return GRTE_E_HIP;
+    std::swap(c->x, c->Es);
 
     // ---- correction, substep 1: Newton per cell
     NewtArgs na;
@@ -2657,8 +2803,7 @@ grte_status grte2d_step(grte2d_ctx *c, double dt, double eps, grte2d_step_info *
         A.S = Sc;
         A.n = c->nE;
         A.En = c->E;
-        A.bv = c->bv;
-        hipLaunchKernelGGL(rhs2d_kernel, dim3(nb), dim3(B2), 0, st, A);
+            rhs_norm(c, A);
     }
     hipLaunchKernelGGL(xcorr0_kernel, dim3(nb), dim3(B2), 0, st, c->x, c->Es, c->acU, c->P, 1.0 / eps, c->nE);
     if (hipGetLastError() != hipSuccess) return GRTE_E_HIP;

@@ -69,25 +69,6 @@ __device__ __forceinline__ double opaque_d(double v)
 // arithmetic of many rows sinks below their loads, which then all stay in registers
 __device__ __forceinline__ void pin(double &v) { __asm__ volatile("" : "+v"(v) : : "memory"); }
 
-// ---- lane exchanges without LDS: data-parallel moves of the two halves of a double
-template <int CTRL, int ROWS = 0xf, int BANKS = 0xf>
-__device__ __forceinline__ double dpp_mov(double old, double v)
-{
-    const long long o = __double_as_longlong(old), x = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp((int)o, (int)x, CTRL, ROWS, BANKS, true);
-    const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(x >> 32), CTRL, ROWS, BANKS, true);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ double lane_at(double v, int lane)
-{
-    const long long x = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)x, lane), hi = __builtin_amdgcn_readlane((int)(x >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-constexpr int DPP_NEXT = 0x130, DPP_PREV = 0x138;         // lane + 1, lane - 1 over the wavefront (0 past its ends)
-constexpr int DPP_HALF_MIRROR = 0x141, DPP_ROW_BCAST = 0x150;   // within 8 lanes; lane n of every 16 to all of them
-constexpr int quad(int a, int b, int c, int d) { return a | b << 2 | c << 4 | d << 6; }
-
 // the largest of the wavefront's non-negative values, in every lane
 __device__ __forceinline__ double wave_max(double v)
 {

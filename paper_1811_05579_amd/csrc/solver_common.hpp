@@ -49,6 +49,43 @@ __device__ __forceinline__ double wave_nb(double v, int o, double dflt)
     return in ? r : dflt;
 }
 
+// ---- lane exchanges without LDS: data-parallel moves of the two halves of a double
+template <int CTRL, int ROWS = 0xf, int BANKS = 0xf>
+__device__ __forceinline__ double dpp_mov(double old, double v)
+{
+    const long long o = __double_as_longlong(old), x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp((int)o, (int)x, CTRL, ROWS, BANKS, true);
+    const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(x >> 32), CTRL, ROWS, BANKS, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double lane_at(double v, int lane)
+{
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)x, lane), hi = __builtin_amdgcn_readlane((int)(x >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+constexpr int DPP_NEXT = 0x130, DPP_PREV = 0x138;         // lane + 1, lane - 1 over the wavefront (0 past its ends)
+constexpr int DPP_MIRROR = 0x140, DPP_HALF_MIRROR = 0x141, DPP_ROW_BCAST = 0x150;   // of 16 lanes; of 8; lane n of every 16 to all of them
+constexpr int quad(int a, int b, int c, int d) { return a | b << 2 | c << 4 | d << 6; }
+
+// v + the value of the lane whose number differs in bit 4 (5): a row (half) of the
+// wavefront swapped with its own neighbour leaves the lower one's values in one
+// result, the upper one's in the other
+__device__ __forceinline__ double add_rows(double v)
+{
+    const long long x = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(x >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ double add_halves(double v)
+{
+    const long long x = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(x >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+
 // LDS scratch (doubles) of a work-group tile's solver, sh[0, 14 W + 16):
 //   tri_factor        sh[0, 5W)            reduced-row exchange
 //   tri_solve         sh[5W + 2W ph, +2W)  right-hand-side exchange, two buffers
