@@ -27,7 +27,7 @@
 #include <new>
 
 #include "../../include/grte.h"
-#include "slab_tile.hpp"
+#include "solver_common.hpp"
 
 namespace {
 
@@ -51,94 +51,6 @@ __device__ __forceinline__ double face_F(const DiffArgs &A, double Kl, double Kr
 }
 
 constexpr int DIFF_MAX_N = 4096;      // largest slab: 16 wavefronts, four cells per thread
-
-// Tridiagonal solve by the work-group: row M k + r is thread k's row r, a, b, c its sub-,
-// main and super-diagonal (a = 0 in the first row, c = 0 in the last; padding rows a = c =
-// 0, b = 1), x the right-hand side in, the solution out.  The threads' rows but their last
-// are eliminated, the last rows of a wavefront merged by blocks of 1, 2, .. 32 lanes
-// (slab_tile.hpp), and what a wavefront's first and last value answer to its neighbours'
-// goes through LDS as lanes 2 w, 2 w + 1 of one more such merge, which every wavefront
-// does on its own.  Two barriers (three for M > 1).
-template <int NW, int M>
-__device__ __forceinline__ void tri_wg(const double (&a)[M], const double (&b)[M], const double (&c)[M], double (&x)[M])
-{
-    static_assert((NW & (NW - 1)) == 0 && NW <= 32, "the wavefronts' ends are the lanes of one wavefront");
-    __shared__ double sEnd[3][2 * NW], sFirst[3][NW + 1];
-    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    double inv[M], fl[M], cp = 0.0;
-    double W0 = 0.0, A0 = 0.0, C0 = 1.0;               // first row = W0 + A0 z_left + C0 z (M > 1)
-#pragma unroll
-    for (int i = 0; i < M - 1; ++i) {
-        inv[i] = rcp64(i > 0 ? b[i] - a[i] * cp : b[i]);
-        x[i] = (i > 0 ? x[i] - a[i] * x[i - 1] : x[i]) * inv[i];
-        fl[i] = (i > 0 ? -a[i] * fl[i - 1] : -a[i]) * inv[i];
-        W0 = fma(C0, x[i], W0);
-        A0 = fma(C0, fl[i], A0);
-        cp = c[i] * inv[i];
-        C0 = -C0 * cp;
-    }
-    double B = b[M - 1], A = a[M - 1], C = c[M - 1], D = x[M - 1];
-    if constexpr (M > 1) {
-        if (l == 0) {
-            sFirst[0][w] = W0;
-            sFirst[1][w] = A0;
-            sFirst[2][w] = C0;
-        }
-        if (threadIdx.x < 3) sFirst[threadIdx.x][NW] = 0.0;
-        __syncthreads();
-        double Wn = dpp_mov<DPP_NEXT>(W0, W0), An = dpp_mov<DPP_NEXT>(A0, A0), Cn = dpp_mov<DPP_NEXT>(C0, C0);
-        if (l == 63) {
-            Wn = sFirst[0][w + 1];
-            An = sFirst[1][w + 1];
-            Cn = sFirst[2][w + 1];
-        }
-        D -= A * x[M > 1 ? M - 2 : 0] + C * Wn;
-        B += C * An - A * cp;
-        A *= fl[M > 1 ? M - 2 : 0];
-        C *= Cn;
-    }
-    const double ib = rcp64(B);
-    double u = D * ib, wl = -A * ib, vr = -C * ib, k[12];
-    auto merge = [&](auto L) {
-        merge_factor<L.v>(l, vr, wl, k);
-        merge_solve<L.v>(u, k);
-    };
-    merge(Int<0>());
-    merge(Int<1>());
-    merge(Int<2>());
-    merge(Int<3>());
-    merge(Int<4>());
-    merge(Int<5>());
-    if (l == 0 || l == 63) {
-        const int e = 2 * w + (l > 0);
-        sEnd[0][e] = u;
-        sEnd[1][e] = vr;
-        sEnd[2][e] = wl;
-    }
-    __syncthreads();
-    double xl, xr;                                     // the values next to the wavefront's rows
-    {
-        const double u0 = u, v0 = vr, w0 = wl;
-        u = l < 2 * NW ? sEnd[0][l] : 0.0;
-        vr = l < 2 * NW ? sEnd[1][l] : 0.0;
-        wl = l < 2 * NW ? sEnd[2][l] : 0.0;
-        if constexpr (NW > 1) merge(Int<1>());
-        if constexpr (NW > 2) merge(Int<2>());
-        if constexpr (NW > 4) merge(Int<3>());
-        if constexpr (NW > 8) merge(Int<4>());
-        if constexpr (NW > 16) merge(Int<5>());
-        xl = w > 0 ? lane_at(u, w > 0 ? 2 * w - 1 : 0) : 0.0;
-        xr = w < NW - 1 ? lane_at(u, w < NW - 1 ? 2 * w + 2 : 0) : 0.0;
-        u = fma(v0, xr, fma(w0, xl, u0));
-    }
-    x[M - 1] = u;
-    if constexpr (M > 1) {
-        double zl = dpp_mov<DPP_PREV>(u, u);
-        if (l == 0) zl = xl;
-#pragma unroll
-        for (int i = M - 2; i >= 0; --i) x[i] = fma(fl[i], zl, x[i]) - c[i] * inv[i] * x[i + 1];
-    }
-}
 
 // One step.  Bound: one chain of dependent operations on one compute unit (loads, two face
 // coefficients, the solve, the Newton iterations), hence no division that a product can

@@ -248,8 +248,10 @@ struct PredArgs {
     double *hist;                      // max|z| / max|rho| of each update (first HIST_CAP)
     unsigned long long *flags;
     unsigned long long gen0;
+    int direct;                        // every work-group sums all rows itself (one barrier per update)
 };
 
+constexpr int PQ = 4;                  // pairs whose partial sums a thread has in flight
 constexpr int HIST_CAP = GRTE_HIST_CAP;
 
 // One sweep of a pair from the iterate rho (position order, LDS):
@@ -257,11 +259,10 @@ constexpr int HIST_CAP = GRTE_HIST_CAP;
 template <int M>
 __device__ __forceinline__ void pred_sweep(const double *rho, const double *sLl, const double *sLu,
                                            const double (&rr)[M], const double (&lmg)[M], double mu, double mu2,
-                                           double bd0, double bdN, int N, const TriFac<NT, M> &Ft, double (&v)[M],
-                                           double *sh, int &ph)
+                                           double bd0, double bdN, int N, const WgFac<M> &Ft, double (&v)[M],
+                                           WgLds<NT / 64> &S, int &ph)
 {
     const int k = threadIdx.x, j0 = k * M;
-    double y[M];
 #pragma unroll
     for (int r = 0; r < M; ++r) {
         const int j = j0 + r;
@@ -278,29 +279,34 @@ __device__ __forceinline__ void pred_sweep(const double *rho, const double *sLl,
             // differences are formed almost exactly
             const double q = ll * (rl - rj) + lu * (rn - rj);
             const double bdj = (j == 0 ? bd0 : 0.0) + (j == N - 1 ? bdN : 0.0);
-            y[r] = rr[r] - lmg[r] * rj - mu2 * q - mu * bdj * rj;
+            v[r] = rr[r] - lmg[r] * rj - mu2 * q - mu * bdj * rj;
         } else {
-            y[r] = 0.0;
+            v[r] = 0.0;
         }
     }
-    tri_solve<NT, M>(mu2, sLl, sLu, Ft, y, v, sh, ph);
+    wg_solve<NT / 64, M>([&](int r) { return mu2 * sLl[r * NT + k]; }, [&](int r) { return mu2 * sLu[r * NT + k]; }, Ft,
+                         v, S, ph);
 }
 
+// One work-group per pair.  Bound: the chain of an update -- the sweep, the exchange of
+// the omega_p v_p between the work-groups, the diffusion solve, every one a few hundred
+// dependent operations or a round trip to the level that the dies share.  Hence the
+// factorisations in registers, merged solves with one work-group barrier each (wg_solve),
+// an exchange that needs no cache write-back, and, where the sums are short, one grid
+// barrier per update instead of two.  On an MI355X, an update of 100 cells x 8 pairs 4.7
+// us, 1543 x 16 8.9, 4096 x 32 (three slabs) 12.7; with a cyclic reduction through LDS and
+// barriers that wrote back and invalidated the L2, 8.8, 11.6 and 15.4.
 template <int M>
 __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, const int nblk)
 {
     extern __shared__ double smem[];
     constexpr int NP = NT * M;           // padded rows
     // Everything an iteration reads besides the other work-groups' partial sums
-    // stays in LDS or registers: the grid barrier's device-scope release and
-    // acquire write back and invalidate the L2, so global data would be
-    // fetched again from memory in every iteration.
+    // stays in LDS or registers.
     double *rho = smem;                  // current iterate (position order)
     double *sLl = smem + NP;             // operator coefficients (position order)
     double *sLu = smem + 2 * NP;
-    double *sh = smem + 3 * NP;          // solver scratch (tile_scratch<NT>())
-    double *redT = sh + tile_scratch<NT>();   // reduced systems of the two factorisations
-    double *redD = redT + red_doubles();
+    __shared__ WgLds<NT / 64> S;
     const int k = threadIdx.x;
     const int N = A.N, P = A.P;
     const int j0 = k * M;
@@ -316,7 +322,7 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
     const int p = bid;                   // one parity pair per work-group
     const double mu = A.mu[p], mu2 = mu * mu, wp = A.omega[p];
 
-    TriFac<NT, M> Ft, Fd;
+    WgFac<M> Ft, Fd;
     double rr[M], gg[M], lmg[M];         // r_p, G and Lam - G of this thread's rows
 #pragma unroll
     for (int r = 0; r < M; ++r) {
@@ -338,21 +344,23 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
                 b[r] = 1.0;
             }
         }
-        tri_factor<NT, M>(mu2, sLl, sLu, b, Ft, sh, redT);
+        wg_factor<NT / 64, M>([&](int r) { return mu2 * sLl[r * NT + k]; }, b,
+                              [&](int r) { return mu2 * sLu[r * NT + k]; }, Ft, S);
 #pragma unroll
         for (int r = 0; r < M; ++r) {
             const int j = j0 + r;
             b[r] = (j < N) ? A.Dd[j] : 1.0;
         }
         __syncthreads();   // the two factorisations share their LDS exchange area
-        tri_factor<NT, M>(A.mu2avg, sLl, sLu, b, Fd, sh, redD);
+        wg_factor<NT / 64, M>([&](int r) { return A.mu2avg * sLl[r * NT + k]; }, b,
+                              [&](int r) { return A.mu2avg * sLu[r * NT + k]; }, Fd, S);
     }
 
     // positions whose angular sum this work-group forms
     const int chunk = (NP + nblk - 1) / nblk;
     const int tb = bid * chunk;
     const int te = min(NP, tb + chunk);
-    double *part_p = A.part + (size_t)p * NP;
+    const size_t half = (size_t)P * NP;  // direct: two buffers of the partial sums, taking turns
     unsigned long long gen = A.gen0;
     int it = 0, converged = 0, ph = 0;
     ChebState C;
@@ -365,42 +373,65 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
     while (true) {
         // ---- sweep: v_p = T_p^{-1} [r_p - (Lam - G + mu^2 L + mu B) rho]
         double v[M];
-        pred_sweep<M>(rho, sLl, sLu, rr, lmg, mu, mu2, bd0, bdN, N, Ft, v, sh, ph);
+        pred_sweep<M>(rho, sLl, sLu, rr, lmg, mu, mu2, bd0, bdN, N, Ft, v, S, ph);
+        double *part = A.part + (M <= WG_KEEP && A.direct && (it & 1) ? half : 0), *part_p = part + (size_t)p * NP;
 #pragma unroll
-        for (int r = 0; r < M; ++r) part_p[r * NT + k] = wp * v[r];   // padded rows give v = 0
+        for (int r = 0; r < M; ++r)
+            if (j0 + r < N) agent_put(&part_p[r * NT + k], wp * v[r]);
         if (!grid_barrier(A.flags, ++gen, A.stat + 6, bid, nblk)) break;
-        // ---- angular sum for my positions: res = sum_p omega_p v_p - (1 - W) rho.
-        // Two adjacent lanes share a position, each summing half of the pairs
-        // (half the dependent load round trips), combined in a fixed order.
-        {
+        double rl[M], f[M];
+        if (M <= WG_KEEP && A.direct) {
+            // ---- the angular sum of this thread's rows, in every work-group:
+            // res = sum_p omega_p v_p - (1 - W) rho
+#pragma unroll
+            for (int r = 0; r < M; ++r) rl[r] = 0.0;
+            if (j0 < N) {
+                for (int q = 0; q < P; q += PQ) {
+                    double t[PQ][M];
+#pragma unroll
+                    for (int u = 0; u < PQ; ++u)
+#pragma unroll
+                        for (int r = 0; r < M; ++r)
+                            t[u][r] = q + u < P && j0 + r < N ? agent_get(&part[(size_t)(q + u) * NP + r * NT + k]) : 0.0;
+#pragma unroll
+                    for (int u = 0; u < PQ; ++u)
+#pragma unroll
+                        for (int r = 0; r < M; ++r) rl[r] += t[u][r];
+                }
+#pragma unroll
+                for (int r = 0; r < M; ++r) rl[r] -= A.one_minus_W * rho[r * NT + k];
+            }
+        } else {
+            // ---- angular sum for my positions: res = sum_p omega_p v_p - (1 - W) rho.
+            // Two adjacent lanes share a position, each summing half of the pairs
+            // (half the dependent load round trips), combined in a fixed order.
             const int h = k & 1, Ph = (P + 1) >> 1;
             const int q0 = h ? Ph : 0, q1 = h ? P : Ph;
             // lanes k and k^1 have the same position, so they iterate together
             for (int t = tb + (k >> 1); t < te; t += NT / 2) {
                 double s = 0.0;
-                int q = q0;
+                const bool in = (t % NT) * M + t / NT < N;
+                int q = in ? q0 : q1;
                 for (; q + 8 <= q1; q += 8) {
                     double t8[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) t8[u] = A.part[(size_t)(q + u) * NP + t];
+                    for (int u = 0; u < 8; ++u) t8[u] = agent_get(&part[(size_t)(q + u) * NP + t]);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) s += t8[u];
                 }
-                for (; q < q1; ++q) s += A.part[(size_t)q * NP + t];
+                for (; q < q1; ++q) s += agent_get(&part[(size_t)q * NP + t]);
                 const double other = __shfl_xor(s, 1);
-                if (h == 0) A.res[t] = (s + other) - A.one_minus_W * rho[t];
+                if (h == 0) agent_put(&A.res[t], (s + other) - A.one_minus_W * rho[t]);
             }
-        }
-        if (!grid_barrier(A.flags, ++gen, A.stat + 6, bid, nblk)) break;
-        // ---- diffusion acceleration, identical in every work-group
-        double rl[M], d[M], f[M];
+            if (!grid_barrier(A.flags, ++gen, A.stat + 6, bid, nblk)) break;
 #pragma unroll
-        for (int r = 0; r < M; ++r) {
-            const int t = r * NT + k;
-            rl[r] = A.res[t];
-            d[r] = gg[r] * rl[r];
+            for (int r = 0; r < M; ++r) rl[r] = j0 + r < N ? agent_get(&A.res[r * NT + k]) : 0.0;
         }
-        tri_solve<NT, M>(A.mu2avg, sLl, sLu, Fd, d, f, sh, ph);
+        // ---- diffusion acceleration, identical in every work-group
+#pragma unroll
+        for (int r = 0; r < M; ++r) f[r] = gg[r] * rl[r];
+        wg_solve<NT / 64, M>([&](int r) { return A.mu2avg * sLl[r * NT + k]; },
+                             [&](int r) { return A.mu2avg * sLu[r * NT + k]; }, Fd, f, S, ph);
         double alpha, beta;
         cheb_coeffs(C, A.accel, A.tol, alpha, beta);
         double md = 0.0, mr = 0.0;
@@ -417,7 +448,7 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
                 mr = fmax(mr, fabs(nw));
             }
         }
-        tile_max2<NT>(md, mr, sh);   // its barriers also publish the rho update
+        wg_max2<NT / 64>(md, mr);   // its barrier also publishes the rho update
         ++it;
         if (bid == 0 && k == 0 && it <= HIST_CAP) A.hist[it - 1] = mr > 0.0 ? md / mr : md;
         const float qprev = C.q1, qprev2 = C.q2, qprev3 = C.q3;
@@ -430,7 +461,7 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
         // E*_p = rho + T_p^{-1} [r_p - (T_p - G) rho] from the final iterate
         // (no grid barrier: each work-group sweeps its own pair once more)
         double v[M];
-        pred_sweep<M>(rho, sLl, sLu, rr, lmg, mu, mu2, bd0, bdN, N, Ft, v, sh, ph);
+        pred_sweep<M>(rho, sLl, sLu, rr, lmg, mu, mu2, bd0, bdN, N, Ft, v, S, ph);
 #pragma unroll
         for (int r = 0; r < M; ++r)
             if (j0 + r < N) A.estar[(size_t)(j0 + r) * P + p] = rho[r * NT + k] + v[r];
@@ -629,36 +660,29 @@ struct CorrArgs {
 template <int M>
 __global__ void __launch_bounds__(NT) corr_kernel(Group<CorrArgs> G)
 {
-    extern __shared__ double smem[];
     constexpr int NP = NT * M;
     const CorrArgs A = G.a[blockIdx.y];
-    double *sLl = smem, *sLu = smem + NP, *sh = smem + 2 * NP;
     const int p = blockIdx.x;
     if (p >= A.P) return;                // contexts of the group may have fewer pairs
     const int N = A.N, P = A.P, k = threadIdx.x;
     const int j0 = k * M;
-    for (int j = k; j < NP; j += NT) {
-        const int t = row_pos(j, M);
-        sLl[t] = (j < N) ? A.Ll[j] : 0.0;
-        sLu[t] = (j < N) ? A.Lu[j] : 0.0;
-    }
-    __syncthreads();
     const double mu = A.mu[p], mu2 = mu * mu;
-    double b[M], d[M], x[M];
+    double a[M], b[M], c[M], x[M];
 #pragma unroll
     for (int r = 0; r < M; ++r) {
         const int j = j0 + r;
         if (j < N) {
-            const double ll = sLl[r * NT + k], lu = sLu[r * NT + k];
+            const double ll = A.Ll[j], lu = A.Lu[j];
+            a[r] = mu2 * ll;
+            c[r] = mu2 * lu;
             b[r] = A.Lam[j] + mu2 * (-(ll + lu)) + mu * A.Bd[j];
-            d[r] = A.r[(size_t)p * NP + r * NT + k];
+            x[r] = A.r[(size_t)p * NP + r * NT + k];
         } else {
+            a[r] = c[r] = x[r] = 0.0;
             b[r] = 1.0;
-            d[r] = 0.0;
         }
     }
-    int ph = 0;
-    tri_factor_solve<NT, M>(mu2, sLl, sLu, b, d, x, sh, ph);
+    tri_wg<NT / 64, M>(a, b, c, x);
 #pragma unroll
     for (int r = 0; r < M; ++r) {
         const int j = j0 + r;
@@ -1227,7 +1251,7 @@ grte_status prof_end(grte_ctx *ctx, int idx)
 template <int M>
 size_t pred_lds_bytes()
 {
-    return (size_t)(3 * NT * M + tile_scratch<NT>() + 2 * red_doubles()) * sizeof(double);
+    return (size_t)(3 * NT * M) * sizeof(double);
 }
 
 // The prediction's work-groups wait for each other at grid barriers, so they
@@ -1254,8 +1278,7 @@ grte_status launch_pred(hipStream_t stream, Group<PredArgs> &g, int grid, bool c
 template <int M>
 grte_status launch_corr(hipStream_t stream, Group<CorrArgs> &g, int maxP)
 {
-    const size_t lds = (size_t)(2 * NT * M + tile_scratch<NT>()) * sizeof(double);
-    hipLaunchKernelGGL(corr_kernel<M>, dim3(maxP, g.n), dim3(NT), lds, stream, g);
+    hipLaunchKernelGGL(corr_kernel<M>, dim3(maxP, g.n), dim3(NT), 0, stream, g);
     HIPCHK(hipGetLastError());
     return GRTE_OK;
 }
@@ -1276,6 +1299,13 @@ grte_status convert_state(grte_ctx *ctx, int to32)
     HIPCHK(hipGetLastError());
     return GRTE_OK;
 }
+
+// Every work-group sums all rows itself while a thread's share, P M words from the level
+// that the dies share, takes less time than a second barrier and its round trips (step
+// of 100 cells x 8 pairs, 16 words: 115 us against 141; 1543 x 16, 128 words: 200 against
+// 172; 512 x 16, 32 words: equal).
+constexpr int DIRECT_WORDS = 32;
+int pred_direct(int P, int M) { return M <= WG_KEEP && P * M <= DIRECT_WORDS; }
 
 template <int M>
 int coop_blocks_per_cu()
@@ -1402,9 +1432,8 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
     double **padded[] = {&ctx->Gt, &ctx->res};
     for (double **q : padded)
         if (st == GRTE_OK) st = alloc(ctx, q, NP);
-    double **padded_pairs[] = {&ctx->part, &ctx->r};
-    for (double **q : padded_pairs)
-        if (st == GRTE_OK) st = alloc(ctx, q, NP * P);
+    if (st == GRTE_OK) st = alloc(ctx, &ctx->part, 2 * NP * P);
+    if (st == GRTE_OK) st = alloc(ctx, &ctx->r, NP * P);
     for (double **q : cells)
         if (st == GRTE_OK) st = alloc(ctx, q, N);
     double **nodes[] = {&ctx->Aw, &ctx->Bc};
@@ -1648,6 +1677,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
         pa.part = ctx->part; pa.res = ctx->res; pa.estar = ctx->estar; pa.rho_out = ctx->rho_b; pa.stat = ctx->stat;
         pa.flags = ctx->flags;
         pa.gen0 = ctx->bar_gen;
+        pa.direct = pred_direct(P, ctx->M);
         ctx->bar_gen += 2ull * (unsigned long long)ctx->pred_maxit + 4ull;   // never reused
         gp.first[g] = grid;
         grid += P;
@@ -1863,6 +1893,7 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
         hipLaunchKernelGGL(coef_kernel, dim3(ncb, 1), dim3(256), 0, stream, gc);
         HIPCHK(hipGetLastError());
         pa.gen0 = ctx->bar_gen;
+        pa.direct = pred_direct(P, ctx->M);
         ctx->bar_gen += 2ull * (unsigned long long)ctx->pred_maxit + 4ull;
         switch (M) {
         case 2: st = launch_pred<2>(stream, gp, P, ctx->coop_launch != 0); break;

@@ -69,81 +69,6 @@ __device__ __forceinline__ double opaque_d(double v)
 // arithmetic of many rows sinks below their loads, which then all stay in registers
 __device__ __forceinline__ void pin(double &v) { __asm__ volatile("" : "+v"(v) : : "memory"); }
 
-// the largest of the wavefront's non-negative values, in every lane
-__device__ __forceinline__ double wave_max(double v)
-{
-    v = fmax(v, dpp_mov<0x111>(v, v));                    // lane - 1, - 2, - 4, - 8 of the row (0 past its end)
-    v = fmax(v, dpp_mov<0x112>(v, v));
-    v = fmax(v, dpp_mov<0x114>(v, v));
-    v = fmax(v, dpp_mov<0x118>(v, v));
-    return fmax(fmax(lane_at(v, 15), lane_at(v, 31)), fmax(lane_at(v, 47), lane_at(v, 63)));
-}
-
-// The values next to the boundary of the two blocks of 2^L lanes that level L
-// merges.  L <= 2: p the other block's, q the own block's; L >= 3: p the lower
-// block's last lane's, q the upper block's first lane's.
-template <int L>
-__device__ __forceinline__ void boundary(double u, double &p, double &q)
-{
-    if constexpr (L == 0) {
-        p = dpp_mov<quad(1, 0, 3, 2)>(u, u);
-        q = u;
-    } else if constexpr (L == 1) {
-        p = dpp_mov<quad(2, 2, 1, 1)>(u, u);
-        q = dpp_mov<quad(1, 1, 2, 2)>(u, u);
-    } else if constexpr (L == 2) {
-        q = dpp_mov<quad(3, 3, 3, 3), 0xf, 0x5>(u, u);
-        q = dpp_mov<quad(0, 0, 0, 0), 0xf, 0xa>(q, u);
-        p = dpp_mov<DPP_HALF_MIRROR>(q, q);
-    } else if constexpr (L == 3) {
-        p = dpp_mov<DPP_ROW_BCAST + 7>(u, u);
-        q = dpp_mov<DPP_ROW_BCAST + 8>(u, u);
-    } else if constexpr (L == 4) {
-        double e = dpp_mov<DPP_ROW_BCAST + 15, 0x5>(u, u);
-        e = dpp_mov<DPP_ROW_BCAST, 0xa>(e, u);
-        // swapping e's odd rows with its own even rows leaves the even rows' value
-        // everywhere in one result, the odd rows' in the other
-        const long long x = __double_as_longlong(e);
-        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
-        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(x >> 32), false, false);
-        p = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
-        q = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
-    } else {
-        p = lane_at(u, 31);
-        q = lane_at(u, 32);
-    }
-}
-
-// Level L of the separators' factorisation.  A block's values are x = u + w x_left +
-// v x_right for the values x_left, x_right next to it.  Merging a lower block (last
-// lane: uA, vA, wA) with an upper one (first lane: uB, vB, wB) gives
-//   x_A = (uA + vA uB) / (1 - vA wB),  x_B = (uB + wB uA) / (1 - vA wB);
-// the lower lanes add v x_B, the upper ones w x_A.
-template <int L>
-__device__ __forceinline__ void merge_factor(int lane, double &v, double &w, double (&k)[12])
-{
-    const bool low = ((lane >> L) & 1) == 0;
-    double vp, vq, wp, wq;
-    boundary<L>(v, vp, vq);
-    boundary<L>(w, wp, wq);
-    const double vA = L >= 3 ? vp : low ? vq : vp, vB = L >= 3 ? vq : low ? vp : vq;
-    const double wA = L >= 3 ? wp : low ? wq : wp, wB = L >= 3 ? wq : low ? wp : wq;
-    const double s = (low ? v : w) * rcp64(fma(-vA, wB, 1.0));
-    const double cA = low ? s * wB : s, cB = low ? s : s * vA;
-    v = low ? cB * vB : fma(cB, vB, v);
-    w = low ? fma(cA, wA, w) : cA * wA;
-    k[2 * L] = L >= 3 ? cA : low ? cB : cA;
-    k[2 * L + 1] = L >= 3 ? cB : low ? cA : cB;
-}
-
-template <int L>
-__device__ __forceinline__ void merge_solve(double &u, const double (&k)[12])
-{
-    double p, q;
-    boundary<L>(u, p, q);
-    u = fma(k[2 * L], p, fma(k[2 * L + 1], q, u));
-}
-
 // Factor the wavefront's system, a(i), b(i), c(i) the sub-, main and super-diagonal of
 // the lane's row i (a = 0 in row 0 of the system, c = 0 in its last row)
 template <int M, class GA, class GB, class GC>
@@ -344,10 +269,6 @@ __device__ __forceinline__ double own_of(const double (&x)[M], int w)
     }
     return v;
 }
-template <int V>
-struct Int {
-    static constexpr int v = V;
-};
 // f(Int<k>, r) for the rows r = k NW + w < M
 template <int NW, int M, int K = 0, class F>
 __device__ __forceinline__ void own_rows(int w, F &f)

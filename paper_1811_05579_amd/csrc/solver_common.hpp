@@ -13,42 +13,6 @@ constexpr int MAX_N = NT * MAX_M;
 constexpr int MAX_P = 64;
 constexpr int BAR_STRIDE = 16;   // 64-bit barrier flags, one 128-byte line per work-group
 
-// -------------------------------------------------------------------------
-// tile tridiagonal solver: factor once, solve for many right-hand sides
-// -------------------------------------------------------------------------
-// A system of up to W*M rows is solved by a tile of W threads: the whole
-// work-group (W = 256) or one wavefront (W = 64).  Row j is owned by tile
-// thread k = j / M as its row r = j % M; all per-row data live in
-// "position" order t = r * W + k (conflict-free LDS, coalesced global
-// traffic).  The systems solved here have off-diagonals that are a scalar
-// multiple of two LDS-resident arrays, a_j = s Lo[t], c_j = s Up[t] (zero where
-// a row has no neighbour, and in padding rows), and a per-row diagonal b_j.
-//
-// Partitioned elimination: each thread eliminates the interior rows 0..M-2 of
-// its chunk (Thomas), which leaves one unknown per chunk -- its last row z_k --
-// in a "reduced" tridiagonal system of W rows.  In a wavefront tile the reduced
-// system has one row per lane and is solved by parallel cyclic reduction
-// through lane shuffles.  In a work-group tile the reduced rows are published
-// in LDS once (one barrier) and every wavefront then solves the whole
-// 256-row reduced system redundantly, as a wavefront tile with four rows per
-// lane, so that each wave obtains the z values it needs without a second
-// barrier.  What does not depend on the right-hand side (interior pivots,
-// reduced coefficients, PCR multipliers) is computed by tri_factor; tri_solve
-// costs two short FMA recurrences per thread, one LDS exchange with one
-// barrier (work-group tiles), and one shuffle PCR sweep.
-
-template <int W>
-__device__ __forceinline__ int tile_lane() { return (W == 64) ? (threadIdx.x & 63) : threadIdx.x; }
-
-// value of lane l + o of this wavefront (o may be negative); `dflt` outside the wave
-__device__ __forceinline__ double wave_nb(double v, int o, double dflt)
-{
-    const int l = threadIdx.x & 63;
-    const bool in = (l + o >= 0) && (l + o < 64);
-    const double r = __shfl(v, l + o, 64);
-    return in ? r : dflt;
-}
-
 // ---- lane exchanges without LDS: data-parallel moves of the two halves of a double
 template <int CTRL, int ROWS = 0xf, int BANKS = 0xf>
 __device__ __forceinline__ double dpp_mov(double old, double v)
@@ -86,371 +50,6 @@ __device__ __forceinline__ double add_halves(double v)
     return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
 }
 
-// LDS scratch (doubles) of a work-group tile's solver, sh[0, 14 W + 16):
-//   tri_factor        sh[0, 5W)            reduced-row exchange
-//   tri_solve         sh[5W + 2W ph, +2W)  right-hand-side exchange, two buffers
-//   tri_factor_solve  sh[7W ph, +7W)       both at once, two buffers
-//   tile_max2         sh[14W, 14W + 16)
-// (the `ph` buffers alternate so that one barrier per call suffices; a kernel
-// uses either tri_factor/tri_solve or tri_factor_solve on one scratch area).
-// Wavefront tiles need no scratch.  A work-group factorisation also keeps its
-// reduced-system data in LDS (red_doubles(), one region per live
-// factorisation, passed to tri_factor).
-template <int W>
-constexpr int tile_scratch() { return W == 256 ? 14 * W + 16 : 16; }
-constexpr int RED_FIELDS = 28;                 // per lane: ra, rc, rce (4 each), inv (3), k1, k2 (6 each), invB
-constexpr int red_doubles() { return RED_FIELDS * 64; }
-
-// parallel cyclic reduction of a 64-row tridiagonal (row l in lane l)
-struct WavePcr {
-    double k1[6], k2[6];
-    double invB;
-};
-
-__device__ __forceinline__ void wave_pcr_factor(double Aa, double Bb, double Cc, WavePcr &F)
-{
-#pragma unroll
-    for (int l = 0; l < 6; ++l) {
-        const int st = 1 << l;
-        const double Am = wave_nb(Aa, -st, 0.0), Bm = wave_nb(Bb, -st, 1.0), Cm = wave_nb(Cc, -st, 0.0);
-        const double Ap = wave_nb(Aa, st, 0.0), Bp = wave_nb(Bb, st, 1.0), Cp = wave_nb(Cc, st, 0.0);
-        const double k1 = Aa / Bm, k2 = Cc / Bp;
-        F.k1[l] = k1;
-        F.k2[l] = k2;
-        Aa = -Am * k1;
-        Cc = -Cp * k2;
-        Bb = Bb - Cm * k1 - Ap * k2;
-    }
-    F.invB = 1.0 / Bb;
-}
-
-__device__ __forceinline__ double wave_pcr_solve(double D, const WavePcr &F)
-{
-#pragma unroll
-    for (int l = 0; l < 6; ++l) {
-        const int st = 1 << l;
-        const double Dm = wave_nb(D, -st, 0.0), Dp = wave_nb(D, st, 0.0);
-        D = D - F.k1[l] * Dm - F.k2[l] * Dp;
-    }
-    return D * F.invB;
-}
-
-// interior rows 0..M-2 of one chunk with off-diagonals a[], c[] and diagonal
-// b[]: reciprocal pivots, and the responses of the interior to the previous
-// chunk's last unknown (Q) and to this chunk's last unknown (R)
-template <int M, class GetA, class GetC>
-__device__ __forceinline__ void chunk_factor(GetA a, GetC c, const double (&b)[M], double (&inv)[M - 1],
-                                             double (&Q)[M - 1], double (&R)[M - 1])
-{
-    static_assert(M >= 2, "at least two rows per thread");
-    double cprev;
-    {
-        const double iv = 1.0 / b[0];
-        inv[0] = iv;
-        cprev = (M > 2) ? c(0) * iv : 0.0;
-        Q[0] = -a(0) * iv;
-        R[0] = (M == 2) ? -c(0) * iv : 0.0;
-    }
-#pragma unroll
-    for (int r = 1; r < M - 1; ++r) {
-        const double ar = a(r), cr = c(r);
-        const double iv = 1.0 / (b[r] - ar * cprev);
-        inv[r] = iv;
-        Q[r] = -ar * Q[r - 1] * iv;
-        R[r] = ((r == M - 2 ? -cr : 0.0) - ar * R[r - 1]) * iv;
-        cprev = (r < M - 2) ? cr * iv : 0.0;
-    }
-#pragma unroll
-    for (int r = M - 3; r >= 0; --r) {
-        const double cp = c(r) * inv[r];
-        Q[r] -= cp * Q[r + 1];
-        R[r] -= cp * R[r + 1];
-    }
-}
-
-// forward elimination + back substitution over the interior rows 0..M-2
-template <int M, class GetA, class GetC>
-__device__ __forceinline__ void chunk_interior(GetA a, GetC c, const double (&inv)[M - 1], double (&y)[M - 1])
-{
-    y[0] = y[0] * inv[0];
-#pragma unroll
-    for (int r = 1; r < M - 1; ++r) y[r] = (y[r] - a(r) * y[r - 1]) * inv[r];
-#pragma unroll
-    for (int r = M - 3; r >= 0; --r) y[r] -= c(r) * inv[r] * y[r + 1];
-}
-
-// ---- wavefront tile, off-diagonals given by accessors a(r), c(r) of the lane's rows
-template <int M>
-struct WaveFac {
-    double inv[M - 1];
-    WavePcr pcr;
-};
-
-template <int M, class GetA, class GetC>
-__device__ __forceinline__ void wave_factor(GetA a, GetC c, const double (&b)[M], WaveFac<M> &F)
-{
-    double Q[M - 1], R[M - 1];
-    chunk_factor<M>(a, c, b, F.inv, Q, R);
-    const double Qn = wave_nb(Q[0], 1, 0.0), Rn = wave_nb(R[0], 1, 0.0);
-    const double ae = a(M - 1), ce = c(M - 1);
-    wave_pcr_factor(ae * Q[M - 2], ae * R[M - 2] + b[M - 1] + ce * Qn, ce * Rn, F.pcr);
-}
-
-template <int M, class GetA, class GetC>
-__device__ __forceinline__ void wave_solve(GetA a, GetC c, const WaveFac<M> &F, const double (&d)[M],
-                                           double (&x)[M])
-{
-    double y[M - 1];
-#pragma unroll
-    for (int r = 0; r < M - 1; ++r) y[r] = d[r];
-    chunk_interior<M>(a, c, F.inv, y);
-    const double yn = wave_nb(y[0], 1, 0.0);
-    const double z = wave_pcr_solve(d[M - 1] - a(M - 1) * y[M - 2] - c(M - 1) * yn, F.pcr);
-    const double zl = wave_nb(z, -1, 0.0);
-#pragma unroll
-    for (int r = 0; r < M - 1; ++r) y[r] = d[r];
-    y[0] -= a(0) * zl;
-    y[M - 2] -= c(M - 2) * z;
-    chunk_interior<M>(a, c, F.inv, y);
-#pragma unroll
-    for (int r = 0; r < M - 1; ++r) x[r] = y[r];
-    x[M - 1] = z;
-}
-
-// ---- the tile solver used by the kernels
-template <int W, int M>
-struct TriFac;
-
-template <int M>
-struct TriFac<64, M> {
-    WaveFac<M> w;
-};
-
-template <int M>
-struct TriFac<256, M> {
-    double inv[M - 1];        // interior pivots of this thread's chunk
-    double *red;              // LDS: the 256-row reduced system, four rows per lane (identical in every
-                              // wave): field f of lane l at red[64 f + l]
-};
-
-// reduced-system data of one lane, kept in registers while it is used
-struct RedFac {
-    double ra[4], rc[4];      // off-diagonals of the lane's four reduced rows
-    double rce[4];            // last-row super-diagonal c_e of the chunks of those rows
-    WaveFac<4> w;             // their wavefront factorisation
-};
-
-__device__ __forceinline__ void red_store(const RedFac &R, double *red)
-{
-    const int l = threadIdx.x & 63;
-    double v[RED_FIELDS];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[i] = R.ra[i];
-        v[4 + i] = R.rc[i];
-        v[8 + i] = R.rce[i];
-    }
-#pragma unroll
-    for (int i = 0; i < 3; ++i) v[12 + i] = R.w.inv[i];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        v[15 + i] = R.w.pcr.k1[i];
-        v[21 + i] = R.w.pcr.k2[i];
-    }
-    v[27] = R.w.pcr.invB;
-#pragma unroll
-    for (int f = 0; f < RED_FIELDS; ++f) red[64 * f + l] = v[f];
-}
-
-__device__ __forceinline__ void red_load(const double *red, RedFac &R)
-{
-    const int l = threadIdx.x & 63;
-    double v[RED_FIELDS];
-#pragma unroll
-    for (int f = 0; f < RED_FIELDS; ++f) v[f] = red[64 * f + l];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        R.ra[i] = v[i];
-        R.rc[i] = v[4 + i];
-        R.rce[i] = v[8 + i];
-    }
-#pragma unroll
-    for (int i = 0; i < 3; ++i) R.w.inv[i] = v[12 + i];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        R.w.pcr.k1[i] = v[15 + i];
-        R.w.pcr.k2[i] = v[21 + i];
-    }
-    R.w.pcr.invB = v[27];
-}
-
-// Factor.  LDS use (work-group tiles): sh[0, 5W) and the reduced-system region
-// `red` (red_doubles()), which must stay untouched while the factorisation is
-// used.  Every wave writes the same values to `red` and reads back its own
-// writes, so no barrier is needed after it.  The caller must separate two
-// factorisations that share sh (or red) by a barrier (a solve in between
-// provides one).
-template <int W, int M>
-__device__ __forceinline__ void tri_factor(double s, const double *Lo, const double *Up, const double (&b)[M],
-                                           TriFac<W, M> &F, double *sh, double *red = nullptr)
-{
-    const int k = tile_lane<W>();
-    auto a = [&](int r) { return s * Lo[r * W + k]; };
-    auto c = [&](int r) { return s * Up[r * W + k]; };
-    if constexpr (W == 64) {
-        wave_factor<M>(a, c, b, F.w);
-    } else {
-        double Q[M - 1], R[M - 1];
-        chunk_factor<M>(a, c, b, F.inv, Q, R);
-        double *fA = sh, *fB = sh + W, *fC = sh + 2 * W, *fQ = sh + 3 * W, *fR = sh + 4 * W;
-        const double ae = a(M - 1), ce = c(M - 1);
-        fA[k] = ae * Q[M - 2];
-        fB[k] = ae * R[M - 2] + b[M - 1];
-        fC[k] = ce;
-        fQ[k] = Q[0];
-        fR[k] = R[0];
-        __syncthreads();
-        // reduced row kk = 4 l + i couples z_{kk-1}, z_kk, z_{kk+1}
-        const int l = threadIdx.x & 63;
-        RedFac RF;
-        double rb[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int kk = 4 * l + i;
-            const double cek = fC[kk];
-            const double qn = (kk + 1 < W) ? fQ[kk + 1] : 0.0;
-            const double rn = (kk + 1 < W) ? fR[kk + 1] : 0.0;
-            RF.ra[i] = fA[kk];
-            rb[i] = fB[kk] + cek * qn;
-            RF.rc[i] = cek * rn;
-            RF.rce[i] = cek;
-        }
-        wave_factor<4>([&](int r) { return RF.ra[r]; }, [&](int r) { return RF.rc[r]; }, rb, RF.w);
-        red_store(RF, red);
-        F.red = red;
-    }
-}
-
-// Solve T x = d.  LDS use (work-group tiles): sh[5W, 9W), alternating halves
-// selected by `ph` (flipped by every call), so that one barrier per solve
-// suffices.
-template <int W, int M>
-__device__ __forceinline__ void tri_solve(double s, const double *Lo, const double *Up, const TriFac<W, M> &F,
-                                          const double (&d)[M], double (&x)[M], double *sh, int &ph)
-{
-    const int k = tile_lane<W>();
-    auto a = [&](int r) { return s * Lo[r * W + k]; };
-    auto c = [&](int r) { return s * Up[r * W + k]; };
-    if constexpr (W == 64) {
-        wave_solve<M>(a, c, F.w, d, x);
-    } else {
-        double y[M - 1];
-#pragma unroll
-        for (int r = 0; r < M - 1; ++r) y[r] = d[r];
-        chunk_interior<M>(a, c, F.inv, y);
-        double *bf = sh + 5 * W + 2 * W * ph;
-        ph ^= 1;
-        bf[k] = d[M - 1] - a(M - 1) * y[M - 2];
-        bf[W + k] = y[0];
-        __syncthreads();
-        const int l = threadIdx.x & 63;
-        RedFac RF;
-        red_load(F.red, RF);
-        double Dr[4], zr[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int kk = 4 * l + i;
-            const double yn = (kk + 1 < W) ? bf[W + kk + 1] : 0.0;
-            Dr[i] = bf[kk] - RF.rce[i] * yn;
-        }
-        wave_solve<4>([&](int r) { return RF.ra[r]; }, [&](int r) { return RF.rc[r]; }, RF.w, Dr, zr);
-        // z_k and z_{k-1} from the lanes that hold them (the same lanes in every wave)
-        const int src = k >> 2, sub = k & 3;
-        const double z0 = __shfl(zr[0], src, 64), z1 = __shfl(zr[1], src, 64);
-        const double z2 = __shfl(zr[2], src, 64), z3 = __shfl(zr[3], src, 64);
-        const double zp = __shfl(zr[3], src > 0 ? src - 1 : 0, 64);
-        const double z = sub == 0 ? z0 : sub == 1 ? z1 : sub == 2 ? z2 : z3;
-        const double zl = sub == 0 ? (k > 0 ? zp : 0.0) : sub == 1 ? z0 : sub == 2 ? z1 : z2;
-#pragma unroll
-        for (int r = 0; r < M - 1; ++r) y[r] = d[r];
-        y[0] -= a(0) * zl;
-        y[M - 2] -= c(M - 2) * z;
-        chunk_interior<M>(a, c, F.inv, y);
-#pragma unroll
-        for (int r = 0; r < M - 1; ++r) x[r] = y[r];
-        x[M - 1] = z;
-    }
-}
-
-// Factor and solve at once, for an operator used with one right-hand side
-// (nothing is kept): the reduced coefficients and the reduced right-hand side
-// are published together, so a work-group tile needs a single barrier.  LDS
-// use (work-group tiles): the solve buffers sh[5W, 9W) selected by `ph`.
-// (Lo, Up of the thread's row r at position base + r * rs; by default the
-// tile's position order, base = the thread's tile index, rs = W.)
-template <int W, int M>
-__device__ __forceinline__ void tri_factor_solve(double s, const double *Lo, const double *Up,
-                                                 const double (&b)[M], const double (&d)[M], double (&x)[M],
-                                                 double *sh, int &ph, int base = -1, int rs = W)
-{
-    const int k = tile_lane<W>();
-    if (base < 0) base = k;
-    auto a = [&](int r) { return s * Lo[base + r * rs]; };
-    auto c = [&](int r) { return s * Up[base + r * rs]; };
-    if constexpr (W == 64) {
-        WaveFac<M> F;
-        wave_factor<M>(a, c, b, F);
-        wave_solve<M>(a, c, F, d, x);
-    } else {
-        double inv[M - 1], Q[M - 1], R[M - 1], y[M - 1];
-        chunk_factor<M>(a, c, b, inv, Q, R);
-#pragma unroll
-        for (int r = 0; r < M - 1; ++r) y[r] = d[r];
-        chunk_interior<M>(a, c, inv, y);
-        // one exchange: A, B-part, c_e, Q[0], R[0], D-part, y[0] of every chunk
-        double *rg = sh + 7 * W * ph;
-        ph ^= 1;
-        const double ae = a(M - 1), ce = c(M - 1);
-        rg[k] = ae * Q[M - 2];
-        rg[W + k] = ae * R[M - 2] + b[M - 1];
-        rg[2 * W + k] = ce;
-        rg[3 * W + k] = Q[0];
-        rg[4 * W + k] = R[0];
-        rg[5 * W + k] = d[M - 1] - ae * y[M - 2];
-        rg[6 * W + k] = y[0];
-        __syncthreads();
-        const int l = threadIdx.x & 63;
-        double ra[4], rb[4], rc[4], Dr[4], zr[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int kk = 4 * l + i;
-            const bool nx = kk + 1 < W;
-            const double cek = rg[2 * W + kk];
-            ra[i] = rg[kk];
-            rb[i] = rg[W + kk] + cek * (nx ? rg[3 * W + kk + 1] : 0.0);
-            rc[i] = cek * (nx ? rg[4 * W + kk + 1] : 0.0);
-            Dr[i] = rg[5 * W + kk] - cek * (nx ? rg[6 * W + kk + 1] : 0.0);
-        }
-        WaveFac<4> RF;
-        wave_factor<4>([&](int r) { return ra[r]; }, [&](int r) { return rc[r]; }, rb, RF);
-        wave_solve<4>([&](int r) { return ra[r]; }, [&](int r) { return rc[r]; }, RF, Dr, zr);
-        const int src = k >> 2, sub = k & 3;
-        const double z0 = __shfl(zr[0], src, 64), z1 = __shfl(zr[1], src, 64);
-        const double z2 = __shfl(zr[2], src, 64), z3 = __shfl(zr[3], src, 64);
-        const double zp = __shfl(zr[3], src > 0 ? src - 1 : 0, 64);
-        const double z = sub == 0 ? z0 : sub == 1 ? z1 : sub == 2 ? z2 : z3;
-        const double zl = sub == 0 ? (k > 0 ? zp : 0.0) : sub == 1 ? z0 : sub == 2 ? z1 : z2;
-#pragma unroll
-        for (int r = 0; r < M - 1; ++r) y[r] = d[r];
-        y[0] -= a(0) * zl;
-        y[M - 2] -= c(M - 2) * z;
-        chunk_interior<M>(a, c, inv, y);
-#pragma unroll
-        for (int r = 0; r < M - 1; ++r) x[r] = y[r];
-        x[M - 1] = z;
-    }
-}
-
 // -------------------------------------------------------------------------
 // a wavefront's solver with many rows per lane (slab_tile.hpp)
 // -------------------------------------------------------------------------
@@ -469,95 +68,352 @@ __device__ __forceinline__ double rcp64(double v)
     return fma(r, e, r);
 }
 
-// max over the tile of two values at once (fixed order; same result in every tile thread)
-template <int W>
-__device__ __forceinline__ void tile_max2(double &a, double &b, double *sh)
+// the largest of the wavefront's non-negative values, in every lane
+__device__ __forceinline__ double wave_max(double v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a = fmax(a, __shfl_xor(a, o, 64));
-        b = fmax(b, __shfl_xor(b, o, 64));
-    }
-    if constexpr (W == 256) {
-        double *m2 = sh + 14 * W;
-        const int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) {
-            m2[w] = a;
-            m2[8 + w] = b;
-        }
-        __syncthreads();
-        a = m2[0];
-        b = m2[8];
-#pragma unroll
-        for (int q = 1; q < W / 64; ++q) {
-            a = fmax(a, m2[q]);
-            b = fmax(b, m2[8 + q]);
-        }
-        __syncthreads();
+    v = fmax(v, dpp_mov<0x111>(v, v));                    // lane - 1, - 2, - 4, - 8 of the row (0 past its end)
+    v = fmax(v, dpp_mov<0x112>(v, v));
+    v = fmax(v, dpp_mov<0x114>(v, v));
+    v = fmax(v, dpp_mov<0x118>(v, v));
+    return fmax(fmax(lane_at(v, 15), lane_at(v, 31)), fmax(lane_at(v, 47), lane_at(v, 63)));
+}
+
+// The values next to the boundary of the two blocks of 2^L lanes that level L
+// merges.  L <= 2: p the other block's, q the own block's; L >= 3: p the lower
+// block's last lane's, q the upper block's first lane's.
+template <int L>
+__device__ __forceinline__ void boundary(double u, double &p, double &q)
+{
+    if constexpr (L == 0) {
+        p = dpp_mov<quad(1, 0, 3, 2)>(u, u);
+        q = u;
+    } else if constexpr (L == 1) {
+        p = dpp_mov<quad(2, 2, 1, 1)>(u, u);
+        q = dpp_mov<quad(1, 1, 2, 2)>(u, u);
+    } else if constexpr (L == 2) {
+        q = dpp_mov<quad(3, 3, 3, 3), 0xf, 0x5>(u, u);
+        q = dpp_mov<quad(0, 0, 0, 0), 0xf, 0xa>(q, u);
+        p = dpp_mov<DPP_HALF_MIRROR>(q, q);
+    } else if constexpr (L == 3) {
+        p = dpp_mov<DPP_ROW_BCAST + 7>(u, u);
+        q = dpp_mov<DPP_ROW_BCAST + 8>(u, u);
+    } else if constexpr (L == 4) {
+        double e = dpp_mov<DPP_ROW_BCAST + 15, 0x5>(u, u);
+        e = dpp_mov<DPP_ROW_BCAST, 0xa>(e, u);
+        // swapping e's odd rows with its own even rows leaves the even rows' value
+        // everywhere in one result, the odd rows' in the other
+        const long long x = __double_as_longlong(e);
+        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(x >> 32), false, false);
+        p = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
+        q = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+    } else {
+        p = lane_at(u, 31);
+        q = lane_at(u, 32);
     }
 }
 
-// sum over the tile of two values at once (fixed order: a butterfly within
-// each wavefront, then the wavefronts' sums in wave order; result in every
-// tile thread), exchanging through the 16 doubles at m2 (work-group tiles)
-template <int W>
-__device__ __forceinline__ void tile_sum2_at(double &a, double &b, double *m2)
+// Level L of the separators' factorisation.  A block's values are x = u + w x_left +
+// v x_right for the values x_left, x_right next to it.  Merging a lower block (last
+// lane: uA, vA, wA) with an upper one (first lane: uB, vB, wB) gives
+//   x_A = (uA + vA uB) / (1 - vA wB),  x_B = (uB + wB uA) / (1 - vA wB);
+// the lower lanes add v x_B, the upper ones w x_A.
+template <int L>
+__device__ __forceinline__ void merge_factor(int lane, double &v, double &w, double (&k)[12])
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o, 64);
-        b += __shfl_xor(b, o, 64);
-    }
-    if constexpr (W == 256) {
-        const int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) {
-            m2[w] = a;
-            m2[8 + w] = b;
-        }
-        __syncthreads();
-        a = m2[0];
-        b = m2[8];
-#pragma unroll
-        for (int q = 1; q < W / 64; ++q) {
-            a += m2[q];
-            b += m2[8 + q];
-        }
-        __syncthreads();
-    }
+    const bool low = ((lane >> L) & 1) == 0;
+    double vp, vq, wp, wq;
+    boundary<L>(v, vp, vq);
+    boundary<L>(w, wp, wq);
+    const double vA = L >= 3 ? vp : low ? vq : vp, vB = L >= 3 ? vq : low ? vp : vq;
+    const double wA = L >= 3 ? wp : low ? wq : wp, wB = L >= 3 ? wq : low ? wp : wq;
+    const double s = (low ? v : w) * rcp64(fma(-vA, wB, 1.0));
+    const double cA = low ? s * wB : s, cB = low ? s : s * vA;
+    v = low ? cB * vB : fma(cB, vB, v);
+    w = low ? fma(cA, wA, w) : cA * wA;
+    k[2 * L] = L >= 3 ? cA : low ? cB : cA;
+    k[2 * L + 1] = L >= 3 ? cB : low ? cA : cB;
 }
 
-// the same with the 16-double exchange area at sh + 14 W (the solver scratch)
-template <int W>
-__device__ __forceinline__ void tile_sum2(double &a, double &b, double *sh)
+template <int L>
+__device__ __forceinline__ void merge_solve(double &u, const double (&k)[12])
 {
-    tile_sum2_at<W>(a, b, sh + 14 * W);
+    double p, q;
+    boundary<L>(u, p, q);
+    u = fma(k[2 * L], p, fma(k[2 * L + 1], q, u));
 }
 
-// block-wide max of a non-negative value (fixed order; result in every thread)
-__device__ __forceinline__ double block_max(double v, double *sh)
+template <int V>
+struct Int {
+    static constexpr int v = V;
+};
+// -------------------------------------------------------------------------
+// a work-group's tridiagonal solver
+// -------------------------------------------------------------------------
+// Tridiagonal solve by the work-group: row M k + r is thread k's row r, a, b, c its sub-,
+// main and super-diagonal (a = 0 in the first row, c = 0 in the last; padding rows a = c =
+// 0, b = 1), x the right-hand side in, the solution out.  The threads' rows but their last
+// are eliminated, the last rows of a wavefront merged by blocks of 1, 2, .. 32 lanes
+// (merge_factor), and what a wavefront's first and last value answer to its neighbours'
+// goes through LDS as lanes 2 w, 2 w + 1 of one more such merge, which every wavefront
+// does on its own.  Two barriers (three for M > 1).
+template <int NW, int M>
+__device__ __forceinline__ void tri_wg(const double (&a)[M], const double (&b)[M], const double (&c)[M], double (&x)[M])
 {
-    const int k = threadIdx.x;
-    sh[k] = v;
+    static_assert((NW & (NW - 1)) == 0 && NW <= 32, "the wavefronts' ends are the lanes of one wavefront");
+    __shared__ double sEnd[3][2 * NW], sFirst[3][NW + 1];
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double inv[M], fl[M], cp = 0.0;
+    double W0 = 0.0, A0 = 0.0, C0 = 1.0;               // first row = W0 + A0 z_left + C0 z (M > 1)
+#pragma unroll
+    for (int i = 0; i < M - 1; ++i) {
+        inv[i] = rcp64(i > 0 ? b[i] - a[i] * cp : b[i]);
+        x[i] = (i > 0 ? x[i] - a[i] * x[i - 1] : x[i]) * inv[i];
+        fl[i] = (i > 0 ? -a[i] * fl[i - 1] : -a[i]) * inv[i];
+        W0 = fma(C0, x[i], W0);
+        A0 = fma(C0, fl[i], A0);
+        cp = c[i] * inv[i];
+        C0 = -C0 * cp;
+    }
+    double B = b[M - 1], A = a[M - 1], C = c[M - 1], D = x[M - 1];
+    if constexpr (M > 1) {
+        if (l == 0) {
+            sFirst[0][w] = W0;
+            sFirst[1][w] = A0;
+            sFirst[2][w] = C0;
+        }
+        if (threadIdx.x < 3) sFirst[threadIdx.x][NW] = 0.0;
+        __syncthreads();
+        double Wn = dpp_mov<DPP_NEXT>(W0, W0), An = dpp_mov<DPP_NEXT>(A0, A0), Cn = dpp_mov<DPP_NEXT>(C0, C0);
+        if (l == 63) {
+            Wn = sFirst[0][w + 1];
+            An = sFirst[1][w + 1];
+            Cn = sFirst[2][w + 1];
+        }
+        D -= A * x[M > 1 ? M - 2 : 0] + C * Wn;
+        B += C * An - A * cp;
+        A *= fl[M > 1 ? M - 2 : 0];
+        C *= Cn;
+    }
+    const double ib = rcp64(B);
+    double u = D * ib, wl = -A * ib, vr = -C * ib, k[12];
+    auto merge = [&](auto L) {
+        merge_factor<L.v>(l, vr, wl, k);
+        merge_solve<L.v>(u, k);
+    };
+    merge(Int<0>());
+    merge(Int<1>());
+    merge(Int<2>());
+    merge(Int<3>());
+    merge(Int<4>());
+    merge(Int<5>());
+    if (l == 0 || l == 63) {
+        const int e = 2 * w + (l > 0);
+        sEnd[0][e] = u;
+        sEnd[1][e] = vr;
+        sEnd[2][e] = wl;
+    }
     __syncthreads();
-#pragma unroll 1
-    for (int s = NT / 2; s > 0; s >>= 1) {
-        if (k < s) sh[k] = fmax(sh[k], sh[k + s]);
-        __syncthreads();
+    double xl, xr;                                     // the values next to the wavefront's rows
+    {
+        const double u0 = u, v0 = vr, w0 = wl;
+        u = l < 2 * NW ? sEnd[0][l] : 0.0;
+        vr = l < 2 * NW ? sEnd[1][l] : 0.0;
+        wl = l < 2 * NW ? sEnd[2][l] : 0.0;
+        if constexpr (NW > 1) merge(Int<1>());
+        if constexpr (NW > 2) merge(Int<2>());
+        if constexpr (NW > 4) merge(Int<3>());
+        if constexpr (NW > 8) merge(Int<4>());
+        if constexpr (NW > 16) merge(Int<5>());
+        xl = w > 0 ? lane_at(u, w > 0 ? 2 * w - 1 : 0) : 0.0;
+        xr = w < NW - 1 ? lane_at(u, w < NW - 1 ? 2 * w + 2 : 0) : 0.0;
+        u = fma(v0, xr, fma(w0, xl, u0));
     }
-    const double r = sh[0];
+    x[M - 1] = u;
+    if constexpr (M > 1) {
+        double zl = dpp_mov<DPP_PREV>(u, u);
+        if (l == 0) zl = xl;
+#pragma unroll
+        for (int i = M - 2; i >= 0; --i) x[i] = fma(fl[i], zl, x[i]) - c[i] * inv[i] * x[i + 1];
+    }
+}
+
+// The same solve in two parts, for an operator with many right-hand sides: wg_factor once,
+// wg_solve per right-hand side (one barrier).  A wavefront's last row sees the first row of
+// the next wavefront, x = W0 + A0 z + C0 z'; its response vr is to W0 + C0 z', so that
+// nothing has to pass between the wavefronts before the merges.  The two ends' buffers in
+// LDS alternate (ph).
+template <int NW>
+struct WgLds {
+    double a0[NW + 1], c0[NW + 1], ev[2 * NW], ew[2 * NW];
+    double u[2][2 * NW], w0[2][NW + 1];
+};
+constexpr int WG_KEEP = 8;                      // rows per thread up to which a / pivot and c / pivot are kept
+template <int M>
+struct WgFac {
+    static constexpr int NK = M <= WG_KEEP ? M - 1 : 1;
+    double inv[M - 1], av[NK], cv[NK];          // interior rows: 1 / pivot, a / pivot, c / pivot
+    double as, cs, ib;                          // last row: a, c, 1 / pivot
+    double k[12], wl, vr;                       // its merges within the wavefront; responses to the rows next to it
+    double kq[12], ve, cx;                      // the wavefronts' ends
+};
+
+template <int NW, int M, class GA, class GC>
+__device__ __forceinline__ void wg_factor(GA a, const double (&b)[M], GC c, WgFac<M> &F, WgLds<NW> &S)
+{
+    static_assert(M >= 2 && (NW == 2 || NW == 4), "rows per thread; levels of the ends' merge below");
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double A0 = 0.0, C0 = 1.0, f = 1.0, cp = 0.0;
+#pragma unroll
+    for (int i = 0; i < M - 1; ++i) {
+        const double ai = a(i);
+        F.inv[i] = rcp64(i > 0 ? b[i] - ai * cp : b[i]);
+        const double av = ai * F.inv[i];
+        cp = c(i) * F.inv[i];
+        if constexpr (M <= WG_KEEP) {
+            F.av[i] = av;
+            F.cv[i] = cp;
+        }
+        f = -f * av;
+        A0 = fma(C0, f, A0);
+        C0 = -C0 * cp;
+    }
+    if (l == 0) {
+        S.a0[w] = A0;
+        S.c0[w] = C0;
+    }
+    if (threadIdx.x == 0) S.a0[NW] = S.c0[NW] = S.w0[0][NW] = S.w0[1][NW] = 0.0;
     __syncthreads();
-    return r;
+    double An = dpp_mov<DPP_NEXT>(A0, A0), Cn = dpp_mov<DPP_NEXT>(C0, C0);
+    if (l == 63) {
+        An = S.a0[w + 1];
+        Cn = 1.0;
+    }
+    F.cx = S.c0[w + 1];
+    F.as = a(M - 1);
+    F.cs = c(M - 1);
+    F.ib = rcp64(b[M - 1] - F.as * cp + F.cs * An);
+    double wl = -(F.as * f) * F.ib, vr = -(F.cs * Cn) * F.ib;
+    merge_factor<0>(l, vr, wl, F.k);
+    merge_factor<1>(l, vr, wl, F.k);
+    merge_factor<2>(l, vr, wl, F.k);
+    merge_factor<3>(l, vr, wl, F.k);
+    merge_factor<4>(l, vr, wl, F.k);
+    merge_factor<5>(l, vr, wl, F.k);
+    F.wl = wl;
+    F.vr = vr;
+    if (l == 0 || l == 63) {
+        S.ev[2 * w + (l > 0)] = vr;
+        S.ew[2 * w + (l > 0)] = wl;
+    }
+    __syncthreads();
+    const bool end = l < 2 * NW;
+    F.ve = end ? S.ev[l] : 0.0;
+    vr = end ? F.ve * S.c0[(l >> 1) + 1] : 0.0;
+    wl = end ? S.ew[l] : 0.0;
+    merge_factor<1>(l, vr, wl, F.kq);
+    if constexpr (NW > 2) merge_factor<2>(l, vr, wl, F.kq);
+}
+
+// x: right-hand side in, solution out; a, c as given to wg_factor
+template <int NW, int M, class GA, class GC>
+__device__ __forceinline__ void wg_solve(GA a, GC c, const WgFac<M> &F, double (&x)[M], WgLds<NW> &S, int &ph)
+{
+    auto av = [&](int i) {
+        if constexpr (M <= WG_KEEP) return F.av[i];
+        else return a(i) * F.inv[i];
+    };
+    auto cv = [&](int i) {
+        if constexpr (M <= WG_KEEP) return F.cv[i];
+        else return c(i) * F.inv[i];
+    };
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double W0 = 0.0, pr = 1.0;
+#pragma unroll
+    for (int i = 0; i < M - 1; ++i) {
+        x[i] = i > 0 ? fma(-av(i), x[i - 1], x[i] * F.inv[i]) : x[0] * F.inv[0];
+        W0 = fma(pr, x[i], W0);
+        pr = -pr * cv(i);
+    }
+    double u = (x[M - 1] - F.as * x[M - 2] - F.cs * dpp_mov<DPP_NEXT>(W0, W0)) * F.ib;
+    merge_solve<0>(u, F.k);
+    merge_solve<1>(u, F.k);
+    merge_solve<2>(u, F.k);
+    merge_solve<3>(u, F.k);
+    merge_solve<4>(u, F.k);
+    merge_solve<5>(u, F.k);
+    if (l == 0) {
+        S.u[ph][2 * w] = u;
+        S.w0[ph][w] = W0;
+    }
+    if (l == 63) S.u[ph][2 * w + 1] = u;
+    __syncthreads();
+    double e = l < 2 * NW ? fma(F.ve, S.w0[ph][(l >> 1) + 1], S.u[ph][l]) : 0.0;
+    merge_solve<1>(e, F.kq);
+    if constexpr (NW > 2) merge_solve<2>(e, F.kq);
+    const double xl = w > 0 ? lane_at(e, w > 0 ? 2 * w - 1 : 0) : 0.0;
+    const double xr = w < NW - 1 ? fma(F.cx, lane_at(e, w < NW - 1 ? 2 * w + 2 : 0), S.w0[ph][w + 1]) : 0.0;
+    ph ^= 1;
+    u = fma(F.vr, xr, fma(F.wl, xl, u));
+    x[M - 1] = u;
+    double f = dpp_mov<DPP_PREV>(u, u);
+    if (l == 0) f = xl;
+#pragma unroll
+    for (int i = 0; i < M - 1; ++i) {
+        f = -f * av(i);
+        x[i] += f;
+    }
+#pragma unroll
+    for (int i = M - 2; i >= 0; --i) x[i] = fma(-cv(i), x[i + 1], x[i]);
+}
+
+// the largest over the work-group of two non-negative values each (the same in every
+// thread; its barrier also separates the caller's LDS writes from what follows; another
+// barrier must lie between two calls)
+template <int NW>
+__device__ __forceinline__ void wg_max2(double &a, double &b)
+{
+    __shared__ double m2[2][NW];
+    a = wave_max(a);
+    b = wave_max(b);
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        m2[0][w] = a;
+        m2[1][w] = b;
+    }
+    __syncthreads();
+    a = m2[0][0];
+    b = m2[1][0];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) {
+        a = fmax(a, m2[0][q]);
+        b = fmax(b, m2[1][q]);
+    }
 }
 
 // -------------------------------------------------------------------------
-// barrier over a set of co-resident work-groups of a cooperative launch
+// exchange and barrier over a set of co-resident work-groups of a cooperative launch
 // -------------------------------------------------------------------------
+// What the work-groups pass to each other between barriers goes through agent-scope
+// accesses of single words: they bypass the caches that the dies do not share, so that
+// the barrier needs no write-back and no invalidation of an L2.
+__device__ __forceinline__ void agent_put(double *p, double v)
+{
+    __hip_atomic_store((unsigned long long *)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double agent_get(const double *p)
+{
+    return __longlong_as_double((long long)__hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT));
+}
+
 // The set is `nblk` work-groups whose member index is `bid` (0..nblk-1), with
 // their own flag array.  Every work-group publishes the generation number in
-// its own flag (no contended counter); lanes of wave 0 watch one flag each.  Each thread makes
-// its own global writes visible at agent scope before the work-group
-// barrier, and the flag store is a release, so the writes are visible on every
-// XCD to a work-group that has observed the flag and executed the acquire.
+// its own flag (no contended counter); lanes of wave 0 watch one flag each.  Every
+// wavefront waits until its own puts have reached the level that all dies share before
+// the work-group barrier ahead of the flag, and the gets behind the closing barrier are
+// issued after the flags were seen.  Ordinary stores are not made visible.
 // The wait is bounded: on a timeout, or when another work-group has already
 // reported one, the error flag is raised and false is returned so that every
 // work-group leaves the iteration instead of hanging the device.
@@ -565,14 +421,11 @@ __device__ __forceinline__ bool grid_barrier(unsigned long long *flags, unsigned
                                              int bid, int nblk)
 {
     __shared__ int s_fail;
-    // The work-group barrier orders every wave's prior stores before thread 0's
-    // agent-scope release, whose write-back covers the work-group's data (one
-    // write-back per work-group rather than one per wave).
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         s_fail = 0;
-        __hip_atomic_store(&flags[(size_t)bid * BAR_STRIDE], gen, __ATOMIC_RELEASE,
-                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&flags[(size_t)bid * BAR_STRIDE], gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (threadIdx.x < 64) {
         bool fail = false;
@@ -585,14 +438,13 @@ __device__ __forceinline__ bool grid_barrier(unsigned long long *flags, unsigned
                     fail = true;
                     break;
                 }
-                __builtin_amdgcn_s_sleep(2);
+                __builtin_amdgcn_s_sleep(1);
             }
         }
         if (fail) {
             atomicOr(err, 1);
             s_fail = 1;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
     return s_fail == 0;
