@@ -69,7 +69,7 @@
 
 #include "../../include/grte.h"
 
-#include "solver_common.hpp"
+#include "slab_tile.hpp"
 #include "mlp_common.hpp"
 
 namespace {
@@ -81,6 +81,7 @@ namespace {
 // every context, each context synchronising only its own work-groups).
 constexpr int GMAX = 4;
 constexpr int NSTAT = 16;    // per-step counters of a context
+constexpr int NSTAT_ALL = NSTAT + 4;     // and the two 64-bit maxima of a Picard update of the reference scheme
 constexpr int STAT_STICKY = NSTAT - 1;   // error flags OR-ed over steps (GRTE_ERRF_*), cleared on request
 
 template <class Args>
@@ -107,7 +108,8 @@ struct CoefArgs {
     int M;                       // rows per thread of the prediction kernel (for Gt)
     double *Dl, *Dd, *Du;        // diffusion operator (prediction only)
     double *rho_n;               // sum_p omega_p E^n_p (prediction only)
-    double *r;                   // right-hand sides, pair-major position order [p*NT*M + row_pos(j)]
+    double *r;                   // right-hand sides, pair-major cell order [p * NP + j]
+    int NP;                      // padded rows of a pair
     int *stat;                   // cleared by the prediction pass
 };
 
@@ -134,7 +136,7 @@ __device__ __forceinline__ void coef_body(const CoefArgs &A)
     const int N = A.N, P = A.P, cpb = A.cpb;
     const int c0 = blockIdx.x * cpb;
     const int t = threadIdx.x;
-    if (A.mode == 0 && blockIdx.x == 0 && t < STAT_STICKY) A.stat[t] = 0;   // the sticky word survives
+    if (A.mode == 0 && blockIdx.x == 0 && t < NSTAT_ALL && t != STAT_STICKY) A.stat[t] = 0;   // the sticky word survives
     // ---- per cell
     if (t < cpb && c0 + t < N) {
         const int j = c0 + t;
@@ -207,7 +209,7 @@ __device__ __forceinline__ void coef_body(const CoefArgs &A)
         double rv = s_keps[cl] * En + s_src[cl] - h * mu * (s_awr[cl] * On_r - s_awl[cl] * On_l);
         if (j == 0) rv += 2.0 * h * mu * A.bL[p] / A.eps;
         if (j == N - 1) rv += 2.0 * h * mu * A.bR[p] / A.eps;
-        A.r[(size_t)p * NT * A.M + (j % A.M) * NT + j / A.M] = rv;   // pair-major, position order
+        A.r[(size_t)p * A.NP + j] = rv;                               // pair-major, cell order
         if (A.mode == 0) s_w[t] = A.omega[p] * En;
     }
     if (A.mode == 0) {
@@ -236,10 +238,11 @@ __global__ void __launch_bounds__(256) coef_kernel(Group<CoefArgs> G)
 struct PredArgs {
     int N, P, maxit;
     int accel;                         // 0 Richardson, 1 adaptive Chebyshev (see cheb_coeffs)
-    double tol, one_minus_W, mu2avg;   // mu2avg = sum_p omega_p mu_p^2 (diffusion operator)
+    double tol, one_minus_W, mu1avg, mu2avg;   // sum_p omega_p mu_p, sum_p omega_p mu_p^2 (diffusion operator)
     const double *Ll, *Lu, *Lam, *LmG, *Bd, *Dd;   // cell order; diffusion off-diagonals are mu2avg * L
     const double *Gt;                  // G in position order (padded entries zero)
-    const double *r, *mu, *omega, *rho0;
+    const double *r, *mu, *omega, *rho0;   // r: pair-major, cell order [p*NP + j], zero in padded rows
+    double *fac;                       // factorisations of the one-work-group form (pred_tile)
     double *part;                      // omega_p v_p, pair-major, position order [p*NP + t]
     double *res;                       // position order
     double *estar;                     // E* of the final iterate, cell-major [j*P + p]
@@ -248,6 +251,7 @@ struct PredArgs {
     double *hist;                      // max|z| / max|rho| of each update (first HIST_CAP)
     unsigned long long *flags;
     unsigned long long gen0;
+    int NP;                            // padded rows of a pair
     int direct;                        // every work-group sums all rows itself (one barrier per update)
 };
 
@@ -327,7 +331,7 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
 #pragma unroll
     for (int r = 0; r < M; ++r) {
         const int j = j0 + r;
-        rr[r] = A.r[(size_t)p * NP + r * NT + k];
+        rr[r] = A.r[(size_t)p * NP + j];
         gg[r] = A.Gt[r * NT + k];
         lmg[r] = (j < N) ? A.LmG[j] : 0.0;
     }
@@ -482,6 +486,51 @@ __global__ void __launch_bounds__(NT) pred_kernel(Group<PredArgs> G)
     while (g + 1 < G.n && (int)blockIdx.x >= G.first[g + 1]) ++g;
     const PredArgs A = G.a[g];
     pred_body<M>(A, (int)blockIdx.x - G.first[g], G.first[g + 1] - G.first[g]);
+}
+
+// The prediction of small slabs: one work-group per context (slab_tile.hpp), no exchange
+// between work-groups and so no cooperative launch.
+constexpr int TILE_NW = 8, TILE_MAX_M = 8;
+
+template <int M>
+__global__ void __launch_bounds__(64 * TILE_NW) pred_tile_kernel(Group<PredArgs> G)
+{
+    __shared__ double sm[tile_lds<TILE_NW, M>()];
+    const PredArgs A = G.a[blockIdx.x];
+    const int N = A.N, P = A.P;
+    TileSys S;
+    S.N = N;
+    S.P = P;
+    S.mu = A.mu;
+    S.om = A.omega;
+    S.Ll = A.Ll;
+    S.Lu = A.Lu;
+    S.Lam = A.Lam;
+    S.LmG = A.LmG;
+    S.bd0 = A.Bd[0];
+    S.bdN = A.Bd[N - 1];
+    S.mu1 = A.mu1avg;
+    S.mu2 = A.mu2avg;
+    S.omw = A.one_minus_W;
+    S.rhs = A.r;
+    S.rhs_stride = A.NP;
+    S.rho0 = A.rho0;
+    S.rho_out = A.rho_out;
+    S.fac = A.fac;
+    S.accel = A.accel;
+    S.maxit = A.maxit;
+    S.tol = A.tol;
+    S.hist = A.hist;
+    int converged = 0;
+    const int it = pred_tile<TILE_NW, M>(S, sm, converged, [&](int p, int j0, const double (&x)[M]) {
+#pragma unroll
+        for (int r = 0; r < M; ++r)
+            if (j0 + r < N) A.estar[(size_t)(j0 + r) * P + p] = x[r];
+    });
+    if (threadIdx.x == 0) {
+        A.stat[0] = it;
+        A.stat[1] = converged;
+    }
 }
 
 // -------------------------------------------------------------------------
@@ -676,7 +725,7 @@ __global__ void __launch_bounds__(NT) corr_kernel(Group<CorrArgs> G)
             a[r] = mu2 * ll;
             c[r] = mu2 * lu;
             b[r] = A.Lam[j] + mu2 * (-(ll + lu)) + mu * A.Bd[j];
-            x[r] = A.r[(size_t)p * NP + r * NT + k];
+            x[r] = A.r[(size_t)p * NP + j];
         } else {
             a[r] = c[r] = x[r] = 0.0;
             b[r] = 1.0;
@@ -857,7 +906,7 @@ __global__ void __launch_bounds__(256) energy_final_kernel(Group<ProjArgs> G)
 // rho_J / (eps K Cv), and the projection (4.14).  Needs sigma0 > 0.
 // -------------------------------------------------------------------------
 struct AltArgs {
-    int N, P, m, cpb, M;
+    int N, P, m, cpb, NP;
     double a, c, cv, eps, dt, dx;
     const double *Tn, *sigma0, *mu, *omega, *bL, *bR;
     const double *En, *On, *Es, *Os, *Us;   // E^n, O^n, E*, O* (cell-major), U*
@@ -933,7 +982,7 @@ __global__ void __launch_bounds__(256) alt_coef_kernel(Group<AltArgs> G)
         } else {
             rv += -h * mu * (ar - al);
         }
-        A.r[(size_t)p * NT * A.M + (j % A.M) * NT + j / A.M] = rv;   // pair-major, position order
+        A.r[(size_t)p * A.NP + j] = rv;                               // pair-major, cell order
     }
 }
 
@@ -1064,11 +1113,6 @@ __global__ void __launch_bounds__(256) picard_update_kernel(int N, double ac, co
     }
 }
 
-__global__ void clear_u64(unsigned long long *x, int n)
-{
-    if ((int)threadIdx.x < n) x[threadIdx.x] = 0ull;
-}
-
 // O at every node from cell values E (cell-major) through the node relation
 __global__ void node_all_kernel(int N, int P, double eps, const double *E, const double *O, const double *Aw,
                                 const double *Bc, const double *mu, const double *bL, const double *bR, double *Oout)
@@ -1147,6 +1191,7 @@ struct grte_ctx {
     double *sigma0, *mu, *omega, *bL, *bR;
     double *Ll, *Lu, *Lam, *LmG, *Gt, *Bd, *Aw, *Bc, *beta, *Dl, *Dd, *Du, *rho_n;
     double *r, *part, *res, *estar, *rho;
+    double *fac = nullptr;        // factorisations of the one-work-group prediction (small slabs)
     double *ustar, *Dv, *ostar, *rho1, *rstar;
     // binary32 storage of the intensity state (f32 != 0): E as E - a c T^4, and O;
     // the binary64 E, O buffers then serve as scratch
@@ -1273,6 +1318,40 @@ grte_status launch_pred(hipStream_t stream, Group<PredArgs> &g, int grid, bool c
     HIPCHK(hipLaunchCooperativeKernel((const void *)pred_kernel<M>, dim3(grid), dim3(NT), args,
                                       (unsigned)pred_lds_bytes<M>(), stream));
     return GRTE_OK;
+}
+
+// The one-work-group form up to TILE_MAX_M rows per lane and TILE_MAX_P pairs: a whole step
+// of 100 cells x 8 pairs 63 us against 116 with a work-group per pair and a cooperative
+// launch, 128 x 32 107 against 147, 512 x 16 106 against 139; at 512 x 32 both take 147, at
+// 512 x 64 246 against 176 (each of the eight wavefronts has eight pairs in turn).
+constexpr int TILE_MAX_P = 32;
+bool pred_tiled(int N, int P) { return N <= 64 * TILE_MAX_M && P <= TILE_MAX_P; }
+
+// The prediction of the group's contexts (M: rows per thread of the form with a
+// work-group per pair, grid: its work-groups)
+grte_status launch_prediction(hipStream_t stream, Group<PredArgs> &g, int M, int grid, bool coop)
+{
+    int rows = 0;
+    bool tiled = true;
+    for (int k = 0; k < g.n; ++k) {
+        rows = std::max(rows, (g.a[k].N + 63) / 64);
+        tiled = tiled && pred_tiled(g.a[k].N, g.a[k].P);
+    }
+    if (tiled) {
+        const dim3 b(64 * TILE_NW);
+        if (rows <= 2) hipLaunchKernelGGL(pred_tile_kernel<2>, dim3(g.n), b, 0, stream, g);
+        else if (rows <= 4) hipLaunchKernelGGL(pred_tile_kernel<4>, dim3(g.n), b, 0, stream, g);
+        else if (rows <= 6) hipLaunchKernelGGL(pred_tile_kernel<6>, dim3(g.n), b, 0, stream, g);
+        else hipLaunchKernelGGL(pred_tile_kernel<8>, dim3(g.n), b, 0, stream, g);
+        HIPCHK(hipGetLastError());
+        return GRTE_OK;
+    }
+    switch (M) {
+    case 2: return launch_pred<2>(stream, g, grid, coop);
+    case 4: return launch_pred<4>(stream, g, grid, coop);
+    case 8: return launch_pred<8>(stream, g, grid, coop);
+    default: return launch_pred<16>(stream, g, grid, coop);
+    }
 }
 
 template <int M>
@@ -1434,6 +1513,7 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
         if (st == GRTE_OK) st = alloc(ctx, q, NP);
     if (st == GRTE_OK) st = alloc(ctx, &ctx->part, 2 * NP * P);
     if (st == GRTE_OK) st = alloc(ctx, &ctx->r, NP * P);
+    if (st == GRTE_OK && pred_tiled(ctx->N, ctx->P)) st = alloc(ctx, &ctx->fac, (size_t)(P + 1) * fac_doubles(TILE_MAX_M));
     for (double **q : cells)
         if (st == GRTE_OK) st = alloc(ctx, q, N);
     double **nodes[] = {&ctx->Aw, &ctx->Bc};
@@ -1452,7 +1532,7 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
     double *flagmem = nullptr;
     if (st == GRTE_OK) st = alloc(ctx, &flagmem, (size_t)MAX_P * BAR_STRIDE);
     ctx->flags = (unsigned long long *)flagmem;
-    if (st == GRTE_OK && hipMalloc((void **)&ctx->stat, NSTAT * sizeof(int)) != hipSuccess) st = GRTE_E_NOMEM;
+    if (st == GRTE_OK && hipMalloc((void **)&ctx->stat, NSTAT_ALL * sizeof(int)) != hipSuccess) st = GRTE_E_NOMEM;
     if (st == GRTE_OK) st = alloc(ctx, &ctx->obnd, 2 * P);
     if (st == GRTE_OK) st = alloc(ctx, &ctx->epart, 2 * N);   // 2 per cell block (at most N blocks)
     if (st == GRTE_OK) st = alloc(ctx, &ctx->energy, 4);
@@ -1495,11 +1575,12 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
     hipLaunchKernelGGL(fill_kernel, dim3((MAX_P * BAR_STRIDE + b - 1) / b), dim3(b), 0, nullptr, flagmem,
                        (size_t)MAX_P * BAR_STRIDE, 0.0);   // all-zero bits: generation 0
     hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(b), 0, nullptr, ctx->energy, 4, 0.0);
-    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, nullptr, ctx->stat, NSTAT, 0);
+    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, nullptr, ctx->stat, NSTAT_ALL, 0);
     // padded rows of the position-ordered arrays stay zero
     const size_t npad = (size_t)NT * ctx->M;
     hipLaunchKernelGGL(fill_kernel, dim3((npad + b - 1) / b), dim3(b), 0, nullptr, ctx->Gt, npad, 0.0);
     hipLaunchKernelGGL(fill_kernel, dim3((npad + b - 1) / b), dim3(b), 0, nullptr, ctx->res, npad, 0.0);
+    hipLaunchKernelGGL(fill_kernel, dim3((npad * P + b - 1) / b), dim3(b), 0, nullptr, ctx->r, npad * P, 0.0);
     if (hipDeviceSynchronize() != hipSuccess) { grte_destroy(ctx); return GRTE_E_HIP; }
     *out = ctx;
     return GRTE_OK;
@@ -1661,7 +1742,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
         ca.T = ctx->T; ca.Tn = ctx->T; ca.sigma0 = ctx->sigma0; ca.mu = ctx->mu; ca.omega = ctx->omega;
         ca.bL = ctx->bL; ca.bR = ctx->bR; ca.E = ctx->E; ca.O = ctx->O;
         ca.mu1 = ctx->mu1; ca.mu2 = ctx->mu2;
-        ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.M = ctx->M;
+        ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.M = ctx->M; ca.NP = NT * ctx->M;
         ca.Bd = ctx->Bd; ca.Aw = ctx->Aw; ca.Bc = ctx->Bc; ca.beta = ctx->beta;
         ca.Dl = ctx->Dl; ca.Dd = ctx->Dd; ca.Du = ctx->Du; ca.rho_n = ctx->rho_n; ca.r = ctx->r;
         ca.stat = ctx->stat;
@@ -1672,12 +1753,13 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
         pa.accel = ctx->pred_accel;
         pa.hist = ctx->hist;
         pa.Ll = ctx->Ll; pa.Lu = ctx->Lu; pa.Lam = ctx->Lam; pa.LmG = ctx->LmG; pa.Gt = ctx->Gt;
-        pa.Bd = ctx->Bd; pa.Dd = ctx->Dd; pa.mu2avg = ctx->mu2;
+        pa.Bd = ctx->Bd; pa.Dd = ctx->Dd; pa.mu1avg = ctx->mu1; pa.mu2avg = ctx->mu2; pa.fac = ctx->fac;
         pa.r = ctx->r; pa.mu = ctx->mu; pa.omega = ctx->omega; pa.rho0 = ctx->warm ? ctx->rho : ctx->rho_n;
         pa.part = ctx->part; pa.res = ctx->res; pa.estar = ctx->estar; pa.rho_out = ctx->rho_b; pa.stat = ctx->stat;
         pa.flags = ctx->flags;
         pa.gen0 = ctx->bar_gen;
         pa.direct = pred_direct(P, ctx->M);
+        pa.NP = NT * ctx->M;
         ctx->bar_gen += 2ull * (unsigned long long)ctx->pred_maxit + 4ull;   // never reused
         gp.first[g] = grid;
         grid += P;
@@ -1695,7 +1777,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
         // the alternative correction (3.14): its operators, E_J into the scratch
         // `part` (cell-major), then the explicit temperature and the projection
         AltArgs &aa = ga.a[g];
-        aa.N = N; aa.P = P; aa.m = ctx->m; aa.cpb = ctx->cpb; aa.M = ctx->M;
+        aa.N = N; aa.P = P; aa.m = ctx->m; aa.cpb = ctx->cpb; aa.NP = NT * ctx->M;
         aa.a = ctx->a; aa.c = ctx->c; aa.cv = ctx->cv; aa.eps = eps; aa.dt = dt; aa.dx = dx;
         aa.Tn = ctx->T; aa.sigma0 = ctx->sigma0; aa.mu = ctx->mu; aa.omega = ctx->omega;
         aa.bL = ctx->bL; aa.bR = ctx->bR; aa.En = ctx->E; aa.On = ctx->O; aa.Es = ctx->estar;
@@ -1737,13 +1819,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
     hipLaunchKernelGGL(coef_kernel, dim3(ncb_max, n), dim3(256), 0, stream, gc);
     HIPCHK(hipGetLastError());
     if (sample && (st = prof_begin(c0, GRTE_TIMING_PREDICT, &ev_pred)) != GRTE_OK) return st;
-    switch (M) {
-    case 2: st = launch_pred<2>(stream, gp, grid, c0->coop_launch != 0); break;
-    case 4: st = launch_pred<4>(stream, gp, grid, c0->coop_launch != 0); break;
-    case 8: st = launch_pred<8>(stream, gp, grid, c0->coop_launch != 0); break;
-    default: st = launch_pred<16>(stream, gp, grid, c0->coop_launch != 0); break;
-    }
-    if (st != GRTE_OK) return st;
+    if ((st = launch_prediction(stream, gp, M, grid, c0->coop_launch != 0)) != GRTE_OK) return st;
     if ((st = prof_end(c0, ev_pred)) != GRTE_OK) return st;
     bool any_guess = false;
     for (int g = 0; g < n; ++g) any_guess = any_guess || gn.a[g].gw != nullptr;
@@ -1858,7 +1934,7 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
     hipStream_t stream = ctx->stream;
     double *Tk = ctx->T2, *Tk1 = ctx->rstar;   // Picard iterates (scratch of the normal step)
     HIPCHK(hipMemcpyAsync(Tk, ctx->T, N * sizeof(double), hipMemcpyDeviceToDevice, stream));
-    unsigned long long *dmax = ctx->flags + (size_t)(MAX_P - 1) * BAR_STRIDE + 8;   // spare words of the last flag line
+    unsigned long long *dmax = (unsigned long long *)(ctx->stat + NSTAT);   // cleared by the coefficients' kernel
     Group<CoefArgs> gc{};
     gc.n = 1;
     CoefArgs &ca = gc.a[0];
@@ -1867,7 +1943,7 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
     ca.Tn = ctx->T; ca.sigma0 = ctx->sigma0; ca.mu = ctx->mu; ca.omega = ctx->omega;
     ca.bL = ctx->bL; ca.bR = ctx->bR; ca.E = ctx->E; ca.O = ctx->O;
     ca.mu1 = ctx->mu1; ca.mu2 = ctx->mu2;
-    ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.M = M;
+    ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.M = M; ca.NP = NT * M;
     ca.Bd = ctx->Bd; ca.Aw = ctx->Aw; ca.Bc = ctx->Bc; ca.beta = ctx->beta;
     ca.Dl = ctx->Dl; ca.Dd = ctx->Dd; ca.Du = ctx->Du; ca.rho_n = ctx->rho_n; ca.r = ctx->r;
     ca.stat = ctx->stat;
@@ -1880,7 +1956,7 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
         pa.accel = ctx->pred_accel;
         pa.hist = ctx->hist;
     pa.Ll = ctx->Ll; pa.Lu = ctx->Lu; pa.Lam = ctx->Lam; pa.LmG = ctx->LmG; pa.Gt = ctx->Gt;
-    pa.Bd = ctx->Bd; pa.Dd = ctx->Dd; pa.mu2avg = ctx->mu2;
+    pa.Bd = ctx->Bd; pa.Dd = ctx->Dd; pa.mu1avg = ctx->mu1; pa.mu2avg = ctx->mu2; pa.fac = ctx->fac;
     pa.r = ctx->r; pa.mu = ctx->mu; pa.omega = ctx->omega; pa.rho0 = ctx->rho_n;
     pa.part = ctx->part; pa.res = ctx->res; pa.estar = ctx->E2; pa.rho_out = ctx->rho; pa.stat = ctx->stat;
     pa.flags = ctx->flags;
@@ -1894,29 +1970,21 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
         HIPCHK(hipGetLastError());
         pa.gen0 = ctx->bar_gen;
         pa.direct = pred_direct(P, ctx->M);
+        pa.NP = NT * ctx->M;
         ctx->bar_gen += 2ull * (unsigned long long)ctx->pred_maxit + 4ull;
-        switch (M) {
-        case 2: st = launch_pred<2>(stream, gp, P, ctx->coop_launch != 0); break;
-        case 4: st = launch_pred<4>(stream, gp, P, ctx->coop_launch != 0); break;
-        case 8: st = launch_pred<8>(stream, gp, P, ctx->coop_launch != 0); break;
-        default: st = launch_pred<16>(stream, gp, P, ctx->coop_launch != 0); break;
-        }
-        if (st != GRTE_OK) return st;
-        hipLaunchKernelGGL(clear_u64, dim3(1), dim3(64), 0, stream, dmax, 2);
+        if ((st = launch_prediction(stream, gp, M, P, ctx->coop_launch != 0)) != GRTE_OK) return st;
         hipLaunchKernelGGL(picard_update_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, N, ac,
                            ctx->T, ctx->beta, ctx->rho, Tk, Tk1, ctx->ustar, dmax);
         HIPCHK(hipGetLastError());
-        unsigned long long h[2];
-        int hs[8];
-        HIPCHK(hipMemcpyAsync(h, dmax, sizeof(h), hipMemcpyDeviceToHost, stream));
+        int hs[NSTAT_ALL];
         HIPCHK(hipMemcpyAsync(hs, ctx->stat, sizeof(hs), hipMemcpyDeviceToHost, stream));
         HIPCHK(hipStreamSynchronize(stream));
         worst_pred = std::max(worst_pred, hs[0]);
         if (!hs[1]) pred_fail = 1;
         if (hs[6]) { sync_err = 1; break; }
         double d, tmax;
-        std::memcpy(&d, &h[0], sizeof(d));
-        std::memcpy(&tmax, &h[1], sizeof(tmax));
+        std::memcpy(&d, &hs[NSTAT], sizeof(d));
+        std::memcpy(&tmax, &hs[NSTAT + 2], sizeof(tmax));
         std::swap(Tk, Tk1);                           // Tk holds T^(k+1)
         if (d <= tol * tmax) { converged = 1; break; }
     }
