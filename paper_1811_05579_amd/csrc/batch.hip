@@ -588,40 +588,60 @@ __device__ __forceinline__ void corr_solve(const BatchArgs &A, int i, double *sm
     tile_sync<NW>();
 }
 
-// binary64 state <-> binary32 storage of every instance (one block per
-// instance): E32 = E - a c T^4, O32 = O (to32), or back; the binary32 arrays
-// are pair-major (see BState)
-__global__ void __launch_bounds__(256) batch_convert(const BInst *inst, const double *T, double *E, double *O,
-                                                    float *E32, float *O32, int to32)
+// binary64 state <-> binary32 storage (a block per cell block, cblk): E32 = E - a c T^4,
+// O32 = O (to32), or back.  The binary64 arrays are cell-major, the binary32 ones
+// pair-major (see BState), so a block turns its cells over in LDS and both sides move in
+// runs: CB cells of all pairs, CB words of a pair.  Bound by the traffic; 4096 slabs on an
+// MI355X 530 us (950 with a thread per word of one side and strided access on the other).
+constexpr int CB = 128;   // cells per block of the per-cell kernels (a multiple of 64, at most 512)
+
+__global__ void __launch_bounds__(256) batch_convert(const BInst *inst, const int2 *cblk, const double *T, double *E,
+                                                     double *O, float *E32, float *O32, int to32)
 {
-    const BInst I = inst[blockIdx.x];
-    const int N = I.N, P = I.P;
-    const int ne = N * P, no = (N + 1) * P;     // per instance: well below 2^31
+    __shared__ float s[BMAX_P * (CB + 2)];
+    __shared__ double base[CB + 1];
+    const int2 cb = cblk[blockIdx.x];
+    const BInst I = inst[cb.x];
+    const int N = I.N, P = I.P, j0 = cb.y, t = threadIdx.x;
     const double ac = I.a * I.c;
-    // t runs over the binary64 (cell-major) index j P + p; the binary32 state is
-    // pair-major, p N + j (cells) and p (N + 1) + i (nodes)
-    for (int t = threadIdx.x; t < ne; t += blockDim.x) {
-        const int j = t / P, p = t - j * P;
-        const double tj = T[I.oT + j];
-        const double base = ac * (tj * tj) * (tj * tj);
-        const size_t q = I.oE + (size_t)p * N + j;
-        if (to32) E32[q] = (float)(E[I.oE + t] - base);
-        else E[I.oE + t] = base + (double)E32[q];
-    }
-    for (int t = threadIdx.x; t < no; t += blockDim.x) {
-        const int i = t / P, p = t - i * P;
-        const size_t q = I.oO + (size_t)p * (N + 1) + i;
-        if (to32) O32[q] = (float)O[I.oO + t];
-        else O[I.oO + t] = (double)O32[q];
+    // cells first, then nodes (the last block also takes node N)
+    for (int nodes = 0; nodes < 2; ++nodes) {
+        const int total = N + nodes;
+        const int n = j0 + CB >= N ? total - j0 : CB, str = CB + 2;
+        double *wide = (nodes ? O + I.oO : E + I.oE) + (size_t)j0 * P;
+        float *narrow = (nodes ? O32 + I.oO : E32 + I.oE) + j0;
+        if (t < n) {
+            const double tj = nodes ? 0.0 : T[I.oT + j0 + t];
+            base[t] = nodes ? 0.0 : ac * (tj * tj) * (tj * tj);
+        }
+        __syncthreads();
+        if (to32) {
+            for (int q = t; q < n * P; q += 256) {
+                const int j = q / P, p = q - j * P;
+                s[p * str + j] = (float)(wide[q] - base[j]);
+            }
+        } else {
+            for (int p = t >> 6; p < P; p += 4)
+                for (int j = t & 63; j < n; j += 64) s[p * str + j] = narrow[(size_t)p * total + j];
+        }
+        __syncthreads();
+        if (to32) {
+            for (int p = t >> 6; p < P; p += 4)
+                for (int j = t & 63; j < n; j += 64) narrow[(size_t)p * total + j] = s[p * str + j];
+        } else {
+            for (int q = t; q < n * P; q += 256) {
+                const int j = q / P, p = q - j * P;
+                wide[q] = base[j] + (double)s[p * str + j];
+            }
+        }
+        __syncthreads();
     }
 }
-
 
 // The step's kernels, in stream order (one graph per state-buffer parity):
 //   batch_reset, cells_kernel<CP_PRED>, solve_kernel<0>, cells_kernel<CP_NEWTON>,
 //   cells_kernel<CP_CORR>, solve_kernel<1>, cells_kernel<CP_PROJECT>, batch_energy.
 enum { CP_PRED = 0, CP_NEWTON = 1, CP_CORR = 2, CP_PROJECT = 3 };
-constexpr int CB = 128;   // cells per block of the per-cell kernels (a multiple of 64, at most 512)
 
 template <int PH, bool F32>
 __global__ void __launch_bounds__(CB) cells_kernel(BatchArgs A)
@@ -1220,8 +1240,8 @@ grte_status grte_batch_set_inflow(grte_batch *b, const double *b_left, const dou
 namespace {
 grte_status convert_state(grte_batch *b, int to32)
 {
-    hipLaunchKernelGGL(batch_convert, dim3((unsigned)b->n), dim3(256), 0, b->stream, b->d_inst, b->T[b->cur],
-                       b->E[b->cur], b->O[b->cur], b->E32[b->cur], b->O32[b->cur], to32);
+    hipLaunchKernelGGL(batch_convert, dim3((unsigned)b->n_cblk), dim3(256), 0, b->stream, b->d_inst, b->d_cblk,
+                       b->T[b->cur], b->E[b->cur], b->O[b->cur], b->E32[b->cur], b->O32[b->cur], to32);
     BCHK(hipGetLastError());
     return GRTE_OK;
 }
