@@ -629,7 +629,8 @@ grte_status grte2d_set_stream(grte2d_ctx *ctx, void *hip_stream);
 grte_status grte2d_set_solver(grte2d_ctx *ctx, double tol, int maxit);
 
 /* Launch shape of the Krylov kernels: each thread takes `items_per_thread`
- * (cell, pair) items (1..64, default 4; at most 16384 blocks of 256 threads),
+ * (cell, pair) items (1..64, by default 8, fewer on grids of less than 2^21
+ * items; at most 16384 blocks of 256 threads),
  * and the per-block partial sums of the inner products are reduced in two
  * levels when there are more than `first_level` of them (1..16384, default
  * 16384: blocks of that many partials, then one block), else by one block of

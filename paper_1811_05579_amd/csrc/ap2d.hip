@@ -53,8 +53,8 @@ constexpr int MAXB = 2048;     // blocks of the grid-stride kernels outside the 
 // FIN_T threads, or in two levels (RED_B partials per block of the first
 // level, then that block) when there are more than RED_B of them (both figures
 // can be set per context; by default every count takes the one level)
-constexpr int KRYB = 16384, KRY_ITEMS = 4, RED_B = KRYB;
-constexpr int OPC_N = 8;       // doubles per cell of the operator's packed coefficients (opc2d_kernel)
+constexpr int KRYB = 16384, KRY_ITEMS = 8, RED_B = KRYB;
+constexpr int OPC_N = 6;       // doubles per cell of the operator's packed coefficients (opc2d_kernel)
 constexpr int CHUNK = 8;       // most BiCGStab iterations enqueued between convergence checks
 constexpr int KRY_RESTARTS = 12;     // restarts from the true residual per solve
 // a pass of binary32-stored iterations ends once the recursion's residual is
@@ -487,9 +487,10 @@ __global__ void __launch_bounds__(B2) residual2d_kernel(VecArgs A)
 // The operator products of the iteration by columns: the grid is cut into tiles
 // of (B2 / P) cells across by `rows` cells down (op_rows); thread (cell c, pair p) of a
 // tile walks down its column keeping the 3 x 3 neighbourhood of its pair in
-// registers, so that a row costs three new loads of x instead of nine and the
-// shared face coefficient of two rows one, and it loads the next row's values
-// and coefficients before it computes the current row (their latency overlaps
+// registers, so that a row costs three new loads of x instead of nine; the value at a
+// row's top face is the next row's at its bottom face, and the difference across of a
+// row serves both faces next to it.  The next row's values and the next two rows'
+// coefficients are loaded before the current row is computed (their latency overlaps
 // the arithmetic).  Per (cell, pair): y = (Lambda - g W1) x_p + g (W1 x_p -
 // sum_q omega_q x_q) + k div O(x) with O(x) the part of faces() linear in x (the
 // coupling referred to the cell's first pair, exact for a nearly isotropic x).
@@ -497,6 +498,10 @@ __global__ void __launch_bounds__(B2) residual2d_kernel(VecArgs A)
 // part[k * KRYB + blockIdx.x].  The products are stored as V.
 // MODE 1: v = A ph, partial (h, v) and, with the isotropic correction, the moment
 // of v;  MODE 2: t = A sh, partial (t, s), (t, t)
+// Bound: about 110 vector instructions per item and two to three vectors' traffic.
+// 1024 x 1024 cells of 16 pairs on an MI355X: 74 us (MODE 1) and 78 (MODE 2); with every
+// face formed in its row and the pairs' number read at run time 84 and 86; two pairs per
+// thread, three or four rows of x ahead, or tiles handed to the dies in runs gave nothing.
 constexpr int OP_ROWS = 16, OP_ROWS_MIN = 2, OP_TILES = 1024;
 
 __device__ __forceinline__ void block_sums_at(double *vals, int k, double *part, int bid)
@@ -515,19 +520,21 @@ __device__ __forceinline__ void block_sums_at(double *vals, int k, double *part,
     }
 }
 
-template <int MODE, class V>
-__global__ void __launch_bounds__(B2, 5) apply2d_col_kernel(VecArgs A, int ncol, int ntile, int rows)
+// LP: log2 of the pairs (the lanes of a cell), -1: read at run time
+template <int MODE, class V, int LP>
+__global__ void __launch_bounds__(B2, 4) apply2d_col_kernel(VecArgs A, int ncol, int ntile, int rows)
 {
     if (A.fl[F_STATE] != 0) return;
     const Sys &S = A.S;
-    const int P = S.P, lgP = S.lgP, nx = S.nx, ny = S.ny;
+    const int lgP = LP >= 0 ? LP : S.lgP, P = 1 << lgP, nx = S.nx, ny = S.ny;
     const int c = threadIdx.x >> lgP, p = threadIdx.x & (P - 1);
     const int cw = B2 >> lgP, rs = nx * P;
     const V *xv = (const V *)(MODE == 1 ? A.ph : A.sh);
     const V *sa = (const V *)A.s;
     V *out = (V *)(MODE == 1 ? A.v : A.t);
     const double mu = S.mu[p], eta = S.eta[p], w = S.om[p];
-    const double sx = mu > 0.0 ? 1.0 : -1.0, sy = eta > 0.0 ? 1.0 : -1.0;
+    const double mux = mu * S.idx, ety = eta * S.idy, kf = S.k2 * S.fe;
+    const double kx = mu > 0.0 ? -kf : kf, ky = eta > 0.0 ? -kf : kf;   // an edge face: kx (ky) x - the opposite face
     double acc[2] = {0.0, 0.0};
     for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
         const int ty = tile / ncol, tx = tile - ty * ncol;
@@ -535,84 +542,92 @@ __global__ void __launch_bounds__(B2, 5) apply2d_col_kernel(VecArgs A, int ncol,
         if (ix >= nx) continue;                 // whole cells: a cell's P lanes agree
         const int iy0 = ty * rows, iy1 = min(iy0 + rows, ny);
         const int o0 = max(ix - 1, 0) * P + p, o1 = ix * P + p, o2 = min(ix + 1, nx - 1) * P + p;
-        auto ldrow = [&](int row, double(&v)[3]) {
-            const V *q = xv + row * rs;
+        // centred differences across, one-sided next to a wall
+        const double hx = 0.5 * mu * (ix == 0 || ix == nx - 1 ? S.idx : 0.5 * S.idx);
+        // rings of three rows, the row number modulo 3 (the loop is unrolled by 3, so every
+        // index is a constant): x in use; the coefficients and s of the row, the next two
+        // on their way.  (Row numbers clamped in range: what lies beyond the tile is unused.)
+        double X[3][3];
+        V nxt[3], sr[3];
+        double2 cf[3][3];
+        auto ldrow = [&](int row, V(&v)[3]) {
+            const V *q = xv + min(max(row, 0), ny - 1) * rs;
             v[0] = q[o0];
             v[1] = q[o1];
             v[2] = q[o2];
         };
-        Nb X;
-        ldrow(max(iy0 - 1, 0), X.v[0]);
-        ldrow(iy0, X.v[1]);
-        ldrow(min(iy0 + 1, ny - 1), X.v[2]);
-        int j = iy0 * nx + ix;
-        auto ldc = [&](int jj, double2(&c)[4]) {
-            const double2 *q = (const double2 *)(S.opc + (size_t)OPC_N * jj);
+        auto put = [&](double(&x)[3], const V(&v)[3]) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) c[k] = q[k];
+            for (int k = 0; k < 3; ++k) x[k] = (double)v[k];
         };
-        double2 cf[4];
-        ldc(j, cf);
-        double sv = MODE == 2 ? (double)sa[j * P + p] : 0.0;
-        for (int iy = iy0; iy < iy1; ++iy) {
-            // the next row's loads (row indices clamped in range; unused after
-            // the tile's last row)
-            const int yn = min(iy + 1, ny - 1), jn = yn * nx + ix;
-            double xn[3];
-            ldrow(min(iy + 2, ny - 1), xn);
-            double2 cfn[4];
-            ldc(jn, cfn);
-            const double svn = MODE == 2 ? (double)sa[jn * P + p] : 0.0;
-            // row iy: faces<false, true> with the coefficients in registers
-            const double dm = cf[0].x, cgv = cf[0].y, kc = cf[1].x;
-            const Grad g = face_grad(X, mu, eta, S, iy, ix);
-            Grad O;
-            O.l = -cf[2].x * g.l;
-            O.r = -cf[2].y * g.r;
-            O.b = -cf[3].x * g.b;
-            O.t = -cf[3].y * g.t;
-            const double xp = X.v[1][1];
-            const double k2 = S.k2;
-            auto edge = [&](double sg) {
-                const double d = -S.fe * xp;
-                return sg * k2 * d;
-            };
-            if (ix == 0) O.l = edge(sx) - O.r;
-            if (ix == nx - 1) O.r = edge(-sx) - O.l;
-            if (iy == 0) O.b = edge(sy) - O.t;
-            if (iy == ny - 1) O.t = edge(-sy) - O.b;
-            const double div = mu * (O.r - O.l) * S.idx + eta * (O.t - O.b) * S.idy;
-            double y;
-            if (S.corr) {
-                y = dm * xp + kc * div;             // no angular coupling (g = 0)
-            } else {
-                const double xr = group_lane0(xp, P);
-                const double cpl = S.W1 * (xp - xr) - group_sum(w * (xp - xr), P);
-                y = dm * xp + cgv * cpl + kc * div;
-            }
-            const int t = j * P + p;
-            const double yf = (double)(V)y;         // the stored product
-            out[t] = (V)y;
-            if (MODE == 1) {
-                if (A.mv) {
-                    const double m = group_sum(w * yf, P);
-                    if (p == 0) A.mv[j] = m;
+        auto ldc = [&](int row, double2(&k)[3], V &sv) {
+            const int j = min(row, ny - 1) * nx + ix;
+            const double2 *q = (const double2 *)(S.opc + (size_t)OPC_N * j);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) k[i] = q[i];
+            if (MODE == 2) sv = sa[j * P + p];
+        };
+        {
+            V a0[3], a1[3];
+            ldrow(iy0 - 1, a0);
+            ldrow(iy0, a1);
+            ldrow(iy0 + 1, nxt);
+            ldc(iy0, cf[0], sr[0]);
+            ldc(iy0 + 1, cf[1], sr[1]);
+            put(X[0], a0);
+            put(X[1], a1);
+        }
+        // the row's bottom face is the last row's top face (the wall's is set below), and
+        // the difference across of a row serves the faces above and below it
+        double E1 = X[1][2] - X[1][0];
+        double Ob = -S.gy[iy0 * nx + ix] * (ety * (X[1][1] - X[0][1]) + hx * ((X[0][2] - X[0][0]) + E1));
+        for (int iyb = iy0; iyb < iy1; iyb += 3) {
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                const int iy = iyb + e;
+                if (iy >= iy1) break;
+                const double(&Xd)[3] = X[e], (&Xc)[3] = X[(e + 1) % 3];
+                double(&Xu)[3] = X[(e + 2) % 3];
+                put(Xu, nxt);
+                ldrow(iy + 2, nxt);
+                ldc(iy + 2, cf[(e + 2) % 3], sr[(e + 2) % 3]);
+                const double2(&k)[3] = cf[e];
+                const double hy = 0.5 * eta * (iy == 0 || iy == ny - 1 ? S.idy : 0.5 * S.idy);
+                const double D0 = Xu[0] - Xd[0], D1 = Xu[1] - Xd[1], D2 = Xu[2] - Xd[2];
+                const double E2 = Xu[2] - Xu[0], xp = Xc[1];
+                // O = -gamma Omega . grad x at the faces
+                double Ol = -k[1].y * (mux * (xp - Xc[0]) + hy * (D0 + D1));
+                double Or = -k[2].x * (mux * (Xc[2] - xp) + hy * (D1 + D2));
+                double Ot = -k[2].y * (ety * (Xu[1] - xp) + hx * (E1 + E2));
+                if (ix == 0) Ol = kx * xp - Or;
+                if (ix == nx - 1) Or = -kx * xp - Ol;
+                if (iy == 0) Ob = ky * xp - Ot;
+                if (iy == ny - 1) Ot = -ky * xp - Ob;
+                const double div = mux * (Or - Ol) + ety * (Ot - Ob);
+                Ob = Ot;
+                E1 = E2;
+                double y;
+                if (S.corr) {
+                    y = k[0].x * xp + k[1].x * div;     // no angular coupling (g = 0)
+                } else {
+                    const double dr = xp - group_lane0(xp, P);
+                    const double cpl = S.W1 * dr - group_sum(w * dr, P);
+                    y = k[0].x * xp + k[0].y * cpl + k[1].x * div;
                 }
-                acc[0] += shadow(t) * yf;
-            } else {
-                acc[0] += yf * sv;
-                acc[1] += yf * yf;
+                const int j = iy * nx + ix, t = j * P + p;
+                const double yf = (double)(V)y;         // the stored product
+                out[t] = (V)y;
+                if (MODE == 1) {
+                    if (A.mv) {
+                        const double m = group_sum(w * yf, P);
+                        if (p == 0) A.mv[j] = m;
+                    }
+                    acc[0] += shadow(t) * yf;
+                } else {
+                    acc[0] += yf * (double)sr[e];
+                    acc[1] += yf * yf;
+                }
             }
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                X.v[0][k] = X.v[1][k];
-                X.v[1][k] = X.v[2][k];
-                X.v[2][k] = xn[k];
-            }
-            j = jn;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) cf[k] = cfn[k];
-            sv = svn;
         }
     }
     block_sums_at(acc, MODE == 1 ? 1 : 2, A.part, blockIdx.x);
@@ -671,9 +686,8 @@ __global__ void set_int_kernel(int *a, int v)
 }
 
 // The coefficients the operator products read per cell and row, packed once per
-// solve so that a row takes four 16-byte loads instead of six 8-byte ones:
-// {Lambda - g W1, g, k, 0, gamma of the left, right, bottom and top faces}
-
+// solve so that a row takes three 16-byte loads instead of five 8-byte ones:
+// {Lambda - g W1, g, k, gamma of the left, right and top faces}
 __global__ void __launch_bounds__(B2) opc2d_kernel(Sys S, double *opc)
 {
     const int n = S.nx * S.ny;
@@ -683,9 +697,8 @@ __global__ void __launch_bounds__(B2) opc2d_kernel(Sys S, double *opc)
         const int fl = j + iy;
         double2 *q = (double2 *)(opc + (size_t)OPC_N * j);
         q[0] = make_double2(S.dmg[j], S.cg[j]);
-        q[1] = make_double2(S.kco[j], 0.0);
-        q[2] = make_double2(S.gx[fl], S.gx[fl + 1]);
-        q[3] = make_double2(S.gy[j], S.gy[j + S.nx]);
+        q[1] = make_double2(S.kco[j], S.gx[fl]);
+        q[2] = make_double2(S.gx[fl + 1], S.gy[j + S.nx]);
     }
 }
 
@@ -997,18 +1010,22 @@ __global__ void __launch_bounds__(B2) iso_step_kernel(IsoArgs A)
     }
 }
 
-// the cells' Jacobi-scaled rows, once per solve: w_l, w_r, w_b, w_t, 1 / diag, n of each
-__global__ void __launch_bounds__(B2) iso_rows_kernel(IsoArgs A, double *rows)
+// the cells' Jacobi-scaled rows, once per solve (d: 1 / diag)
+struct MgRows {
+    int nx, ny;
+    double *d, *wl, *wr, *wb, *wt;
+};
+__global__ void __launch_bounds__(B2) iso_rows_kernel(IsoArgs A, MgRows L)
 {
     const int n = A.S.nx * A.S.ny;
     for (int j = blockIdx.x * B2 + threadIdx.x; j < n; j += gridDim.x * B2) {
         int iy, ix;
         const IsoRow R = iso_row_at(A, j, iy, ix);
-        rows[j] = R.wl;
-        rows[n + j] = R.wr;
-        rows[2 * n + j] = R.wb;
-        rows[3 * n + j] = R.wt;
-        rows[4 * n + j] = R.rdg;
+        L.wl[j] = R.wl;
+        L.wr[j] = R.wr;
+        L.wb[j] = R.wb;
+        L.wt[j] = R.wt;
+        L.d[j] = R.rdg;
     }
 }
 
@@ -1037,7 +1054,8 @@ struct IsoFused {
     int nsteps;                 // stencil steps of this launch
     int hx, hy;                 // halo across, down
     int ymode;                  // input: 0 A.y, 1 the direction's moment (yP, kept in ynew by the owner), 2 that of s
-    const double *rows, *mr, *mv, *yP, *sc;
+    MgRows L;                   // the rows (iso_rows_kernel)
+    const double *mr, *mv, *yP, *sc;
     double *ynew;
     const double *din;          // the direction to continue from (first = 0)
     double *dout;               // the direction after the launch (null: not kept)
@@ -1049,7 +1067,7 @@ __global__ void __launch_bounds__(64 * ISO_W) iso_tile_kernel(IsoFused F)
 {
     const IsoArgs &A = F.A;
     if (A.fl[F_STATE] != 0) return;
-    const int nx = A.S.nx, ny = A.S.ny, n = nx * ny;
+    const int nx = A.S.nx, ny = A.S.ny;
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ry0 = w * RPW;
     const int tile = die_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
@@ -1065,11 +1083,11 @@ __global__ void __launch_bounds__(64 * ISO_W) iso_tile_kernel(IsoFused F)
         yr[r] = wl[r] = wr[r] = wb[r] = wt[r] = d[r] = x[r] = 0.0;
         if (ix < 0 || ix >= nx || iy < 0 || iy >= ny) continue;
         const int j = iy * nx + ix;
-        wl[r] = F.rows[j];
-        wr[r] = F.rows[n + j];
-        wb[r] = F.rows[2 * n + j];
-        wt[r] = F.rows[3 * n + j];
-        const double rdg = F.rows[4 * n + j];
+        wl[r] = F.L.wl[j];
+        wr[r] = F.L.wr[j];
+        wb[r] = F.L.wb[j];
+        wt[r] = F.L.wt[j];
+        const double rdg = F.L.d[j];
         double y;
         if (F.ymode == 0) {
             y = A.y[j];
@@ -1088,12 +1106,16 @@ __global__ void __launch_bounds__(64 * ISO_W) iso_tile_kernel(IsoFused F)
             x[r] = A.xin[j];
         }
     }
+    const bool live = iy0 < ny && iy0 + RPW > 0;       // of the whole wavefront: rows of the grid among its own
+    // step s's coefficients in lane s (a scalar load in every step would wait for memory)
+    const double c1s = F.c1[min(l, ISO_STEPS - 1)], c2s = F.c2[min(l, ISO_STEPS - 1)];
     for (int s = 0; s < F.nsteps; ++s) {
-        const double c1 = F.c1[s], c2 = F.c2[s];
+        const double c1 = lane_at(c1s, s), c2 = lane_at(c2s, s);
         const int b = s & 1;
         sLo[b][w][l] = x[0];
         sHi[b][w][l] = x[RPW - 1];
         __syncthreads();
+        if (!live) continue;
         double lo = w > 0 ? sHi[b][w > 0 ? w - 1 : 0][l] : 0.0;
         const double hi = w < ISO_W - 1 ? sLo[b][w < ISO_W - 1 ? w + 1 : 0][l] : 0.0;
 #pragma unroll
@@ -1123,11 +1145,6 @@ __global__ void __launch_bounds__(64 * ISO_W) iso_tile_kernel(IsoFused F)
 // Each level stores its 5-point rows: diagonal d and the couplings wl, wr, wb, wt
 // to the left, right, bottom and top neighbours (zero at a wall).
 // ---------------------------------------------------------------------------
-struct MgRows {
-    int nx, ny;
-    double *d, *wl, *wr, *wb, *wt;
-};
-
 constexpr double MG_COUPLE = 0.5;   // coarse coupling = this x the summed fine couplings across a side
 
 __global__ void __launch_bounds__(B2) mg_fine_kernel(IsoArgs A, MgRows L)
@@ -1818,7 +1835,7 @@ struct grte2d_ctx {
     double Mxx = 0, Myy = 0, Sx = 0, Sy = 0;
     double *yP = nullptr, *yS = nullptr, *dP = nullptr, *dS = nullptr, *itmp = nullptr, *idir = nullptr;
     double *pgc = nullptr;               // per-cell scalar of the block inverse
-    int kry_items = KRY_ITEMS;           // launch shape of the Krylov kernels (grte2d_set_launch_shape)
+    int kry_items = 0;                   // items per thread of the Krylov kernels (grte2d_set_launch_shape; 0: kry_items_auto)
     int red_b = RED_B;
     // energy balance: edge outflow per edge cell, rho^{n+1}, block partials,
     // the blocks-done counter and the four results
@@ -1829,7 +1846,6 @@ struct grte2d_ctx {
     float *idg32 = nullptr;              // the same in binary32
     double *opc = nullptr;               // the operator's packed per-cell coefficients (OPC_N per cell)
     double *mr = nullptr, *mv = nullptr;  // angular moments of r and v (isotropic correction)
-    double *irows = nullptr, *yP2 = nullptr;   // the isotropic operator's rows; second buffer of yP
     double *idir2 = nullptr;             // second Chebyshev direction buffer of the tiled launches
     // sampled timing of the operator kernel (first iteration of every chunk)
     int profiling = 0;
@@ -1866,8 +1882,21 @@ int nblocks(size_t n)
     return (int)std::max<size_t>(1, std::min<size_t>(b, MAXB));
 }
 
+// items per thread of the Krylov kernels unless the caller sets them: the most that leaves
+// KRY_FILL blocks (47 x 33 cells x 4 pairs: the residual 5.3 us with one item per
+// thread, 10.6 with four; 1024 x 1024 x 16: the reduction of eight items' 8192 partial
+// sums 4.7 us, of four items' 16384 7.5)
+constexpr int KRY_FILL = 1024;
+int kry_items_auto(size_t n)
+{
+    int items = KRY_ITEMS;
+    while (items > 1 && n < (size_t)B2 * items * KRY_FILL) items /= 2;
+    return items;
+}
+
 int kblocks(size_t n, int items)
 {
+    if (items == 0) items = kry_items_auto(n);
     const size_t b = (n + (size_t)B2 * items - 1) / ((size_t)B2 * items);
     return (int)std::max<size_t>(1, std::min<size_t>(b, KRYB));
 }
@@ -2051,7 +2080,8 @@ void launch_iso_tile(int rpw, dim3 grid, hipStream_t st, const IsoFused &F)
 
 // K Chebyshev steps for D z = y, y the moment of the direction (which 0) or of s (1); the
 // result lands in out (tmp is scratch).  The tiled launches form y themselves (yP in the
-// other of its two buffers), the per-step ones read it
+// other of its two buffers) and keep their rows and that buffer in the multigrid's first
+// level, which only that variant uses; the per-step launches read y
 void iso_cheb(grte2d_ctx *c, const Sys &S, int which, double *out, hipStream_t st)
 {
     const int K = c->iso_k;
@@ -2082,14 +2112,14 @@ void iso_cheb(grte2d_ctx *c, const Sys &S, int which, double *out, hipStream_t s
             F.nsteps = std::min(sh.steps, K - k);
             F.hx = sh.hx;
             F.hy = sh.hy;
-            F.rows = c->irows;
+            F.L = c->mg[0].R;
             F.mr = c->mr;
             F.mv = c->mv;
             F.yP = c->yP;
-            F.ynew = c->yP2;
+            F.ynew = c->mg[0].z1;
             F.sc = c->sc;
             F.ymode = which == 1 ? 2 : l == 0 ? 1 : 0;
-            if (which == 0 && l > 0) F.A.y = c->yP2;
+            if (which == 0 && l > 0) F.A.y = c->mg[0].z1;
             F.A.xin = l == 0 ? nullptr : (((nl - l) % 2 == 0) ? out : c->itmp);
             F.A.xout = ((nl - 1 - l) % 2 == 0) ? out : c->itmp;
             F.din = l == 0 ? nullptr : ((l % 2 == 1) ? c->idir : c->idir2);
@@ -2102,7 +2132,7 @@ void iso_cheb(grte2d_ctx *c, const Sys &S, int which, double *out, hipStream_t s
             }
             launch_iso_tile(sh.rpw, sh.grid, st, F);
         }
-        if (which == 0) std::swap(c->yP, c->yP2);
+        if (which == 0) std::swap(c->yP, c->mg[0].z1);
         return;
     }
     auto buf = [&](int k) { return ((K - k) % 2 == 0) ? out : c->itmp; };   // iterate k lands in buf(k)
@@ -2141,6 +2171,20 @@ void iso_solve(grte2d_ctx *c, const Sys &S, const VecArgs &A, int which, hipStre
     L0.z0 = out;
     mg_vcycle(c, 0, which == 0 ? c->yP : c->yS, st);
     L0.z0 = keep;
+}
+
+// The operator product with the number of pairs known at compile time for binary32
+// vectors (its lane sums are a dozen scalar branches per row otherwise)
+template <int MODE, class V, int LP = 6>
+void launch_apply(int nb, hipStream_t st, const VecArgs &A, int ncol, int ntile, int rows)
+{
+    if constexpr (sizeof(V) == 4 && LP >= 0) {
+        if (A.S.lgP != LP) {
+            launch_apply<MODE, V, LP - 1>(nb, st, A, ncol, ntile, rows);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((apply2d_col_kernel<MODE, V, (sizeof(V) == 4 ? LP : -1)>), dim3(nb), dim3(B2), 0, st, A, ncol, ntile, rows);
 }
 
 // the square norm of the right-hand side of A.S, for the solve that follows
@@ -2201,7 +2245,7 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
     const bool iso = c->iso_kind != 0 && !S.corr;
     if (iso && c->iso_kind == 2) mg_setup(c, S, c->stream);
     if (iso && c->iso_kind == 1)
-        hipLaunchKernelGGL(iso_rows_kernel, dim3(nblocks(c->N)), dim3(B2), 0, c->stream, iso_args(c, S), c->irows);
+        hipLaunchKernelGGL(iso_rows_kernel, dim3(nblocks(c->N)), dim3(B2), 0, c->stream, iso_args(c, S), c->mg[0].R);
     A.dP = iso ? c->dP : nullptr;
     A.dS = iso ? c->dS : nullptr;
     A.yP = iso ? c->yP : nullptr;
@@ -2269,12 +2313,12 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
                 if (iso) iso_solve(c, S, A, 0, st);
                 hipLaunchKernelGGL(pupd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
                 if (timed && k == 0) (void)hipEventRecord(c->ev0, st);
-                hipLaunchKernelGGL((apply2d_col_kernel<1, V>), dim3(nbo), dim3(B2), 0, st, A, ncol, ntile, rows);
+                launch_apply<1, V>(nbo, st, A, ncol, ntile, rows);
                 if (timed && k == 0) (void)hipEventRecord(c->ev1, st);
                 fin(1, 1, nbo);
                 if (iso) iso_solve(c, S, A, 1, st);
                 hipLaunchKernelGGL(supd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-                hipLaunchKernelGGL((apply2d_col_kernel<2, V>), dim3(nbo), dim3(B2), 0, st, A, ncol, ntile, rows);
+                launch_apply<2, V>(nbo, st, A, ncol, ntile, rows);
                 fin(2, 2, nbo);
                 hipLaunchKernelGGL(xupd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
                 fin(3, 2, nb);
@@ -2436,7 +2480,7 @@ grte_status grte2d_create(const grte2d_problem *pb, const double *mu, const doub
                   }
                   return true;
               }() &&
-              dalloc(c, c->dS, c->N) && dalloc(c, c->itmp, c->N) && dalloc(c, c->idir, c->N) && dalloc(c, c->idir2, c->N) && dalloc(c, c->irows, 5 * c->N) && dalloc(c, c->yP2, c->N) && dalloc(c, c->pgc, c->N) && dalloc(c, c->idg, c->nE) && dalloc(c, c->idg32, c->nE) && dalloc(c, c->opc, OPC_N * c->N) && dalloc(c, c->dxv, c->nE) && dalloc(c, c->narrow, 1) && dalloc(c, c->mr, c->N) && dalloc(c, c->mv, c->N) &&
+              dalloc(c, c->dS, c->N) && dalloc(c, c->itmp, c->N) && dalloc(c, c->idir, c->N) && dalloc(c, c->idir2, c->N) && dalloc(c, c->pgc, c->N) && dalloc(c, c->idg, c->nE) && dalloc(c, c->idg32, c->nE) && dalloc(c, c->opc, OPC_N * c->N) && dalloc(c, c->dxv, c->nE) && dalloc(c, c->narrow, 1) && dalloc(c, c->mr, c->N) && dalloc(c, c->mv, c->N) &&
               dalloc(c, c->x, c->nE) && dalloc(c, c->r, c->nE) &&
               dalloc(c, c->p, c->nE) && dalloc(c, c->ph, c->nE) && dalloc(c, c->v, c->nE) &&
               dalloc(c, c->s, c->nE) && dalloc(c, c->sh, c->nE) && dalloc(c, c->t, c->nE) &&
@@ -2769,7 +2813,7 @@ grte_status grte2d_step(grte2d_ctx *c, double dt, double eps, grte2d_step_info *
     na.bflux = c->bflux;
     na.tg = c->tguess;
     na.gtol = c->guess_tol;
-    hipLaunchKernelGGL(moments2d_kernel, dim3(kblocks(c->nE, KRY_ITEMS)), dim3(B2), 0, st, na);
+    hipLaunchKernelGGL(moments2d_kernel, dim3(kblocks(c->nE, 0)), dim3(B2), 0, st, na);
     // (one thread per cell; fewer, longer-lived blocks: one atomic per wavefront and counter)
     const int nbn = std::min(nbc, 2048);
     if (c->guess_w) {
