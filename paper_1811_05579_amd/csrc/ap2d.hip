@@ -91,7 +91,7 @@ struct Sys {
     const double *ax, *gx, *ay, *gy;     // face alpha, gamma (gamma includes fe)
     const double *lam, *dmg, *cg, *kco;  // cell: Lambda, Lambda - g W1, g, K co c dt
     const double *rb1, *rb0, *acU;       // rhs = rb1 E^n_p + rb0; acU (correction's known part)
-    const double *sab, *ue;              // residual in difference form (see residual_at)
+    const double *sab, *ue;              // residual in difference form (residual2d_kernel)
     const double *pgc;                   // cell: g / (1 - g sum_p omega_p / d_p) of the block inverse
     const double *opc;                   // cell: the operator's coefficients packed, OPC_N per cell (opc2d_kernel)
 };
@@ -407,79 +407,155 @@ __global__ void __launch_bounds__(B2) rhs2d_kernel(VecArgs A)
     block_sums(&acc, 1, A.part);
 }
 
-// b - A x evaluated from the full face values and differences of nearly equal
+// r = b - A x (the pass's starting residual, stored as V), partial (r, r)
+// of the binary64 residual, the backward-error scale and (h, r) (h: the shadow vector).
+//
+// b - A x is evaluated from the full face values and differences of nearly equal
 // quantities (E^n - x, a c U - x), so that its rounding stays at the level of the
 // residual itself rather than of the large terms that cancel in it (the inflow
 // relations carry 2/eps times the inflow and the cell value):
 //   prediction  K eps^2 (E^n_p - x_p) + s (a c U^n - x_p) - g (1 - W1) x_p
 //               - g (W1 x_p - sum_q omega_q x_q) - k div O(x),   s = sigma0 c dt / (1 + ac beta)
 //   correction  K eps (E^n_p - a c U - eps x_p) - sigma0 c dt x_p - k div O(x)
-__device__ __forceinline__ double residual_at(const Sys &S, const double *En, const double *x, int t, int j,
-                                              int p, double &mag)
-{
-    const int P = S.P;
-    int iy, ix;
-    cell_yx(S, j, iy, ix);
-    const Nb X = load_nb(x, S.nx, S.ny, iy, ix, P, p);
-    Grad O;
-    faces<true, true>(S, iy, ix, p, &X, O);
-    const double xp = X.v[1][1];
-    const double mu = S.mu[p], eta = S.eta[p];
-    const double k = S.kco[j];
-    const double div = k * divergence(S, O, p);
-    // mag: an upper estimate of (|A| |x| + |b|) for this row -- the scale of the
-    // rounding a binary64 iterate and its residual cannot avoid (normwise
-    // backward error): the face terms bounded by the largest |x| of the
-    // neighbourhood, the inflow and O^n terms by their magnitudes
-    double xm = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) xm = fmax(xm, fabs(X.v[a][c]));
-    const int fl = iy * (S.nx + 1) + ix, fb = iy * S.nx + ix;
-    const double gsum = S.gx[fl] + S.gx[fl + 1] + S.gy[fb] + S.gy[fb + S.nx];
-    const double grad_bound = 2.0 * (fabs(mu) * S.idx + fabs(eta) * S.idy) * xm;
-    const double k2 = S.k2;
-    const double edge_bound = ((ix == 0 || ix == S.nx - 1) + (iy == 0 || iy == S.ny - 1)) * k2 *
-                              (4.0 * S.fe * xm + fabs(S.ue[j]));
-    const double dmag = fabs(k) * (fabs(mu) * S.idx + fabs(eta) * S.idy) *
-                        (fabs(O.l) + fabs(O.r) + fabs(O.b) + fabs(O.t) + gsum * grad_bound + edge_bound);
-    if (S.corr) {
-        const double a1 = S.rb1[j] * ((En[t] - S.ue[j]) - S.eps * xp), a2 = S.sab[j] * xp;
-        mag = fabs(S.rb1[j]) * (fabs(En[t]) + fabs(S.ue[j]) + S.eps * fabs(xp)) + fabs(a2) + dmag;
-        return a1 - a2 - div;
-    }
-    const double xr = group_lane0(xp, P);
-    const double w = S.om[p];
-    const double cpl = S.W1 * (xp - xr) - group_sum(w * (xp - xr), P);
-    const double g = S.cg[j];
-    mag = fabs(S.rb1[j]) * (fabs(En[t]) + fabs(xp)) + S.sab[j] * (fabs(S.ue[j]) + fabs(xp)) +
-          fabs(g) * (S.W1 * fabs(xp) + group_sum(w * fabs(xp), P)) + dmag;
-    return S.rb1[j] * (En[t] - xp) + S.sab[j] * (S.ue[j] - xp) - g * (1.0 - S.W1) * xp - g * cpl - div;
-}
-
-// r = b - A x (the pass's starting residual, stored as V), partial (r, r)
-// of the binary64 residual, the backward-error scale and (h, r) (h: the shadow vector)
-template <class V>
-__global__ void __launch_bounds__(B2) residual2d_kernel(VecArgs A)
+// The scale is an upper estimate of (|A| |x| + |b|) per row -- that of the rounding a
+// binary64 iterate and its residual cannot avoid (normwise backward error): the face
+// terms bounded by the largest |x| of the neighbourhood, the inflow and O^n terms by
+// their magnitudes.
+//
+// By columns, as the operator products below (tiles, the face value and the difference
+// across carried from row to row), the next row's x on its way.  Bound: the loads of a row
+// (7 of its own and 11 coefficients) at three wavefronts per SIMD.  512 x 512 cells of 32
+// pairs on an MI355X 124 us, 1024 x 1024 of 16 237 (prediction) and 248 (correction); a
+// thread per item with nine loads of x, both faces across and down and 13 coefficients
+// took 178 and 365.
+template <class V, bool CORR>
+__global__ void __launch_bounds__(B2, 3) residual2d_kernel(VecArgs A, int ncol, int ntile, int rows)
 {
     const Sys &S = A.S;
-    const int P = S.P;
+    const int P = S.P, nx = S.nx, ny = S.ny;
+    const int c = threadIdx.x >> S.lgP, p = threadIdx.x & (P - 1);
+    const int cw = B2 >> S.lgP;
+    const double *__restrict__ x = A.x;
     V *r = (V *)A.r;
+    const double mu = S.mu[p], eta = S.eta[p], w = S.om[p];
+    const double mux = mu * S.idx, ety = eta * S.idy, k2 = S.k2, ife = CORR ? 1.0 / S.fe : 0.0;
+    const double kx = mu > 0.0 ? k2 : -k2, ky = eta > 0.0 ? k2 : -k2;
+    const double ab = fabs(mux) + fabs(ety);
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int t = blockIdx.x * B2 + threadIdx.x; t < (int)A.n; t += gridDim.x * B2) {
-        const int j = t >> A.S.lgP, p = t & (P - 1);
-        double mag;
-        const double rr = residual_at(S, A.En, A.x, t, j, p, mag);
-        const V rf = (V)rr;
-        r[t] = rf;
-        if (A.mr) {
-            const double m = group_sum(S.om[p] * (double)rf, P);
-            if (p == 0) A.mr[j] = m;
+    for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+        const int ty = tile / ncol, tx = tile - ty * ncol;
+        const int ix = tx * cw + c;
+        if (ix >= nx) continue;                 // whole cells: a cell's P lanes agree
+        const int iy0 = ty * rows, iy1 = min(iy0 + rows, ny);
+        const int xl = max(ix - 1, 0), xr = min(ix + 1, nx - 1);
+        const bool wx = ix == 0 || ix == nx - 1;
+        const double hx = 0.5 * mu * (wx ? S.idx : 0.5 * S.idx);
+        auto ldrow = [&](int row, double(&v)[3]) {
+            const int q = min(max(row, 0), ny - 1) * nx;
+            v[0] = x[(size_t)(q + xl) * P + p];
+            v[1] = x[(size_t)(q + ix) * P + p];
+            v[2] = x[(size_t)(q + xr) * P + p];
+        };
+        auto ldu = [&](int row, double(&v)[3]) {   // a c U^{n+1} (the correction's known part)
+            const int q = min(max(row, 0), ny - 1) * nx;
+            v[0] = S.acU[q + xl];
+            v[1] = S.acU[q + ix];
+            v[2] = S.acU[q + xr];
+        };
+        auto amax = [](const double(&v)[3]) { return fmax(fmax(fabs(v[0]), fabs(v[1])), fabs(v[2])); };
+        double X[3][3], U[3][3], nxt[3], nxu[3];
+        ldrow(iy0 - 1, X[0]);
+        ldrow(iy0, X[1]);
+        ldrow(iy0 + 1, nxt);
+        if constexpr (CORR) {
+            ldu(iy0 - 1, U[0]);
+            ldu(iy0, U[1]);
+            ldu(iy0 + 1, nxu);
         }
-        acc[0] += rr * rr;
-        acc[1] += mag * mag;
-        acc[2] += shadow(t) * (double)rf;
+        double m0 = amax(X[0]), m1 = amax(X[1]);
+        // Omega . grad through the top face of row `d` (u: the row above)
+        auto vert = [&](const double(&d)[3], const double(&u)[3]) {
+            return ety * (u[1] - d[1]) + hx * ((d[2] - d[0]) + (u[2] - u[0]));
+        };
+        double gb = S.gy[iy0 * nx + ix];
+        double Ob = -gb * vert(X[0], X[1]) + S.ay[iy0 * nx + ix] * S.Oy0[(size_t)(iy0 * nx + ix) * P + p];
+        if constexpr (CORR) Ob -= gb * ife * vert(U[0], U[1]);
+        for (int iyb = iy0; iyb < iy1; iyb += 3) {
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                const int iy = iyb + e;
+                if (iy >= iy1) break;
+                const int j = iy * nx + ix, fl = j + iy, ft = j + nx;
+                const size_t t = (size_t)j * P + p;
+                const double En = A.En[t], ol = S.Ox0[(size_t)fl * P + p], orr = S.Ox0[(size_t)(fl + 1) * P + p],
+                             ot = S.Oy0[(size_t)ft * P + p];
+                const double gl = S.gx[fl], gr = S.gx[fl + 1], gt = S.gy[ft];
+                const double al = S.ax[fl], ar = S.ax[fl + 1], at = S.ay[ft];
+                const double k = S.kco[j], rb1 = S.rb1[j], sab = S.sab[j], ue = S.ue[j], cg = CORR ? 0.0 : S.cg[j];
+                const double(&Xd)[3] = X[e], (&Xc)[3] = X[(e + 1) % 3];
+                double(&Xu)[3] = X[(e + 2) % 3];
+                const double(&Ud)[3] = U[e], (&Uc)[3] = U[(e + 1) % 3];
+                double(&Uu)[3] = U[(e + 2) % 3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) Xu[q] = nxt[q];
+                ldrow(iy + 2, nxt);
+                if constexpr (CORR) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) Uu[q] = nxu[q];
+                    ldu(iy + 2, nxu);
+                }
+                const double m2 = amax(Xu), xm = fmax(fmax(m0, m1), m2);
+                m0 = m1;
+                m1 = m2;
+                const bool wy = iy == 0 || iy == ny - 1;
+                const double hy = 0.5 * eta * (wy ? S.idy : 0.5 * S.idy);
+                const double xp = Xc[1], uc = CORR ? Uc[1] : 0.0;
+                const double D1 = Xu[1] - Xd[1];
+                double Ol = -gl * (mux * (xp - Xc[0]) + hy * ((Xu[0] - Xd[0]) + D1)) + al * ol;
+                double Or = -gr * (mux * (Xc[2] - xp) + hy * (D1 + (Xu[2] - Xd[2]))) + ar * orr;
+                double Ot = -gt * vert(Xc, Xu) + at * ot;
+                if constexpr (CORR) {
+                    const double F1 = Uu[1] - Ud[1];
+                    Ol -= gl * ife * (mux * (uc - Uc[0]) + hy * ((Uu[0] - Ud[0]) + F1));
+                    Or -= gr * ife * (mux * (Uc[2] - uc) + hy * (F1 + (Uu[2] - Ud[2])));
+                    Ot -= gt * ife * vert(Uc, Uu);
+                }
+                // inflow relations at an edge face: the difference inflow - cell value is
+                // formed first (both terms carry 2/eps)
+                const double fx = S.fe * xp;
+                if (ix == 0) Ol = kx * ((S.b[p] - uc) - fx) - Or;
+                if (ix == nx - 1) Or = -kx * ((S.b[P + p] - uc) - fx) - Ol;
+                if (iy == 0) Ob = ky * ((S.b[2 * P + p] - uc) - fx) - Ot;
+                if (iy == ny - 1) Ot = -ky * ((S.b[3 * P + p] - uc) - fx) - Ob;
+                const double div = k * (mux * (Or - Ol) + ety * (Ot - Ob));
+                const double edge_bound = ((wx ? 1 : 0) + (wy ? 1 : 0)) * k2 * (4.0 * S.fe * xm + fabs(ue));
+                const double dmag = fabs(k) * ab * (fabs(Ol) + fabs(Or) + fabs(Ob) + fabs(Ot) +
+                                                    (gl + gr + gb + gt) * (2.0 * ab * xm) + edge_bound);
+                double rr, mag;
+                if constexpr (CORR) {
+                    const double a2 = sab * xp;
+                    mag = fabs(rb1) * (fabs(En) + fabs(ue) + S.eps * fabs(xp)) + fabs(a2) + dmag;
+                    rr = rb1 * ((En - ue) - S.eps * xp) - a2 - div;
+                } else {
+                    const double dr = xp - group_lane0(xp, P);
+                    const double cpl = S.W1 * dr - group_sum(w * dr, P);
+                    mag = fabs(rb1) * (fabs(En) + fabs(xp)) + sab * (fabs(ue) + fabs(xp)) +
+                          fabs(cg) * (S.W1 * fabs(xp) + group_sum(w * fabs(xp), P)) + dmag;
+                    rr = rb1 * (En - xp) + sab * (ue - xp) - cg * (1.0 - S.W1) * xp - cg * cpl - div;
+                }
+                gb = gt;
+                Ob = Ot;
+                const V rf = (V)rr;
+                r[t] = rf;
+                if (A.mr) {
+                    const double m = group_sum(w * (double)rf, P);
+                    if (p == 0) A.mr[j] = m;
+                }
+                acc[0] += rr * rr;
+                acc[1] += mag * mag;
+                acc[2] += shadow((int)t) * (double)rf;
+            }
+        }
     }
     block_sums(acc, 3, A.part);
 }
@@ -2266,6 +2342,10 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
                                nbk);
         hipLaunchKernelGGL(fin2d_kernel, dim3(1), dim3(FIN_T), 0, st, A, which, nbk);
     };
+    auto residual = [&] {
+        if (S.corr) hipLaunchKernelGGL((residual2d_kernel<V, true>), dim3(nbo), dim3(B2), 0, st, A, ncol, ntile, rows);
+        else hipLaunchKernelGGL((residual2d_kernel<V, false>), dim3(nbo), dim3(B2), 0, st, A, ncol, ntile, rows);
+    };
     int its_total = 0, state = 0;
     // iterations are enqueued in batches between convergence checks; the
     // batches are sized to end where the same pass of the last solve of the
@@ -2276,8 +2356,8 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
     for (int k = 0; k <= KRY_RESTARTS; ++k) pass_its[k] = -1;
     for (int restart = 0; restart <= KRY_RESTARTS; ++restart) {
         hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(64), 0, st, c->fl);
-        hipLaunchKernelGGL(residual2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-        fin(0, 3, nb);
+        residual();
+        fin(0, 3, nbo);
         // (the pass's first iteration takes p = r, its moment and dx = alpha ph +
         // omega sh, so p, v, dx and the moments need no clearing)
         if (hipMemcpyAsync(c->h_fl, c->fl, F_NF * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess)
@@ -2344,8 +2424,8 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
         if (c->h_fl[F_STATE] == 3 && its_total >= c->maxit) {
             // one more true residual for the report
             hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(64), 0, st, c->fl);
-            hipLaunchKernelGGL(residual2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-            fin(0, 3, nb);
+            residual();
+            fin(0, 3, nbo);
             if (hipMemcpyAsync(c->h_sc, c->sc, S_NS * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
                 return GRTE_E_HIP;
             if (hipStreamSynchronize(st) != hipSuccess) return GRTE_E_HIP;
