@@ -346,6 +346,8 @@ struct VecArgs {
     int red_b;                 // partials per block of the first reduction level
     double *sc;                // scalars
     int *fl;                   // flags
+    double *hsc;               // scalars and flags as the host reads them (pinned; written by
+    int *hfl;                  // fin2d_kernel at the start of a pass and after every iteration)
     double tol;
     int maxit;
     // isotropic (diffusion) correction of the preconditioner (null: none): the
@@ -1427,7 +1429,12 @@ __global__ void __launch_bounds__(FIN_T) fin2d_kernel(VecArgs A, int which, int 
             sc[S_MM] = mm;
             sc[S_ALPHA] = sc[S_OMEGA] = 1.0;
             sc[S_BETA] = 0.0;
-            A.fl[F_STATE] = (rr <= A.tol * A.tol * bb) ? 1 : 0;
+            const int done = (rr <= A.tol * A.tol * bb) ? 1 : 0;
+            A.fl[F_ITS] = A.hfl[F_ITS] = 0;
+            A.fl[F_STATE] = A.hfl[F_STATE] = done;
+            A.hsc[S_R0] = rr;
+            A.hsc[S_BB] = bb;
+            A.hsc[S_MM] = mm;
         }
     } else if (which == 1) {
         double f[1];
@@ -1435,7 +1442,7 @@ __global__ void __launch_bounds__(FIN_T) fin2d_kernel(VecArgs A, int which, int 
         const double rv = f[0];
         if (threadIdx.x == 0) {
             sc[S_RV] = rv;
-            if (rv == 0.0 || !isfinite(rv)) A.fl[F_STATE] = 2;
+            if (rv == 0.0 || !isfinite(rv)) A.fl[F_STATE] = A.hfl[F_STATE] = 2;
             else sc[S_ALPHA] = sc[S_RHO] / rv;
         }
     } else if (which == 2) {
@@ -1447,7 +1454,7 @@ __global__ void __launch_bounds__(FIN_T) fin2d_kernel(VecArgs A, int which, int 
             sc[S_TT] = tt;
             // t = A sh vanishes only with s: omega = 0 lets the last update still
             // take x += alpha ph, and the test after it stops on r = s
-            if (!isfinite(tt) || !isfinite(ts)) A.fl[F_STATE] = 2;
+            if (!isfinite(tt) || !isfinite(ts)) A.fl[F_STATE] = A.hfl[F_STATE] = 2;
             else sc[S_OMEGA] = tt == 0.0 ? 0.0 : ts / tt;
         }
     } else {
@@ -1456,16 +1463,16 @@ __global__ void __launch_bounds__(FIN_T) fin2d_kernel(VecArgs A, int which, int 
         const double rho = f[0], rr = f[1];
         if (threadIdx.x == 0) {
             const int its = A.fl[F_ITS] + 1;
-            A.fl[F_ITS] = its;
+            A.fl[F_ITS] = A.hfl[F_ITS] = its;
             sc[S_RR] = rr;
             const double rec = A.rec * A.tol;
             const bool done = rr <= rec * rec * sc[S_BB] || rr <= A.pass_red * A.pass_red * sc[S_R0];
             if (!done && its >= A.maxit) {
-                A.fl[F_STATE] = 3;
+                A.fl[F_STATE] = A.hfl[F_STATE] = 3;
             } else if (done) {
-                A.fl[F_STATE] = 1;              // the end of the pass
+                A.fl[F_STATE] = A.hfl[F_STATE] = 1;              // the end of the pass
             } else if (sc[S_OMEGA] == 0.0 || rho == 0.0 || !isfinite(rho)) {
-                A.fl[F_STATE] = 2;
+                A.fl[F_STATE] = A.hfl[F_STATE] = 2;
             } else {
                 sc[S_BETA] = (rho / sc[S_RHO]) * (sc[S_ALPHA] / sc[S_OMEGA]);
                 sc[S_RHO] = rho;
@@ -1483,11 +1490,6 @@ __global__ void __launch_bounds__(B2) xadd_kernel(double *x, const void *dv, siz
     if (fl[F_ITS] == 0) return;
     const V *d = (const V *)dv;
     for (int t = blockIdx.x * B2 + threadIdx.x; t < (int)n; t += gridDim.x * B2) x[t] += (double)d[t];
-}
-
-__global__ void reset_flags_kernel(int *fl)
-{
-    if (threadIdx.x < F_NF) fl[threadIdx.x] = 0;
 }
 
 // x0 of the correction: E_J = (E* - a c U^{n+1}) / eps
@@ -2316,6 +2318,8 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
     A.fl = c->fl;
     A.tol = c->tol;
     A.maxit = c->maxit;
+    A.hsc = c->h_sc;
+    A.hfl = c->h_fl;
     // the isotropic correction targets the angular coupling of the prediction;
     // the correction's systems have none
     const bool iso = c->iso_kind != 0 && !S.corr;
@@ -2350,86 +2354,90 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
     // iterations are enqueued in batches between convergence checks; the
     // batches are sized to end where the same pass of the last solve of the
     // same kind ended (iteration counts change slowly from step to step), and
-    // iterations enqueued past the end of a pass return at once
+    // iterations enqueued past the end of a pass return at once.  Where that pass
+    // iterated, the first batch goes out before the true residual is looked at: should the
+    // iterate be accepted after all, x has not changed
+    const bool timed = c->profiling != 0 && narrow;   // the binary32 products only
+    auto enqueue = [&](int batch) {
+        for (int k = 0; k < batch; ++k) {
+            if (iso) iso_solve(c, S, A, 0, st);
+            hipLaunchKernelGGL(pupd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
+            if (timed && k == 0) (void)hipEventRecord(c->ev0, st);
+            launch_apply<1, V>(nbo, st, A, ncol, ntile, rows);
+            if (timed && k == 0) (void)hipEventRecord(c->ev1, st);
+            fin(1, 1, nbo);
+            if (iso) iso_solve(c, S, A, 1, st);
+            hipLaunchKernelGGL(supd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
+            launch_apply<2, V>(nbo, st, A, ncol, ntile, rows);
+            fin(2, 2, nbo);
+            hipLaunchKernelGGL(xupd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
+            fin(3, 2, nb);
+        }
+    };
+    // wait for what is enqueued (a batch of iterations among it: its product's time)
+    auto wait = [&](bool batch) {
+        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) return false;
+        if (timed && batch) {
+            float ms = 0.0f;
+            if (hipEventElapsedTime(&ms, c->ev0, c->ev1) == hipSuccess) {
+                c->prof_ms += ms;
+                ++c->prof_n;
+            }
+        }
+        return true;
+    };
+    const volatile double *hsc = c->h_sc;
+    const volatile int *hfl = c->h_fl;
+    auto start_res = [&] { return hsc[S_BB] > 0 ? sqrt(hsc[S_R0] / hsc[S_BB]) : 0.0; };
     double res = INFINITY;
     int pass_its[KRY_RESTARTS + 1];
     for (int k = 0; k <= KRY_RESTARTS; ++k) pass_its[k] = -1;
     for (int restart = 0; restart <= KRY_RESTARTS; ++restart) {
-        hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(64), 0, st, c->fl);
         residual();
         fin(0, 3, nbo);
         // (the pass's first iteration takes p = r, its moment and dx = alpha ph +
         // omega sh, so p, v, dx and the moments need no clearing)
-        if (hipMemcpyAsync(c->h_fl, c->fl, F_NF * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess)
-            return GRTE_E_HIP;
-        if (hipMemcpyAsync(c->h_sc, c->sc, S_NS * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
-            return GRTE_E_HIP;
-        if (hipStreamSynchronize(st) != hipSuccess) return GRTE_E_HIP;
+        A.maxit = c->maxit - its_total;    // the cap holds for the whole solve
+        const int last = c->last_its[S.corr][restart];
+        const bool may = restart < KRY_RESTARTS && its_total < c->maxit;
+        int inpass = may && last > 0 ? std::min(CHUNK, last) : 0;   // iterations enqueued in this pass
+        enqueue(inpass);
+        if (!wait(inpass > 0)) return GRTE_E_HIP;
         const double prev = res;
-        res = c->h_sc[S_BB] > 0 ? sqrt(c->h_sc[S_RR] / c->h_sc[S_BB]) : 0.0;
+        res = start_res();
         // accept the iterate when its true residual meets the tolerance, or when
         // a pass of iterations no longer reduces it and it lies within KRY_FLOOR
         // units of binary64 rounding of || |A| |x| + |b| || / ||b|| (the
         // normwise backward-error floor) or of the tolerance, whichever is larger
-        if (c->h_fl[F_STATE] == 1 || c->h_sc[S_BB] == 0.0) {
+        if ((hfl[F_STATE] == 1 && hfl[F_ITS] == 0) || hsc[S_BB] == 0.0) {
             state = 1;
             break;
         }
-        const double lvl = c->h_sc[S_BB] > 0 ? 0x1p-53 * sqrt(c->h_sc[S_MM] / c->h_sc[S_BB]) : 0.0;
+        const double lvl = hsc[S_BB] > 0 ? 0x1p-53 * sqrt(hsc[S_MM] / hsc[S_BB]) : 0.0;
         if (restart > 0 && res > 0.5 * prev && res <= KRY_FLOOR * fmax(c->tol, lvl)) {
             state = 1;
             floor = 1;
             break;
         }
-        if (restart == KRY_RESTARTS || its_total >= c->maxit) break;
-        A.maxit = c->maxit - its_total;    // the cap holds for the whole solve
-        int inpass = 0;                    // iterations enqueued in this pass
-        while (true) {
-            const bool timed = c->profiling != 0 && narrow;   // the binary32 products only
-            const int last = c->last_its[S.corr][restart], left = last - inpass;
+        if (!may) break;
+        while (inpass == 0 || hfl[F_STATE] == 0) {
+            const int left = last - inpass;
             const int batch = last < 0 ? CHUNK : (left >= 1 ? std::min(CHUNK, left) : 2);
             inpass += batch;
-            for (int k = 0; k < batch; ++k) {
-                if (iso) iso_solve(c, S, A, 0, st);
-                hipLaunchKernelGGL(pupd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-                if (timed && k == 0) (void)hipEventRecord(c->ev0, st);
-                launch_apply<1, V>(nbo, st, A, ncol, ntile, rows);
-                if (timed && k == 0) (void)hipEventRecord(c->ev1, st);
-                fin(1, 1, nbo);
-                if (iso) iso_solve(c, S, A, 1, st);
-                hipLaunchKernelGGL(supd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-                launch_apply<2, V>(nbo, st, A, ncol, ntile, rows);
-                fin(2, 2, nbo);
-                hipLaunchKernelGGL(xupd2d_kernel<V>, dim3(nb), dim3(B2), 0, st, A);
-                fin(3, 2, nb);
-            }
-            if (hipGetLastError() != hipSuccess) return GRTE_E_HIP;
-            if (hipMemcpyAsync(c->h_fl, c->fl, F_NF * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess)
-                return GRTE_E_HIP;
-            if (hipStreamSynchronize(st) != hipSuccess) return GRTE_E_HIP;
-            if (timed) {
-                float ms = 0.0f;
-                if (hipEventElapsedTime(&ms, c->ev0, c->ev1) == hipSuccess) {
-                    c->prof_ms += ms;
-                    ++c->prof_n;
-                }
-            }
-            if (c->h_fl[F_STATE] != 0) break;
+            enqueue(batch);
+            if (!wait(true)) return GRTE_E_HIP;
         }
-        its_total += c->h_fl[F_ITS];
-        pass_its[restart] = c->h_fl[F_ITS];
+        its_total += hfl[F_ITS];
+        pass_its[restart] = hfl[F_ITS];
         hipLaunchKernelGGL(xadd_kernel<V>, dim3(nb), dim3(B2), 0, st, c->x, (const void *)c->dxv, c->nE, c->fl);
         // the recursion's residual has met the tolerance (or broken down): the
         // next pass recomputes the true residual and restarts from it if needed
-        if (c->h_fl[F_STATE] == 3 && its_total >= c->maxit) {
+        if (hfl[F_STATE] == 3 && its_total >= c->maxit) {
             // one more true residual for the report
-            hipLaunchKernelGGL(reset_flags_kernel, dim3(1), dim3(64), 0, st, c->fl);
             residual();
             fin(0, 3, nbo);
-            if (hipMemcpyAsync(c->h_sc, c->sc, S_NS * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
-                return GRTE_E_HIP;
-            if (hipStreamSynchronize(st) != hipSuccess) return GRTE_E_HIP;
-            res = c->h_sc[S_BB] > 0 ? sqrt(c->h_sc[S_RR] / c->h_sc[S_BB]) : 0.0;
+            if (!wait(false)) return GRTE_E_HIP;
+            res = start_res();
             state = 0;
             break;
         }
