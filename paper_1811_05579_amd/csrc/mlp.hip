@@ -194,9 +194,9 @@ __global__ void __launch_bounds__(256) mlp_grad_kernel(const float *theta, const
 
 // Adam on AE parameters per block: thread (a, s) sums the partials s, s + AS, .. of
 // parameter a, then the AS sums are joined in order.  Bound by the latency of the
-// partials' loads: 16 per thread in flight.  256 partials: 6.6 us (64 partials by one
-// thread per parameter: 20 us).
-constexpr int AE = 16, AS = 16;
+// partials' loads: 16 per thread in flight, 128 bytes of a partial per block.  256
+// partials: 5.3 us (64 bytes 6.4; 64 partials by one thread per parameter 20).
+constexpr int AE = 32, AS = 16;
 
 __global__ void __launch_bounds__(AE *AS) mlp_adam_kernel(float *theta, float *am, float *av, uint16_t *wbf,
                                                           const float *gpart, int nblk, const float *lpart, int B,
