@@ -1328,30 +1328,37 @@ constexpr int TILE_MAX_P = 32;
 bool pred_tiled(int N, int P) { return N <= 64 * TILE_MAX_M && P <= TILE_MAX_P; }
 
 // The prediction of the group's contexts (M: rows per thread of the form with a
-// work-group per pair, grid: its work-groups)
-grte_status launch_prediction(hipStream_t stream, Group<PredArgs> &g, int M, int grid, bool coop)
+// work-group per pair).  Each context takes the form and the rows per lane that it takes
+// alone, so a group's results are those of the single steps to the bit: one launch per
+// form and row count that occurs.
+grte_status launch_prediction(hipStream_t stream, const Group<PredArgs> &g, int M, bool coop)
 {
-    int rows = 0;
-    bool tiled = true;
-    for (int k = 0; k < g.n; ++k) {
-        rows = std::max(rows, (g.a[k].N + 63) / 64);
-        tiled = tiled && pred_tiled(g.a[k].N, g.a[k].P);
-    }
-    if (tiled) {
-        const dim3 b(64 * TILE_NW);
-        if (rows <= 2) hipLaunchKernelGGL(pred_tile_kernel<2>, dim3(g.n), b, 0, stream, g);
-        else if (rows <= 4) hipLaunchKernelGGL(pred_tile_kernel<4>, dim3(g.n), b, 0, stream, g);
-        else if (rows <= 6) hipLaunchKernelGGL(pred_tile_kernel<6>, dim3(g.n), b, 0, stream, g);
-        else hipLaunchKernelGGL(pred_tile_kernel<8>, dim3(g.n), b, 0, stream, g);
+    auto rows = [](const PredArgs &a) { return pred_tiled(a.N, a.P) ? std::max(2, (a.N + 127) / 128 * 2) : 0; };
+    for (int r = 0; r <= TILE_MAX_M; r += 2) {
+        Group<PredArgs> q{};
+        int grid = 0;
+        for (int k = 0; k < g.n; ++k) {
+            if (rows(g.a[k]) != r) continue;
+            q.first[q.n] = grid;
+            q.a[q.n++] = g.a[k];
+            grid += g.a[k].P;
+        }
+        if (q.n == 0) continue;
+        q.first[q.n] = grid;
+        const dim3 n(q.n), b(64 * TILE_NW);
+        grte_status st = GRTE_OK;
+        if (r == 2) hipLaunchKernelGGL(pred_tile_kernel<2>, n, b, 0, stream, q);
+        else if (r == 4) hipLaunchKernelGGL(pred_tile_kernel<4>, n, b, 0, stream, q);
+        else if (r == 6) hipLaunchKernelGGL(pred_tile_kernel<6>, n, b, 0, stream, q);
+        else if (r == 8) hipLaunchKernelGGL(pred_tile_kernel<8>, n, b, 0, stream, q);
+        else if (M == 2) st = launch_pred<2>(stream, q, grid, coop);
+        else if (M == 4) st = launch_pred<4>(stream, q, grid, coop);
+        else if (M == 8) st = launch_pred<8>(stream, q, grid, coop);
+        else st = launch_pred<16>(stream, q, grid, coop);
+        if (st != GRTE_OK) return st;
         HIPCHK(hipGetLastError());
-        return GRTE_OK;
     }
-    switch (M) {
-    case 2: return launch_pred<2>(stream, g, grid, coop);
-    case 4: return launch_pred<4>(stream, g, grid, coop);
-    case 8: return launch_pred<8>(stream, g, grid, coop);
-    default: return launch_pred<16>(stream, g, grid, coop);
-    }
+    return GRTE_OK;
 }
 
 template <int M>
@@ -1819,7 +1826,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
     hipLaunchKernelGGL(coef_kernel, dim3(ncb_max, n), dim3(256), 0, stream, gc);
     HIPCHK(hipGetLastError());
     if (sample && (st = prof_begin(c0, GRTE_TIMING_PREDICT, &ev_pred)) != GRTE_OK) return st;
-    if ((st = launch_prediction(stream, gp, M, grid, c0->coop_launch != 0)) != GRTE_OK) return st;
+    if ((st = launch_prediction(stream, gp, M, c0->coop_launch != 0)) != GRTE_OK) return st;
     if ((st = prof_end(c0, ev_pred)) != GRTE_OK) return st;
     bool any_guess = false;
     for (int g = 0; g < n; ++g) any_guess = any_guess || gn.a[g].gw != nullptr;
@@ -1972,7 +1979,7 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
         pa.direct = pred_direct(P, ctx->M);
         pa.NP = NT * ctx->M;
         ctx->bar_gen += 2ull * (unsigned long long)ctx->pred_maxit + 4ull;
-        if ((st = launch_prediction(stream, gp, M, P, ctx->coop_launch != 0)) != GRTE_OK) return st;
+        if ((st = launch_prediction(stream, gp, M, ctx->coop_launch != 0)) != GRTE_OK) return st;
         hipLaunchKernelGGL(picard_update_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, N, ac,
                            ctx->T, ctx->beta, ctx->rho, Tk, Tk1, ctx->ustar, dmax);
         HIPCHK(hipGetLastError());
