@@ -4,7 +4,7 @@ and Section 5).
 
 The Python layer only marshals arguments into the C ABI of include/grte.h;
 every stage of the step runs in the HIP kernels of csrc/grte.hip (one
-slab), csrc/batch.hip (many slabs in one persistent launch) and csrc/ap2d.hip
+slab), csrc/batch.hip (many slabs in one launch per phase) and csrc/ap2d.hip
 (a 2-D rectangle).  Arrays may
 be numpy arrays (host memory, copied by the library) or torch CUDA tensors
 (device memory, borrowed for the call).
@@ -357,7 +357,7 @@ def step_group(ctxs, dts, epss, info=False):
 
 
 class GrteBatch:
-    """Many independent slabs advanced by one persistent launch per step.
+    """Many independent slabs advanced by one graph of eight kernels per step.
 
     `members` is a sequence of objects with attributes N, P, m, L, a, c, Cv,
     dt, eps, mu, omega (e.g. workloads.Workload); arrays are exchanged in the

@@ -1212,7 +1212,6 @@ struct grte_ctx {
     unsigned long long *flags = nullptr;   // grid-barrier flags of the prediction kernel
     unsigned long long bar_gen = 0;        // generations used so far (strictly increasing)
     int cpb = 1;                           // cells per work-group of the per-cell kernels
-    size_t pred_lds = 0;
     int *stat = nullptr;
     // energy balance of the last step (projection kernel): O* at the end nodes,
     // per-block partial sums, and the four results

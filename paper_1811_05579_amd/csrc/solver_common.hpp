@@ -1,13 +1,12 @@
 // solver_common.hpp -- device building blocks shared by the single-instance
-// and the batched AP-step kernels (tridiagonal factor/solve in one
-// work-group, block reductions, grid barrier, node relations).
+// and the batched AP-step kernels (lane exchanges, tridiagonal factor/solve in
+// one work-group, block reductions, grid barrier, node relations).
 #pragma once
 #include <hip/hip_runtime.h>
 
 namespace {
 
 constexpr int NT = 256;          // threads per work-group of the tridiagonal solvers
-constexpr int LOGNT = 8;
 constexpr int MAX_M = 16;        // rows per thread -> N <= NT * MAX_M = 4096
 constexpr int MAX_N = NT * MAX_M;
 constexpr int MAX_P = 64;
