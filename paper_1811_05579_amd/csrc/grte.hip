@@ -50,9 +50,9 @@
 //
 // Tridiagonal systems are solved inside one work-group by a partitioned
 // method: each thread owns M consecutive rows, eliminates its interior rows
-// (Thomas), the chunk-boundary rows form a tridiagonal system of size NT that
-// every wavefront solves redundantly (published once in LDS; parallel cyclic
-// reduction across the lanes), and each thread back-substitutes.  All systems are M-matrices (diagonally
+// (Thomas), the chunk-boundary rows form a tridiagonal system, one row per thread, that
+// is merged by blocks of 1, 2, .. 32 lanes and then over the wavefronts' ends, and each
+// thread back-substitutes.  All systems are M-matrices (diagonally
 // dominant), so no pivoting is needed.  All reductions have a fixed order:
 // results are bitwise reproducible.
 
@@ -104,8 +104,7 @@ struct CoefArgs {
     const float *E32, *O32;      // binary32 storage: E^n = a c (T^n)^4 + E32, O^n = O32
     int f32;
     double mu1, mu2;             // sum omega mu, sum omega mu^2 (diffusion operator)
-    double *Ll, *Lu, *Lam, *LmG, *Gt, *Bd, *Aw, *Bc, *beta;   // Gt: position order (row_pos)
-    int M;                       // rows per thread of the prediction kernel (for Gt)
+    double *Ll, *Lu, *Lam, *LmG, *Gt, *Bd, *Aw, *Bc, *beta;
     double *Dl, *Dd, *Du;        // diffusion operator (prediction only)
     double *rho_n;               // sum_p omega_p E^n_p (prediction only)
     double *r;                   // right-hand sides, pair-major cell order [p * NP + j]
@@ -173,7 +172,7 @@ __device__ __forceinline__ void coef_body(const CoefArgs &A)
             const double lmg = Kc * eps * eps + s0 * c * dt / opb;
             A.beta[j] = beta;
             A.LmG[j] = lmg;
-            A.Gt[(j % A.M) * NT + j / A.M] = s0 * c * dt * (ac * beta) / opb;
+            A.Gt[j] = s0 * c * dt * (ac * beta) / opb;
             A.Dl[j] = A.mu2 * (-fl);
             A.Du[j] = A.mu2 * (-fr);
             A.Dd[j] = lmg + A.mu2 * (fl + fr) + A.mu1 * bd;
@@ -240,7 +239,7 @@ struct PredArgs {
     int accel;                         // 0 Richardson, 1 adaptive Chebyshev (see cheb_coeffs)
     double tol, one_minus_W, mu1avg, mu2avg;   // sum_p omega_p mu_p, sum_p omega_p mu_p^2 (diffusion operator)
     const double *Ll, *Lu, *Lam, *LmG, *Bd, *Dd;   // cell order; diffusion off-diagonals are mu2avg * L
-    const double *Gt;                  // G in position order (padded entries zero)
+    const double *Gt;                  // G (padded entries zero)
     const double *r, *mu, *omega, *rho0;   // r: pair-major, cell order [p*NP + j], zero in padded rows
     double *fac;                       // factorisations of the one-work-group form (pred_tile)
     double *part;                      // omega_p v_p, pair-major, position order [p*NP + t]
@@ -257,15 +256,24 @@ struct PredArgs {
 
 constexpr int PQ = 4;                  // pairs whose partial sums a thread has in flight
 constexpr int HIST_CAP = GRTE_HIST_CAP;
+constexpr int DIRECT_ROWS = 8;         // rows per thread of 256 above which the sums are always split
+
+// Wavefronts of a pair's work-group, for S4 rows per thread of 256 threads.  16 rows run as
+// 8 rows of 512 threads: half the serial elimination, and two wavefronts per SIMD to hide
+// the LDS reads of the off-diagonals (a step of three slabs of 4096 x 32: 264 us against
+// 312).  8 rows as 4 of 512 threads gain nothing (1543 x 16: 174 us against 169): their
+// update is the exchange between the work-groups.
+constexpr int wg_waves(int S4) { return S4 > 8 ? 8 : 4; }
 
 // One sweep of a pair from the iterate rho (position order, LDS):
 // v = T_p^{-1} [r_p - (Lam - G + mu^2 L + mu B) rho] for this thread's rows.
-template <int M>
+template <int NW, int M, bool KEEP>
 __device__ __forceinline__ void pred_sweep(const double *rho, const double *sLl, const double *sLu,
                                            const double (&rr)[M], const double (&lmg)[M], double mu, double mu2,
-                                           double bd0, double bdN, int N, const WgFac<M> &Ft, double (&v)[M],
-                                           WgLds<NT / 64> &S, int &ph)
+                                           double bd0, double bdN, int N, const WgFac<M, KEEP> &Ft, double (&v)[M],
+                                           WgLds<NW> &S, int &ph)
 {
+    constexpr int NT = 64 * NW;
     const int k = threadIdx.x, j0 = k * M;
 #pragma unroll
     for (int r = 0; r < M; ++r) {
@@ -288,7 +296,7 @@ __device__ __forceinline__ void pred_sweep(const double *rho, const double *sLl,
             v[r] = 0.0;
         }
     }
-    wg_solve<NT / 64, M>([&](int r) { return mu2 * sLl[r * NT + k]; }, [&](int r) { return mu2 * sLu[r * NT + k]; }, Ft,
+    wg_solve<NW, M>([&](int r) { return mu2 * sLl[r * NT + k]; }, [&](int r) { return mu2 * sLu[r * NT + k]; }, Ft,
                          v, S, ph);
 }
 
@@ -298,41 +306,47 @@ __device__ __forceinline__ void pred_sweep(const double *rho, const double *sLl,
 // factorisations in registers, merged solves with one work-group barrier each (wg_solve),
 // an exchange that needs no cache write-back, and, where the sums are short, one grid
 // barrier per update instead of two.  On an MI355X, an update of 100 cells x 8 pairs 4.7
-// us, 1543 x 16 8.9, 4096 x 32 (three slabs) 12.7; with a cyclic reduction through LDS and
+// us, 1543 x 16 8.9, 4096 x 32 (three slabs) 10.5 (12.7
+// with 16 rows of 256 threads); with a cyclic reduction through LDS and
 // barriers that wrote back and invalidated the L2, 8.8, 11.6 and 15.4.
-template <int M>
+template <int S4>
 __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, const int nblk)
 {
     extern __shared__ double smem[];
-    constexpr int NP = NT * M;           // padded rows
+    constexpr int NW = wg_waves(S4), M = 4 * S4 / NW, NT = 64 * NW, NP = NT * M;   // NP: padded rows
+    // 8 rows of 512 threads leave no registers for a / pivot, c / pivot and G (179 spilled
+    // with them, 50 without): LDS holds G and the off-diagonals
+    constexpr bool KEEP = S4 <= WG_KEEP;
     // Everything an iteration reads besides the other work-groups' partial sums
     // stays in LDS or registers.
     double *rho = smem;                  // current iterate (position order)
     double *sLl = smem + NP;             // operator coefficients (position order)
     double *sLu = smem + 2 * NP;
-    __shared__ WgLds<NT / 64> S;
+    double *sG = smem + 3 * NP;          // G (!KEEP)
+    __shared__ WgLds<NW> S;
     const int k = threadIdx.x;
     const int N = A.N, P = A.P;
     const int j0 = k * M;
     for (int j = k; j < NP; j += NT) {
         const bool in = j < N;
-        const int t = row_pos(j, M);
+        const int t = (j % M) * NT + j / M;
         rho[t] = in ? A.rho0[j] : 0.0;
         sLl[t] = in ? A.Ll[j] : 0.0;
         sLu[t] = in ? A.Lu[j] : 0.0;
+        if constexpr (!KEEP) sG[t] = A.Gt[j];
     }
     const double bd0 = A.Bd[0], bdN = A.Bd[N - 1];
     __syncthreads();
     const int p = bid;                   // one parity pair per work-group
     const double mu = A.mu[p], mu2 = mu * mu, wp = A.omega[p];
 
-    WgFac<M> Ft, Fd;
-    double rr[M], gg[M], lmg[M];         // r_p, G and Lam - G of this thread's rows
+    WgFac<M, KEEP> Ft, Fd;
+    double rr[M], gg[KEEP ? M : 1], lmg[M];         // r_p, G and Lam - G of this thread's rows
 #pragma unroll
     for (int r = 0; r < M; ++r) {
         const int j = j0 + r;
         rr[r] = A.r[(size_t)p * NP + j];
-        gg[r] = A.Gt[r * NT + k];
+        if constexpr (KEEP) gg[r] = A.Gt[j];
         lmg[r] = (j < N) ? A.LmG[j] : 0.0;
     }
     {
@@ -348,7 +362,7 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
                 b[r] = 1.0;
             }
         }
-        wg_factor<NT / 64, M>([&](int r) { return mu2 * sLl[r * NT + k]; }, b,
+        wg_factor<NW, M>([&](int r) { return mu2 * sLl[r * NT + k]; }, b,
                               [&](int r) { return mu2 * sLu[r * NT + k]; }, Ft, S);
 #pragma unroll
         for (int r = 0; r < M; ++r) {
@@ -356,7 +370,7 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
             b[r] = (j < N) ? A.Dd[j] : 1.0;
         }
         __syncthreads();   // the two factorisations share their LDS exchange area
-        wg_factor<NT / 64, M>([&](int r) { return A.mu2avg * sLl[r * NT + k]; }, b,
+        wg_factor<NW, M>([&](int r) { return A.mu2avg * sLl[r * NT + k]; }, b,
                               [&](int r) { return A.mu2avg * sLu[r * NT + k]; }, Fd, S);
     }
 
@@ -375,16 +389,17 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
 #pragma unroll
     for (int r = 0; r < M; ++r) dch[r] = 0.0f;
     while (true) {
+        const int kx = KEEP ? k : opaque(k);   // the words' addresses are formed anew, not kept (41 registers)
         // ---- sweep: v_p = T_p^{-1} [r_p - (Lam - G + mu^2 L + mu B) rho]
         double v[M];
-        pred_sweep<M>(rho, sLl, sLu, rr, lmg, mu, mu2, bd0, bdN, N, Ft, v, S, ph);
-        double *part = A.part + (M <= WG_KEEP && A.direct && (it & 1) ? half : 0), *part_p = part + (size_t)p * NP;
+        pred_sweep<NW, M>(rho, sLl, sLu, rr, lmg, mu, mu2, bd0, bdN, N, Ft, v, S, ph);
+        double *part = A.part + (S4 <= DIRECT_ROWS && A.direct && (it & 1) ? half : 0), *part_p = part + (size_t)p * NP;
 #pragma unroll
         for (int r = 0; r < M; ++r)
-            if (j0 + r < N) agent_put(&part_p[r * NT + k], wp * v[r]);
+            if (j0 + r < N) agent_put(&part_p[r * NT + kx], wp * v[r]);
         if (!grid_barrier(A.flags, ++gen, A.stat + 6, bid, nblk)) break;
         double rl[M], f[M];
-        if (M <= WG_KEEP && A.direct) {
+        if (S4 <= DIRECT_ROWS && A.direct) {
             // ---- the angular sum of this thread's rows, in every work-group:
             // res = sum_p omega_p v_p - (1 - W) rho
 #pragma unroll
@@ -412,7 +427,7 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
             const int h = k & 1, Ph = (P + 1) >> 1;
             const int q0 = h ? Ph : 0, q1 = h ? P : Ph;
             // lanes k and k^1 have the same position, so they iterate together
-            for (int t = tb + (k >> 1); t < te; t += NT / 2) {
+            for (int t = tb + (kx >> 1); t < te; t += NT / 2) {
                 double s = 0.0;
                 const bool in = (t % NT) * M + t / NT < N;
                 int q = in ? q0 : q1;
@@ -429,12 +444,12 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
             }
             if (!grid_barrier(A.flags, ++gen, A.stat + 6, bid, nblk)) break;
 #pragma unroll
-            for (int r = 0; r < M; ++r) rl[r] = j0 + r < N ? agent_get(&A.res[r * NT + k]) : 0.0;
+            for (int r = 0; r < M; ++r) rl[r] = j0 + r < N ? agent_get(&A.res[r * NT + kx]) : 0.0;
         }
         // ---- diffusion acceleration, identical in every work-group
 #pragma unroll
-        for (int r = 0; r < M; ++r) f[r] = gg[r] * rl[r];
-        wg_solve<NT / 64, M>([&](int r) { return A.mu2avg * sLl[r * NT + k]; },
+        for (int r = 0; r < M; ++r) f[r] = (KEEP ? gg[KEEP ? r : 0] : sG[r * NT + k]) * rl[r];
+        wg_solve<NW, M>([&](int r) { return A.mu2avg * sLl[r * NT + k]; },
                              [&](int r) { return A.mu2avg * sLu[r * NT + k]; }, Fd, f, S, ph);
         double alpha, beta;
         cheb_coeffs(C, A.accel, A.tol, alpha, beta);
@@ -452,7 +467,7 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
                 mr = fmax(mr, fabs(nw));
             }
         }
-        wg_max2<NT / 64>(md, mr);   // its barrier also publishes the rho update
+        wg_max2<NW>(md, mr);   // its barrier also publishes the rho update
         ++it;
         if (bid == 0 && k == 0 && it <= HIST_CAP) A.hist[it - 1] = mr > 0.0 ? md / mr : md;
         const float qprev = C.q1, qprev2 = C.q2, qprev3 = C.q3;
@@ -465,13 +480,13 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
         // E*_p = rho + T_p^{-1} [r_p - (T_p - G) rho] from the final iterate
         // (no grid barrier: each work-group sweeps its own pair once more)
         double v[M];
-        pred_sweep<M>(rho, sLl, sLu, rr, lmg, mu, mu2, bd0, bdN, N, Ft, v, S, ph);
+        pred_sweep<NW, M>(rho, sLl, sLu, rr, lmg, mu, mu2, bd0, bdN, N, Ft, v, S, ph);
 #pragma unroll
         for (int r = 0; r < M; ++r)
             if (j0 + r < N) A.estar[(size_t)(j0 + r) * P + p] = rho[r * NT + k] + v[r];
     }
     if (bid == 0) {
-        for (int j = k; j < N; j += NT) A.rho_out[j] = rho[row_pos(j, M)];
+        for (int j = k; j < N; j += NT) A.rho_out[j] = rho[(j % M) * NT + j / M];
         if (k == 0) {
             A.stat[0] = it;
             A.stat[1] = converged;
@@ -479,13 +494,13 @@ __device__ __forceinline__ void pred_body(const PredArgs &A, const int bid, cons
     }
 }
 
-template <int M>
-__global__ void __launch_bounds__(NT) pred_kernel(Group<PredArgs> G)
+template <int S4>
+__global__ void __launch_bounds__(64 * wg_waves(S4)) pred_kernel(Group<PredArgs> G)
 {
     int g = 0;
     while (g + 1 < G.n && (int)blockIdx.x >= G.first[g + 1]) ++g;
     const PredArgs A = G.a[g];
-    pred_body<M>(A, (int)blockIdx.x - G.first[g], G.first[g + 1] - G.first[g]);
+    pred_body<S4>(A, (int)blockIdx.x - G.first[g], G.first[g + 1] - G.first[g]);
 }
 
 // The prediction of small slabs: one work-group per context (slab_tile.hpp), no exchange
@@ -706,10 +721,10 @@ struct CorrArgs {
     int f32;
 };
 
-template <int M>
-__global__ void __launch_bounds__(NT) corr_kernel(Group<CorrArgs> G)
+template <int S4>
+__global__ void __launch_bounds__(64 * wg_waves(S4)) corr_kernel(Group<CorrArgs> G)
 {
-    constexpr int NP = NT * M;
+    constexpr int NW = wg_waves(S4), M = 4 * S4 / NW, NP = 64 * NW * M;
     const CorrArgs A = G.a[blockIdx.y];
     const int p = blockIdx.x;
     if (p >= A.P) return;                // contexts of the group may have fewer pairs
@@ -731,7 +746,7 @@ __global__ void __launch_bounds__(NT) corr_kernel(Group<CorrArgs> G)
             b[r] = 1.0;
         }
     }
-    tri_wg<NT / 64, M>(a, b, c, x);
+    tri_wg<NW, M>(a, b, c, x);
 #pragma unroll
     for (int r = 0; r < M; ++r) {
         const int j = j0 + r;
@@ -1292,10 +1307,10 @@ grte_status prof_end(grte_ctx *ctx, int idx)
     return GRTE_OK;
 }
 
-template <int M>
+template <int S4>
 size_t pred_lds_bytes()
 {
-    return (size_t)(3 * NT * M) * sizeof(double);
+    return (size_t)((S4 <= WG_KEEP ? 3 : 4) * NT * S4) * sizeof(double);
 }
 
 // The prediction's work-groups wait for each other at grid barriers, so they
@@ -1305,17 +1320,17 @@ size_t pred_lds_bytes()
 // other work occupying it -- when that fails the bounded barrier times out and
 // the step reports a sync error (grte_step_info.sync_error, GRTE_E_HIP) instead
 // of waiting forever.
-template <int M>
+template <int S4>
 grte_status launch_pred(hipStream_t stream, Group<PredArgs> &g, int grid, bool coop)
 {
     if (!coop) {
-        hipLaunchKernelGGL(pred_kernel<M>, dim3(grid), dim3(NT), pred_lds_bytes<M>(), stream, g);
+        hipLaunchKernelGGL(pred_kernel<S4>, dim3(grid), dim3(64 * wg_waves(S4)), pred_lds_bytes<S4>(), stream, g);
         HIPCHK(hipGetLastError());
         return GRTE_OK;
     }
     void *args[] = {&g};
-    HIPCHK(hipLaunchCooperativeKernel((const void *)pred_kernel<M>, dim3(grid), dim3(NT), args,
-                                      (unsigned)pred_lds_bytes<M>(), stream));
+    HIPCHK(hipLaunchCooperativeKernel((const void *)pred_kernel<S4>, dim3(grid), dim3(64 * wg_waves(S4)), args,
+                                      (unsigned)pred_lds_bytes<S4>(), stream));
     return GRTE_OK;
 }
 
@@ -1360,14 +1375,15 @@ grte_status launch_prediction(hipStream_t stream, const Group<PredArgs> &g, int 
     return GRTE_OK;
 }
 
-template <int M>
+template <int S4>
 grte_status launch_corr(hipStream_t stream, Group<CorrArgs> &g, int maxP)
 {
-    hipLaunchKernelGGL(corr_kernel<M>, dim3(maxP, g.n), dim3(NT), 0, stream, g);
+    hipLaunchKernelGGL(corr_kernel<S4>, dim3(maxP, g.n), dim3(64 * wg_waves(S4)), 0, stream, g);
     HIPCHK(hipGetLastError());
     return GRTE_OK;
 }
 
+// the work-group solvers' shape: rows per thread of 256 threads (wg_waves)
 int rows_per_thread(int N)
 {
     int M = 2;
@@ -1390,17 +1406,17 @@ grte_status convert_state(grte_ctx *ctx, int to32)
 // of 100 cells x 8 pairs, 16 words: 115 us against 141; 1543 x 16, 128 words: 200 against
 // 172; 512 x 16, 32 words: equal).
 constexpr int DIRECT_WORDS = 32;
-int pred_direct(int P, int M) { return M <= WG_KEEP && P * M <= DIRECT_WORDS; }
+int pred_direct(int P, int M) { return M <= DIRECT_ROWS && P * M <= DIRECT_WORDS; }
 
-template <int M>
+template <int S4>
 int coop_blocks_per_cu()
 {
     int nb = 0;
-    const size_t lds = pred_lds_bytes<M>();
-    if (hipFuncSetAttribute((const void *)pred_kernel<M>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    const size_t lds = pred_lds_bytes<S4>();
+    if (hipFuncSetAttribute((const void *)pred_kernel<S4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
         return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)pred_kernel<M>, NT, lds) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)pred_kernel<S4>, 64 * wg_waves(S4), lds) != hipSuccess)
         return 0;
     return nb;
 }
@@ -1748,7 +1764,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
         ca.T = ctx->T; ca.Tn = ctx->T; ca.sigma0 = ctx->sigma0; ca.mu = ctx->mu; ca.omega = ctx->omega;
         ca.bL = ctx->bL; ca.bR = ctx->bR; ca.E = ctx->E; ca.O = ctx->O;
         ca.mu1 = ctx->mu1; ca.mu2 = ctx->mu2;
-        ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.M = ctx->M; ca.NP = NT * ctx->M;
+        ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.NP = NT * ctx->M;
         ca.Bd = ctx->Bd; ca.Aw = ctx->Aw; ca.Bc = ctx->Bc; ca.beta = ctx->beta;
         ca.Dl = ctx->Dl; ca.Dd = ctx->Dd; ca.Du = ctx->Du; ca.rho_n = ctx->rho_n; ca.r = ctx->r;
         ca.stat = ctx->stat;
@@ -1949,7 +1965,7 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
     ca.Tn = ctx->T; ca.sigma0 = ctx->sigma0; ca.mu = ctx->mu; ca.omega = ctx->omega;
     ca.bL = ctx->bL; ca.bR = ctx->bR; ca.E = ctx->E; ca.O = ctx->O;
     ca.mu1 = ctx->mu1; ca.mu2 = ctx->mu2;
-    ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.M = M; ca.NP = NT * M;
+    ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.NP = NT * M;
     ca.Bd = ctx->Bd; ca.Aw = ctx->Aw; ca.Bc = ctx->Bc; ca.beta = ctx->beta;
     ca.Dl = ctx->Dl; ca.Dd = ctx->Dd; ca.Du = ctx->Du; ca.rho_n = ctx->rho_n; ca.r = ctx->r;
     ca.stat = ctx->stat;

@@ -248,19 +248,19 @@ struct WgLds {
     double u[2][2 * NW], w0[2][NW + 1];
 };
 constexpr int WG_KEEP = 8;                      // rows per thread up to which a / pivot and c / pivot are kept
-template <int M>
+template <int M, bool KEEP = M <= WG_KEEP>
 struct WgFac {
-    static constexpr int NK = M <= WG_KEEP ? M - 1 : 1;
+    static constexpr int NK = KEEP ? M - 1 : 1;
     double inv[M - 1], av[NK], cv[NK];          // interior rows: 1 / pivot, a / pivot, c / pivot
     double as, cs, ib;                          // last row: a, c, 1 / pivot
     double k[12], wl, vr;                       // its merges within the wavefront; responses to the rows next to it
     double kq[12], ve, cx;                      // the wavefronts' ends
 };
 
-template <int NW, int M, class GA, class GC>
-__device__ __forceinline__ void wg_factor(GA a, const double (&b)[M], GC c, WgFac<M> &F, WgLds<NW> &S)
+template <int NW, int M, bool KEEP, class GA, class GC>
+__device__ __forceinline__ void wg_factor(GA a, const double (&b)[M], GC c, WgFac<M, KEEP> &F, WgLds<NW> &S)
 {
-    static_assert(M >= 2 && (NW == 2 || NW == 4), "rows per thread; levels of the ends' merge below");
+    static_assert(M >= 2 && (NW == 2 || NW == 4 || NW == 8), "rows per thread; levels of the ends' merge below");
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double A0 = 0.0, C0 = 1.0, f = 1.0, cp = 0.0;
 #pragma unroll
@@ -269,7 +269,7 @@ __device__ __forceinline__ void wg_factor(GA a, const double (&b)[M], GC c, WgFa
         F.inv[i] = rcp64(i > 0 ? b[i] - ai * cp : b[i]);
         const double av = ai * F.inv[i];
         cp = c(i) * F.inv[i];
-        if constexpr (M <= WG_KEEP) {
+        if constexpr (KEEP) {
             F.av[i] = av;
             F.cv[i] = cp;
         }
@@ -312,18 +312,19 @@ __device__ __forceinline__ void wg_factor(GA a, const double (&b)[M], GC c, WgFa
     wl = end ? S.ew[l] : 0.0;
     merge_factor<1>(l, vr, wl, F.kq);
     if constexpr (NW > 2) merge_factor<2>(l, vr, wl, F.kq);
+    if constexpr (NW > 4) merge_factor<3>(l, vr, wl, F.kq);
 }
 
 // x: right-hand side in, solution out; a, c as given to wg_factor
-template <int NW, int M, class GA, class GC>
-__device__ __forceinline__ void wg_solve(GA a, GC c, const WgFac<M> &F, double (&x)[M], WgLds<NW> &S, int &ph)
+template <int NW, int M, bool KEEP, class GA, class GC>
+__device__ __forceinline__ void wg_solve(GA a, GC c, const WgFac<M, KEEP> &F, double (&x)[M], WgLds<NW> &S, int &ph)
 {
     auto av = [&](int i) {
-        if constexpr (M <= WG_KEEP) return F.av[i];
+        if constexpr (KEEP) return F.av[i];
         else return a(i) * F.inv[i];
     };
     auto cv = [&](int i) {
-        if constexpr (M <= WG_KEEP) return F.cv[i];
+        if constexpr (KEEP) return F.cv[i];
         else return c(i) * F.inv[i];
     };
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -350,6 +351,7 @@ __device__ __forceinline__ void wg_solve(GA a, GC c, const WgFac<M> &F, double (
     double e = l < 2 * NW ? fma(F.ve, S.w0[ph][(l >> 1) + 1], S.u[ph][l]) : 0.0;
     merge_solve<1>(e, F.kq);
     if constexpr (NW > 2) merge_solve<2>(e, F.kq);
+    if constexpr (NW > 4) merge_solve<3>(e, F.kq);
     const double xl = w > 0 ? lane_at(e, w > 0 ? 2 * w - 1 : 0) : 0.0;
     const double xr = w < NW - 1 ? fma(F.cx, lane_at(e, w < NW - 1 ? 2 * w + 2 : 0), S.w0[ph][w + 1]) : 0.0;
     ph ^= 1;
@@ -450,10 +452,6 @@ __device__ __forceinline__ bool grid_barrier(unsigned long long *flags, unsigned
 }
 
 __device__ __forceinline__ double kpow(double T, int m) { return m == 0 ? 1.0 : T * T * T; }
-
-// position of row j in the per-thread-chunk ("position") order used by the
-// tridiagonal solvers: t = (j % M) * NT + j / M
-__device__ __forceinline__ int row_pos(int j, int M) { return (j % M) * NT + j / M; }
 
 // O^n may be stored in binary64 or binary32 (OT); arithmetic is binary64
 template <class OT>

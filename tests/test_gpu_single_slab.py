@@ -43,3 +43,12 @@ def test_group_of_both_forms(shapes):
             assert np.array_equal(a, b)
         one.close()
         g.close()
+
+
+# work-groups of eight wavefronts (more than 2048 cells): ragged ends, pairs that the two
+# lanes of a position do not share evenly, more pairs than one batch of sums
+@pytest.mark.parametrize("N,nv,m,eps", [(2050, 10, 3, 1e-4), (3001, 22, 0, 1e-2), (4095, 36, 3, 1e-3)])
+def test_wide_work_group(N, nv, m, eps):
+    w = random_state(N, nv, seed=970 + N, m=m, eps=eps)
+    w.dt = 0.5 / N
+    compare(w, w.E, w.O, w.T)
