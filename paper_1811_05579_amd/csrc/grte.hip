@@ -564,8 +564,9 @@ struct NewtonArgs {
     const uint16_t *gw;      // learned initial guess: bfloat16 weights (null: Newton from T^n)
     const float *gnorm;      // and its normalisation
     double gtol;             // residual below which the guess is taken as the root
-    int *stat;   // [2] max its, [3] failed, [4] K* clamped, [5] negative root,
-                 // [7] guesses accepted, [8] guesses not used (Newton from T^n), [9] sum of Newton its,
+    int *its;    // Newton iterations of each cell
+    int *stat;   // [3] failed, [4] K* clamped, [5] negative root,
+                 // [7] guesses accepted, [8] guesses not used (Newton from T^n),
                  // [10] Newton started from the guess
 };
 
@@ -665,8 +666,10 @@ __device__ __forceinline__ void newton_body(const NewtonArgs &A, const uint16_t 
         if (!ok) atomicAdd(&A.stat[3], 1);
     }
     A.Tnew[j] = T;
-    atomicMax(&A.stat[2], its);
-    atomicAdd(&A.stat[9], its);
+    // an atomic per wavefront and counter on two words of the context takes longer than
+    // all the rest (21.6 us for three slabs of 4096 x 32, 10.4 without): the maximum and
+    // the sum over the cells are left to energy_final_kernel
+    A.its[j] = its;
 }
 
 // GUESS: some context of the launch carries a learned guess (its weights are
@@ -783,6 +786,7 @@ struct ProjArgs {
     const double *Tn, *Tnew, *rho_n, *obnd;
     double *epart;          // 2 per block
     double *energy;         // E_before, E_after, outflow dt, defect
+    const int *its;         // Newton iterations of each cell
     int *stat;              // per-step counters; the sticky word collects their error flags
 };
 
@@ -877,15 +881,38 @@ __global__ void __launch_bounds__(256) project_kernel(Group<ProjArgs> G)
     energy_partial(e0, e1, A.epart);
 }
 
-// the energy balance of each context (one block per context) and the step's
-// error flags, after project_kernel
+// the energy balance of each context (one block per context), the largest and the sum of
+// its cells' Newton iterations and the step's error flags, after project_kernel
 __global__ void __launch_bounds__(256) energy_final_kernel(Group<ProjArgs> G)
 {
     const ProjArgs A = G.a[blockIdx.x];
     const int nb = (A.N + A.cpb - 1) / A.cpb;
+    __shared__ int s_mx[4], s_sum[4];
+    int mx = 0, sum = 0, q[MAX_N / 256];     // all loads in flight (one after the other: 4 us more)
+#pragma unroll
+    for (int u = 0; u < MAX_N / 256; ++u) {
+        const int j = u * 256 + threadIdx.x;
+        q[u] = j < A.N ? A.its[j] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < MAX_N / 256; ++u) {
+        mx = max(mx, q[u]);
+        sum += q[u];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        mx = max(mx, __shfl_xor(mx, o));
+        sum += __shfl_xor(sum, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        s_mx[threadIdx.x >> 6] = mx;
+        s_sum[threadIdx.x >> 6] = sum;
+    }
     double eb, ea;
     energy_total(A.epart, nb, eb, ea);
+    __syncthreads();
     if (threadIdx.x == 0) {
+        A.stat[2] = max(max(s_mx[0], s_mx[1]), max(s_mx[2], s_mx[3]));
+        A.stat[9] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
         const int P = A.P;
         double fl = 0.0;
         for (int q = 0; q < P; ++q) fl += A.omega[q] * A.mu[q] * (A.obnd[P + q] - A.obnd[q]);
@@ -1227,7 +1254,7 @@ struct grte_ctx {
     unsigned long long *flags = nullptr;   // grid-barrier flags of the prediction kernel
     unsigned long long bar_gen = 0;        // generations used so far (strictly increasing)
     int cpb = 1;                           // cells per work-group of the per-cell kernels
-    int *stat = nullptr;
+    int *stat = nullptr;         // NSTAT_ALL counters, then the cells' Newton iterations
     // energy balance of the last step (projection kernel): O* at the end nodes,
     // per-block partial sums, and the four results
     double *obnd = nullptr, *epart = nullptr, *energy = nullptr;
@@ -1554,7 +1581,7 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
     double *flagmem = nullptr;
     if (st == GRTE_OK) st = alloc(ctx, &flagmem, (size_t)MAX_P * BAR_STRIDE);
     ctx->flags = (unsigned long long *)flagmem;
-    if (st == GRTE_OK && hipMalloc((void **)&ctx->stat, NSTAT_ALL * sizeof(int)) != hipSuccess) st = GRTE_E_NOMEM;
+    if (st == GRTE_OK && hipMalloc((void **)&ctx->stat, (NSTAT_ALL + ctx->N) * sizeof(int)) != hipSuccess) st = GRTE_E_NOMEM;
     if (st == GRTE_OK) st = alloc(ctx, &ctx->obnd, 2 * P);
     if (st == GRTE_OK) st = alloc(ctx, &ctx->epart, 2 * N);   // 2 per cell block (at most N blocks)
     if (st == GRTE_OK) st = alloc(ctx, &ctx->energy, 4);
@@ -1793,7 +1820,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
         na.O = ctx->O; na.Aw = ctx->Aw; na.Bc = ctx->Bc; na.beta = ctx->beta;
         na.rho_n = ctx->rho_n; na.Tn = ctx->T; na.sigma0 = ctx->sigma0; na.mu = ctx->mu; na.omega = ctx->omega;
         na.bL = ctx->bL; na.bR = ctx->bR; na.Tnew = ctx->T2; na.ustar = ctx->ustar; na.Dv = ctx->Dv;
-        na.ostar = ctx->ostar; na.stat = ctx->stat; na.rstar = ctx->rstar;
+        na.ostar = ctx->ostar; na.stat = ctx->stat; na.its = ctx->stat + NSTAT_ALL; na.rstar = ctx->rstar;
         na.obnd = ctx->obnd;
         na.moments_only = alt ? 1 : 0;
         // the alternative correction (3.14): its operators, E_J into the scratch
@@ -1827,7 +1854,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
         pj.O32 = ctx->O32; pj.O32out = ctx->O32b; pj.f32 = ctx->f32;
         pj.dx = dx; pj.c = ctx->c; pj.cv = ctx->cv; pj.dt = dt;
         pj.Tn = ctx->T; pj.Tnew = ctx->T2; pj.rho_n = ctx->rho_n; pj.obnd = ctx->obnd;
-        pj.epart = ctx->epart; pj.energy = ctx->energy; pj.stat = ctx->stat;
+        pj.epart = ctx->epart; pj.energy = ctx->energy; pj.stat = ctx->stat; pj.its = ctx->stat + NSTAT_ALL;
     }
     gp.first[n] = grid;
     if (grid > c0->coop_capacity) return GRTE_E_UNSUPPORTED;
