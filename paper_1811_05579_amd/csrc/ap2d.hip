@@ -47,6 +47,7 @@
 namespace {
 
 constexpr int B2 = 256;        // threads per block of the (cell, pair) kernels
+constexpr int NEWT_BLOCKS = 2048;   // most blocks of the temperature kernel (one thread per cell, grid-stride)
 constexpr int MAXB = 2048;     // blocks of the grid-stride kernels outside the Krylov loop
 // the Krylov kernels over the N*P items run KRY_ITEMS items per thread (up to
 // KRYB blocks); their per-block partial sums are reduced by one block of
@@ -1552,7 +1553,8 @@ struct NewtArgs {
     int m, maxit;
     double *Tnew, *ustar, *Dv, *rhon, *rstar;
     double *bflux;               // edge cells: outflow through their edge faces, sum_p omega_p (...)
-    int *stat;                   // [0] max its, [1] failed, [2] K* clamped, [3] negative root, [4] sum its,
+    int2 *its;                   // the largest and the sum of each block's Newton iterations
+    int *stat;                   // [1] failed, [2] K* clamped, [3] negative root,
                                  // [5] guesses accepted, [6] guesses not used, [7] Newton started from a guess
     const double *tg;            // learned starting values (guess2d_kernel; GUESS kernels only)
     double gtol;                 // residual below which the guess is taken as the root
@@ -1695,7 +1697,6 @@ __global__ void __launch_bounds__(B2) newton2d_kernel(NewtArgs A)
         mx = max(mx, its);
         sum += its;
     }
-    // one atomic per wavefront and counter
     for (int o = 32; o > 0; o >>= 1) {
         mx = max(mx, __shfl_xor(mx, o, 64));
         sum += __shfl_xor(sum, o, 64);
@@ -1706,15 +1707,27 @@ __global__ void __launch_bounds__(B2) newton2d_kernel(NewtArgs A)
         unused += __shfl_xor(unused, o, 64);
         started += __shfl_xor(started, o, 64);
     }
+    // atomics of every wavefront on one word take far longer than the Newton itself (512 x
+    // 512 cells 99 us, 9 with a maximum and a sum per block left to the energy kernel); the
+    // other counters are rare
+    __shared__ int s_mx[B2 / 64], s_sum[B2 / 64];
     if (__lane_id() == 0) {
-        if (mx) atomicMax(&A.stat[0], mx);
+        s_mx[threadIdx.x >> 6] = mx;
+        s_sum[threadIdx.x >> 6] = sum;
         if (failed) atomicAdd(&A.stat[1], failed);
         if (clamped) atomicAdd(&A.stat[2], clamped);
         if (neg) atomicAdd(&A.stat[3], neg);
-        if (sum) atomicAdd(&A.stat[4], sum);
         if (acc) atomicAdd(&A.stat[5], acc);
         if (unused) atomicAdd(&A.stat[6], unused);
         if (started) atomicAdd(&A.stat[7], started);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < B2 / 64; ++q) {
+            mx = max(mx, s_mx[q]);
+            sum += s_sum[q];
+        }
+        A.its[blockIdx.x] = make_int2(mx, sum);
     }
 }
 
@@ -1786,6 +1799,9 @@ struct EnergyArgs {
     double *epart;            // 3 per block
     unsigned *ecnt;           // blocks done (reset to 0 by the last one)
     double *energy;           // E_before, E_after, outflow dt, defect
+    int nits;                 // blocks of newton2d_kernel
+    const int2 *its;          // their Newton iterations, reduced by block 0
+    int *stat;                // [0] max its, [4] sum its
 };
 
 __global__ void __launch_bounds__(B2) energy2d_kernel(EnergyArgs A)
@@ -1793,6 +1809,38 @@ __global__ void __launch_bounds__(B2) energy2d_kernel(EnergyArgs A)
     __shared__ double s0[B2], s1[B2], s2[B2];
     __shared__ int s_last;
     const int t = threadIdx.x;
+    if (blockIdx.x == 0) {
+        __shared__ int s_mx[B2 / 64], s_sum[B2 / 64];
+        int2 q[NEWT_BLOCKS / B2];
+#pragma unroll
+        for (int u = 0; u < NEWT_BLOCKS / B2; ++u) {
+            const int b = u * B2 + t;
+            q[u] = b < A.nits ? A.its[b] : make_int2(0, 0);
+        }
+        int mx = 0, sum = 0;
+#pragma unroll
+        for (int u = 0; u < NEWT_BLOCKS / B2; ++u) {
+            mx = max(mx, q[u].x);
+            sum += q[u].y;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            mx = max(mx, __shfl_xor(mx, o, 64));
+            sum += __shfl_xor(sum, o, 64);
+        }
+        if (__lane_id() == 0) {
+            s_mx[t >> 6] = mx;
+            s_sum[t >> 6] = sum;
+        }
+        __syncthreads();
+        if (t == 0) {
+            for (int w = 1; w < B2 / 64; ++w) {
+                mx = max(mx, s_mx[w]);
+                sum += s_sum[w];
+            }
+            A.stat[0] = mx;
+            A.stat[4] = sum;
+        }
+    }
     double e0 = 0.0, e1 = 0.0, fo = 0.0;
     for (int j = blockIdx.x * B2 + t; j < A.n; j += A.nb * B2) {
         e0 += A.dxdy * (A.rhon[j] / A.c + A.cv * A.Tn[j]);
@@ -2573,7 +2621,7 @@ grte_status grte2d_create(const grte2d_problem *pb, const double *mu, const doub
               dalloc(c, c->p, c->nE) && dalloc(c, c->ph, c->nE) && dalloc(c, c->v, c->nE) &&
               dalloc(c, c->s, c->nE) && dalloc(c, c->sh, c->nE) && dalloc(c, c->t, c->nE) &&
               dalloc(c, c->Es, c->nE) && dalloc(c, c->part, 4 * KRYB) && dalloc(c, c->part2, 4 * KRYB) && dalloc(c, c->sc, S_NS) &&
-              dalloc(c, c->fl, F_NF) && dalloc(c, c->stat, 8);
+              dalloc(c, c->fl, F_NF) && dalloc(c, c->stat, 8 + 2 * NEWT_BLOCKS);
     if (ok) ok = hipHostMalloc((void **)&c->h_fl, F_NF * sizeof(int)) == hipSuccess;
     if (ok) ok = hipHostMalloc((void **)&c->h_sc, S_NS * sizeof(double)) == hipSuccess;
     if (!ok) {
@@ -2897,13 +2945,13 @@ grte_status grte2d_step(grte2d_ctx *c, double dt, double eps, grte2d_step_info *
     na.Dv = c->Dv;
     na.rhon = c->rhon;
     na.stat = c->stat;
+    na.its = (int2 *)(c->stat + 8);
     na.rstar = c->rstar;
     na.bflux = c->bflux;
     na.tg = c->tguess;
     na.gtol = c->guess_tol;
     hipLaunchKernelGGL(moments2d_kernel, dim3(kblocks(c->nE, 0)), dim3(B2), 0, st, na);
-    // (one thread per cell; fewer, longer-lived blocks: one atomic per wavefront and counter)
-    const int nbn = std::min(nbc, 2048);
+    const int nbn = std::min(nbc, NEWT_BLOCKS);
     if (c->guess_w) {
         GuessArgs ga;
         ga.n = (int)c->N;
@@ -2974,6 +3022,9 @@ grte_status grte2d_step(grte2d_ctx *c, double dt, double eps, grte2d_step_info *
         ea.epart = c->epart;
         ea.ecnt = c->ecnt;
         ea.energy = c->energy;
+        ea.nits = nbn;
+        ea.its = na.its;
+        ea.stat = c->stat;
         hipLaunchKernelGGL(energy2d_kernel, dim3(ea.nb), dim3(B2), 0, st, ea);
     }
     if (hipGetLastError() != hipSuccess) return GRTE_E_HIP;
