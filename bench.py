@@ -55,7 +55,7 @@ HBM_PEAK_GBS = 8000.0
 # WRITE_SIZE runs, scaled by a plain-copy calibration; commands and raw values in
 # the named profiles/ files).  Set to None when the kernel changes.
 TRAFFIC = {
-    ("config2", "fp64"): (1.1019e8, "profiles/pred_kernel_config2_hbm_traffic.txt"),
+    ("config2", "fp64"): (1.1035e8, "profiles/pred_kernel_config2_hbm_traffic.txt"),
     ("config2", "fp32"): (None, None),
     ("config4", "fp64"): (None, None),
     ("config4", "fp32"): (2.3314e+10, "profiles/batch_step_config4_hbm_traffic.txt"),
