@@ -60,7 +60,8 @@ typedef struct grte_problem {
 
 /* Diagnostics of one step (filled only when a non-NULL pointer is passed). */
 typedef struct grte_step_info {
-    int pred_iters;       /* iterations of the prediction solve                 */
+    int pred_iters;       /* iterations of the prediction solve (those that
+                             confirm its end not counted; see grte_set_solver)  */
     int pred_converged;   /* 1 if the prediction met its tolerance              */
     int newton_max_iters; /* largest Newton iteration count over the cells      */
     int newton_failed;    /* cells whose Newton solve hit the cap               */
@@ -267,7 +268,13 @@ grte_status grte_get_stage(grte_ctx *ctx, int stage, double *out, int on_device)
  * optically thick slabs, e.g. N = 4096, 64 ordinates, eps = 1e-4, and up to
  * ~2.3e-14 on some binary32-stored states of the batched ensemble right after
  * the cold start).  Both count as converged (info pred_converged); the second
- * also sets pred_floor_stop (the batched path applies the same test). */
+ * also sets pred_floor_stop (the batched path applies the same test).
+ * Slabs of up to 512 cells and 32 pairs, and all slabs of a batch, meet the test
+ * with a residual carried from update to update; further plain updates with
+ * residuals formed anew (usually one) then confirm it.  The cap, pred_iters and
+ * the history hold for the updates up to the one that met the test; the
+ * confirming ones have a cap of the same size, and if they run out of it the
+ * solve has not converged and pred_iters and the history take them all. */
 grte_status grte_set_solver(grte_ctx *ctx, double pred_tol, int pred_maxit, int newton_maxit);
 
 /* Acceleration of the prediction iteration (default GRTE_ACCEL_CHEBYSHEV).

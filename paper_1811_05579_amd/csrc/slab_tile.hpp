@@ -280,8 +280,9 @@ __device__ __forceinline__ void own_rows(int w, F &f)
 }
 
 // Runs the iteration; store(p, first row, x) takes E*_p of the lane's M rows.
-// Returns the updates up to the one that met the stopping test (those that confirm it
-// with true residuals are not counted); converged as pred_stop.
+// Returns the updates up to the one that met the stopping test: the cap holds for those.
+// The updates that confirm it with true residuals are not counted and have a cap of the
+// same size; if they run out of it, all updates are returned.  converged as pred_stop.
 template <int NW, int M, class Store>
 __device__ __forceinline__ int pred_tile(const TileSys &S, double *sm, int &converged, Store store)
 {
@@ -495,7 +496,7 @@ __device__ __forceinline__ int pred_tile(const TileSys &S, double *sm, int &conv
             tile_sync<NW>();
         }
         ++it;
-        if (S.hist && tid == 0 && it <= GRTE_HIST_CAP && !polish) S.hist[it - 1] = mr > 0.0 ? md / mr : md;
+        if (S.hist && tid == 0 && it <= GRTE_HIST_CAP) S.hist[it - 1] = mr > 0.0 ? md / mr : md;
         const float qprev = C.q1, qprev2 = C.q2, qprev3 = C.q3;
         const float q = (float)(mr > 0.0 ? md / mr : md);
         cheb_record(C, q);
@@ -505,7 +506,7 @@ __device__ __forceinline__ int pred_tile(const TileSys &S, double *sm, int &conv
             converged = stop;
             break;
         }
-        if (it >= S.maxit) break;
+        if (polish ? it - met >= S.maxit : !stop && it >= S.maxit) break;
         if (stop && !polish) {                         // plain updates, and the test's history anew
             polish = true;
             met = it;
@@ -558,7 +559,7 @@ __device__ __forceinline__ int pred_tile(const TileSys &S, double *sm, int &conv
     }
     for (int j = tid; j < N; j += 64 * NW) S.rho_out[j] = slot[lpos(j)];
     tile_sync<NW>();                                   // the tile's LDS and E* settled
-    return polish ? met : it;
+    return polish && converged ? met : it;
 }
 
 }  // namespace
