@@ -504,14 +504,25 @@ __global__ void __launch_bounds__(64 * wg_waves(S4)) pred_kernel(Group<PredArgs>
 }
 
 // The prediction of small slabs: one work-group per context (slab_tile.hpp), no exchange
-// between work-groups and so no cooperative launch.
-constexpr int TILE_NW = 8, TILE_MAX_M = 8;
+// between work-groups and so no cooperative launch.  Up to TILE_MAX_M rows per lane and
+// TILE_MAX_P pairs: a whole step of 100 cells x 8 pairs 63 us against 116 with a work-group
+// per pair and a cooperative launch, 128 x 32 107 against 147, 512 x 16 106 against 139; at
+// 512 x 32 both take 147, at 512 x 64 246 against 176 (each of the eight wavefronts has
+// eight pairs in turn).  An ordinary launch takes about 22 us off the other form and none
+// off this one (512 x 32 140 us, 512 x 33 in the other form 144 and 118), so there the line
+// would lie lower; it is the same for both launches, which give the same bits.
+constexpr int TILE_NW = 8, TILE_MAX_M = 8, TILE_MAX_P = 32;
+
+// rows per lane of a context's tile; 0: a work-group per pair
+__host__ __device__ constexpr int tiled_rows(int N, int P)
+{
+    const int M = (N + 127) / 128 * 2;
+    return N <= 64 * TILE_MAX_M && P <= TILE_MAX_P ? M : 0;
+}
 
 template <int M>
-__global__ void __launch_bounds__(64 * TILE_NW) pred_tile_kernel(Group<PredArgs> G)
+__device__ __forceinline__ void tile_body(const PredArgs &A, double *sm)
 {
-    __shared__ double sm[tile_lds<TILE_NW, M>()];
-    const PredArgs A = G.a[blockIdx.x];
     const int N = A.N, P = A.P;
     TileSys S;
     S.N = N;
@@ -546,6 +557,38 @@ __global__ void __launch_bounds__(64 * TILE_NW) pred_tile_kernel(Group<PredArgs>
         A.stat[0] = it;
         A.stat[1] = converged;
     }
+}
+
+template <int M>
+__global__ void __launch_bounds__(64 * TILE_NW) pred_tile_kernel(Group<PredArgs> G)
+{
+    __shared__ double sm[tile_lds<TILE_NW, M>()];
+    tile_body<M>(G.a[blockIdx.x], sm);
+}
+
+// A group whose contexts differ in form or rows per lane, each in the form that it takes
+// alone: the tiles and the pairs' work-groups run beside each other.  Bound by the longest
+// context's chain.  A whole step on an MI355X: 100, 200, 300 and 500 cells of 8 pairs 80 us
+// (173 with a launch per row count, one after the other), 512 x 32 beside 512 x 33 172 (243),
+// under the ordinary launch 148 (220).  A pair's work-group is the first wavefronts only (a work-group barrier waits for the
+// wavefronts that have not ended).
+constexpr int MIXED_LDS = tile_lds<TILE_NW, TILE_MAX_M>();   // also covers the pairs' work-groups
+
+__global__ void __launch_bounds__(64 * TILE_NW) pred_mixed_kernel(Group<PredArgs> G)
+{
+    static_assert(TILE_MAX_M == 8 && 3 * NT * 2 <= MIXED_LDS, "the cases below; the pairs' LDS");
+    extern __shared__ double smem[];
+    int g = 0;
+    while (g + 1 < G.n && (int)blockIdx.x >= G.first[g + 1]) ++g;
+    const PredArgs A = G.a[g];
+    switch (tiled_rows(A.N, A.P)) {
+    case 2: tile_body<2>(A, smem); return;
+    case 4: tile_body<4>(A, smem); return;
+    case 6: tile_body<6>(A, smem); return;
+    case 8: tile_body<8>(A, smem); return;
+    }
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= wg_waves(2)) return;
+    pred_body<2>(A, (int)blockIdx.x - G.first[g], G.first[g + 1] - G.first[g]);
 }
 
 // -------------------------------------------------------------------------
@@ -1223,6 +1266,7 @@ struct grte_ctx {
     int pred_accel = GRTE_ACCEL_CHEBYSHEV;
     double *hist = nullptr;       // convergence history of the last prediction solve
     int coop_capacity = 0;                 // co-resident prediction work-groups on the device
+    int mixed_capacity = 0;                // of pred_mixed_kernel (slabs that the tiles take)
     int coop_launch = 1;                   // 1: cooperative launch of the prediction; 0: ordinary launch
     int keep = 1;
     int corr_kind = GRTE_CORRECTION_CONSERVATIVE;   // grte_set_correction
@@ -1361,45 +1405,59 @@ grte_status launch_pred(hipStream_t stream, Group<PredArgs> &g, int grid, bool c
     return GRTE_OK;
 }
 
-// The one-work-group form up to TILE_MAX_M rows per lane and TILE_MAX_P pairs: a whole step
-// of 100 cells x 8 pairs 63 us against 116 with a work-group per pair and a cooperative
-// launch, 128 x 32 107 against 147, 512 x 16 106 against 139; at 512 x 32 both take 147, at
-// 512 x 64 246 against 176 (each of the eight wavefronts has eight pairs in turn).
-constexpr int TILE_MAX_P = 32;
-bool pred_tiled(int N, int P) { return N <= 64 * TILE_MAX_M && P <= TILE_MAX_P; }
+// contexts of unlike forms by one launch; coop as launch_pred
+grte_status launch_mixed(hipStream_t stream, Group<PredArgs> &g, int grid, bool coop)
+{
+    const size_t lds = MIXED_LDS * sizeof(double);
+    if (!coop) {
+        hipLaunchKernelGGL(pred_mixed_kernel, dim3(grid), dim3(64 * TILE_NW), lds, stream, g);
+        HIPCHK(hipGetLastError());
+        return GRTE_OK;
+    }
+    void *args[] = {&g};
+    HIPCHK(hipLaunchCooperativeKernel((const void *)pred_mixed_kernel, dim3(grid), dim3(64 * TILE_NW), args,
+                                      (unsigned)lds, stream));
+    return GRTE_OK;
+}
 
 // The prediction of the group's contexts (M: rows per thread of the form with a
-// work-group per pair).  Each context takes the form and the rows per lane that it takes
-// alone, so a group's results are those of the single steps to the bit: one launch per
-// form and row count that occurs.
-grte_status launch_prediction(hipStream_t stream, const Group<PredArgs> &g, int M, bool coop)
+// work-group per pair; capacity: work-groups of pred_mixed_kernel that the device holds at
+// once).  Each context takes the form and the rows per lane that it takes alone, so a
+// group's results are those of the single steps to the bit.  Like contexts run in the
+// kernel made for them, unlike ones in one launch of pred_mixed_kernel; should the device
+// not hold that, the tiles go first.
+grte_status launch_prediction(hipStream_t stream, const Group<PredArgs> &g, int M, int capacity, bool coop)
 {
-    auto rows = [](const PredArgs &a) { return pred_tiled(a.N, a.P) ? std::max(2, (a.N + 127) / 128 * 2) : 0; };
-    for (int r = 0; r <= TILE_MAX_M; r += 2) {
-        Group<PredArgs> q{};
-        int grid = 0;
-        for (int k = 0; k < g.n; ++k) {
-            if (rows(g.a[k]) != r) continue;
-            q.first[q.n] = grid;
-            q.a[q.n++] = g.a[k];
-            grid += g.a[k].P;
-        }
-        if (q.n == 0) continue;
-        q.first[q.n] = grid;
-        const dim3 n(q.n), b(64 * TILE_NW);
-        grte_status st = GRTE_OK;
-        if (r == 2) hipLaunchKernelGGL(pred_tile_kernel<2>, n, b, 0, stream, q);
-        else if (r == 4) hipLaunchKernelGGL(pred_tile_kernel<4>, n, b, 0, stream, q);
-        else if (r == 6) hipLaunchKernelGGL(pred_tile_kernel<6>, n, b, 0, stream, q);
-        else if (r == 8) hipLaunchKernelGGL(pred_tile_kernel<8>, n, b, 0, stream, q);
-        else if (M == 2) st = launch_pred<2>(stream, q, grid, coop);
-        else if (M == 4) st = launch_pred<4>(stream, q, grid, coop);
-        else if (M == 8) st = launch_pred<8>(stream, q, grid, coop);
-        else st = launch_pred<16>(stream, q, grid, coop);
-        if (st != GRTE_OK) return st;
+    Group<PredArgs> all{}, tiles{}, pairs{};
+    auto add = [](Group<PredArgs> &q, const PredArgs &a, int blocks) {
+        q.a[q.n++] = a;
+        q.first[q.n] = q.first[q.n - 1] + blocks;
+    };
+    int rows = 0;                                      // of the tiles (-1: they differ)
+    for (int k = 0; k < g.n; ++k) {
+        const int r = tiled_rows(g.a[k].N, g.a[k].P);
+        add(all, g.a[k], r ? 1 : g.a[k].P);
+        add(r ? tiles : pairs, g.a[k], r ? 1 : g.a[k].P);
+        if (r) rows = rows == 0 || rows == r ? r : -1;
+    }
+    if (tiles.n && pairs.n && all.first[all.n] <= capacity) return launch_mixed(stream, all, all.first[all.n], coop);
+    if (tiles.n) {
+        const dim3 n(tiles.n), b(64 * TILE_NW);
+        if (rows == 2) hipLaunchKernelGGL(pred_tile_kernel<2>, n, b, 0, stream, tiles);
+        else if (rows == 4) hipLaunchKernelGGL(pred_tile_kernel<4>, n, b, 0, stream, tiles);
+        else if (rows == 6) hipLaunchKernelGGL(pred_tile_kernel<6>, n, b, 0, stream, tiles);
+        else if (rows == 8) hipLaunchKernelGGL(pred_tile_kernel<8>, n, b, 0, stream, tiles);
+        else hipLaunchKernelGGL(pred_mixed_kernel, n, b, MIXED_LDS * sizeof(double), stream, tiles);
         HIPCHK(hipGetLastError());
     }
-    return GRTE_OK;
+    if (!pairs.n) return GRTE_OK;
+    const int grid = pairs.first[pairs.n];
+    switch (M) {
+    case 2: return launch_pred<2>(stream, pairs, grid, coop);
+    case 4: return launch_pred<4>(stream, pairs, grid, coop);
+    case 8: return launch_pred<8>(stream, pairs, grid, coop);
+    default: return launch_pred<16>(stream, pairs, grid, coop);
+    }
 }
 
 template <int S4>
@@ -1562,7 +1620,7 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
         if (st == GRTE_OK) st = alloc(ctx, q, NP);
     if (st == GRTE_OK) st = alloc(ctx, &ctx->part, 2 * NP * P);
     if (st == GRTE_OK) st = alloc(ctx, &ctx->r, NP * P);
-    if (st == GRTE_OK && pred_tiled(ctx->N, ctx->P)) st = alloc(ctx, &ctx->fac, (size_t)(P + 1) * fac_doubles(TILE_MAX_M));
+    if (st == GRTE_OK && tiled_rows(ctx->N, ctx->P)) st = alloc(ctx, &ctx->fac, (size_t)(P + 1) * fac_doubles(TILE_MAX_M));
     for (double **q : cells)
         if (st == GRTE_OK) st = alloc(ctx, q, N);
     double **nodes[] = {&ctx->Aw, &ctx->Bc};
@@ -1606,6 +1664,10 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
         return GRTE_E_UNSUPPORTED;
     }
     ctx->coop_capacity = nb * ncu;
+    int nm = 0;
+    if (ctx->M == 2 && hipOccupancyMaxActiveBlocksPerMultiprocessor(&nm, (const void *)pred_mixed_kernel, 64 * TILE_NW,
+                                                                    MIXED_LDS * sizeof(double)) == hipSuccess)
+        ctx->mixed_capacity = nm * ncu;
     ctx->cpb = std::max(1, 256 / ctx->P);
 
     if (hipMemcpy(ctx->mu, mu, P * sizeof(double), hipMemcpyHostToDevice) != hipSuccess ||
@@ -1868,7 +1930,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
     hipLaunchKernelGGL(coef_kernel, dim3(ncb_max, n), dim3(256), 0, stream, gc);
     HIPCHK(hipGetLastError());
     if (sample && (st = prof_begin(c0, GRTE_TIMING_PREDICT, &ev_pred)) != GRTE_OK) return st;
-    if ((st = launch_prediction(stream, gp, M, c0->coop_launch != 0)) != GRTE_OK) return st;
+    if ((st = launch_prediction(stream, gp, M, c0->mixed_capacity, c0->coop_launch != 0)) != GRTE_OK) return st;
     if ((st = prof_end(c0, ev_pred)) != GRTE_OK) return st;
     bool any_guess = false;
     for (int g = 0; g < n; ++g) any_guess = any_guess || gn.a[g].gw != nullptr;
@@ -2021,7 +2083,7 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
         pa.direct = pred_direct(P, ctx->M);
         pa.NP = NT * ctx->M;
         ctx->bar_gen += 2ull * (unsigned long long)ctx->pred_maxit + 4ull;
-        if ((st = launch_prediction(stream, gp, M, ctx->coop_launch != 0)) != GRTE_OK) return st;
+        if ((st = launch_prediction(stream, gp, M, ctx->mixed_capacity, ctx->coop_launch != 0)) != GRTE_OK) return st;
         hipLaunchKernelGGL(picard_update_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, N, ac,
                            ctx->T, ctx->beta, ctx->rho, Tk, Tk1, ctx->ustar, dmax);
         HIPCHK(hipGetLastError());
