@@ -2425,7 +2425,8 @@ grte_status krylov_run(grte2d_ctx *c, const Sys &S, int &its_out, int &state_out
     // wait for what is enqueued (a batch of iterations among it: its product's time)
     auto wait = [&](bool batch) {
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) return false;
-        if (timed && batch) {
+        // (a batch behind an iterate that meets the tolerance returns at once: no product)
+        if (timed && batch && c->h_fl[F_ITS] > 0) {
             float ms = 0.0f;
             if (hipEventElapsedTime(&ms, c->ev0, c->ev1) == hipSuccess) {
                 c->prof_ms += ms;

@@ -570,8 +570,8 @@ __global__ void __launch_bounds__(64 * TILE_NW) pred_tile_kernel(Group<PredArgs>
 // alone: the tiles and the pairs' work-groups run beside each other.  Bound by the longest
 // context's chain.  A whole step on an MI355X: 100, 200, 300 and 500 cells of 8 pairs 80 us
 // (173 with a launch per row count, one after the other), 512 x 32 beside 512 x 33 172 (243),
-// under the ordinary launch 148 (220).  A pair's work-group is the first wavefronts only (a work-group barrier waits for the
-// wavefronts that have not ended).
+// under the ordinary launch 148 (220).  A pair's work-group is the first four wavefronts
+// only (a work-group barrier waits for the wavefronts that have not ended).
 constexpr int MIXED_LDS = tile_lds<TILE_NW, TILE_MAX_M>();   // also covers the pairs' work-groups
 
 __global__ void __launch_bounds__(64 * TILE_NW) pred_mixed_kernel(Group<PredArgs> G)
