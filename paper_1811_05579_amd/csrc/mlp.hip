@@ -298,6 +298,24 @@ __device__ __forceinline__ Split split3(float v)
 // the upper halves of a and b as two bfloat16 values, a first
 __device__ __forceinline__ unsigned pack_hi(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
+// One row by the whole wavefront, lane l unit l of both layers, in plain binary32 sums: what
+// the rows need whose values are not finite on the way.  The split turns an infinity into
+// NaN (inf - inf), and so does an infinite weight with a zero term.  Behind the main loop, not in
+// it, where its registers cost 3 us of 85.
+__device__ __forceinline__ float eval_row(const uint16_t *wbf, const float *norm, const float *f, int l)
+{
+    float z = bf16_to_f(wbf[MLP_OB1 + l]);
+#pragma unroll
+    for (int k = 0; k < MLP_IN; ++k) z += bf16_to_f(wbf[MLP_OW1 + MLP_IN * l + k]) * ((f[k] - norm[k]) / norm[MLP_IN + k]);
+    const float h = gelu_f(z);
+    z = bf16_to_f(wbf[MLP_OB2 + l]);
+    for (int j = 0; j < MLP_H; ++j) z += bf16_to_f(wbf[MLP_OW2 + MLP_H * l + j]) * __shfl(h, j);
+    const float t = bf16_to_f(wbf[MLP_OW3 + l]) * gelu_f(z);
+    float y = bf16_to_f(wbf[MLP_OB3]);
+    for (int j = 0; j < MLP_H; ++j) y += __shfl(t, j);
+    return y;
+}
+
 __global__ void __launch_bounds__(256) mlp_predict_kernel(const uint16_t *wbf, const float *norm, const float *data,
                                                           long long n, float *y)
 {
@@ -336,6 +354,7 @@ __global__ void __launch_bounds__(256) mlp_predict_kernel(const uint16_t *wbf, c
                                                        0, 0, 0);
     };
     const long long tiles = (n + 31) / 32, stride = (long long)gridDim.x * 4;
+    bool bad = false;
     for (long long tile = (long long)blockIdx.x * 4 + (t >> 6); tile < tiles; tile += stride) {
         const long long row = tile * 32 + c;
         const float *f = data + (row < n ? row : n - 1) * 6;
@@ -366,7 +385,7 @@ __global__ void __launch_bounds__(256) mlp_predict_kernel(const uint16_t *wbf, c
                 unsigned hi[4], mid[4], lo[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const Split a = split3(gelu_f(z1[8 * k + 2 * j])), b = split3(gelu_f(z1[8 * k + 2 * j + 1]));
+                    const Split a = split3(gelu_finite(z1[8 * k + 2 * j])), b = split3(gelu_finite(z1[8 * k + 2 * j + 1]));
                     hi[j] = pack_hi(a.hi, b.hi);
                     mid[j] = pack_hi(a.mid, b.mid);
                     lo[j] = pack_hi(a.lo, b.lo);
@@ -387,13 +406,26 @@ __global__ void __launch_bounds__(256) mlp_predict_kernel(const uint16_t *wbf, c
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const float4 w = *reinterpret_cast<const float4 *>(&sW3[32 * m + 8 * g + 4 * h]);
-                s = fmaf(w.x, gelu_f(z2[m][4 * g]), s);
-                s = fmaf(w.y, gelu_f(z2[m][4 * g + 1]), s);
-                s = fmaf(w.z, gelu_f(z2[m][4 * g + 2]), s);
-                s = fmaf(w.w, gelu_f(z2[m][4 * g + 3]), s);
+                s = fmaf(w.x, gelu_finite(z2[m][4 * g]), s);
+                s = fmaf(w.y, gelu_finite(z2[m][4 * g + 1]), s);
+                s = fmaf(w.z, gelu_finite(z2[m][4 * g + 2]), s);
+                s = fmaf(w.w, gelu_finite(z2[m][4 * g + 3]), s);
             }
         s += __shfl_xor(s, 32);
-        if (h == 0 && row < n) y[row] = s + b3;
+        s += b3;
+        if (h == 0 && row < n) y[row] = s;
+        bad |= !isfinite(s);
+    }
+    if (!__any(bad)) return;
+    for (long long tile = (long long)blockIdx.x * 4 + (t >> 6); tile < tiles; tile += stride) {
+        const long long row = tile * 32 + c;
+        unsigned long long again = __ballot(h == 0 && row < n && !isfinite(y[row]));
+        while (again) {
+            const int k = __builtin_ctzll(again);
+            again &= again - 1;
+            const float v = eval_row(wbf, norm, data + (tile * 32 + k) * 6, l);
+            if (l == k) y[row] = v;
+        }
     }
 }
 constexpr int PREDICT_BLOCKS = 1024;   // four per compute unit, each wavefront's weights loaded once

@@ -65,18 +65,23 @@ __device__ __forceinline__ float upper_tail(float t)
     return __builtin_amdgcn_exp2f(-p);
 }
 
-__device__ __forceinline__ float gelu_f(float x)
+// of a finite x (an infinity gives NaN: inf 0)
+__device__ __forceinline__ float gelu_finite(float x)
 {
     const float t = fabsf(x);
     return fmaf(-t, upper_tail(t), fmaxf(x, 0.0f));
 }
+
+// of any x, as 0.5 x (1 + erf(x / sqrt 2)) gives it: inf at +inf, NaN at -inf and NaN
+// (above 12 the tail is below half an ulp of x)
+__device__ __forceinline__ float gelu_f(float x) { return x > 12.0f ? x : gelu_finite(x); }
 
 // gelu and its derivative Phi(x) + x phi(x)
 __device__ __forceinline__ float gelu_both(float x, float &d)
 {
     const float t = fabsf(x), q = upper_tail(t);
     d = fmaf(x * 0.39894228040143268f, __builtin_amdgcn_exp2f(-0.72134752044448170f * x * x), x > 0.0f ? 1.0f - q : q);
-    return fmaf(-t, q, fmaxf(x, 0.0f));
+    return x > 12.0f ? x : fmaf(-t, q, fmaxf(x, 0.0f));
 }
 
 // log10 inputs, computed in binary64 and rounded to binary32
