@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstdio>
 #include <new>
@@ -88,7 +89,8 @@ __global__ void __launch_bounds__(64 * NW) diff_kernel(DiffArgs A)
             Fl[r] = fl;
             Fr[r] = fr;
             const double T3 = Tj * Tj * Tj;
-            const double pref = A.dt * 4.0 * T3 * rcp64(4.0 * A.at * T3 + A.cv);
+            const double den = fmin(4.0 * A.at * T3 + A.cv, DBL_MAX);   // (rcp64 of an infinity is NaN)
+            const double pref = A.dt * 4.0 * T3 * rcp64(den);
             // interior faces couple to the neighbour; ghost faces move to the right-hand side
             const double wl = (j >= 1) ? fl * rdx2 : 0.0, wr = (j <= N - 2) ? fr * rdx2 : 0.0;
             const double gl = (j == 0 && A.bc == 1) ? fl * rdx2 : 0.0;
