@@ -1618,9 +1618,10 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
     double **padded[] = {&ctx->Gt, &ctx->res};
     for (double **q : padded)
         if (st == GRTE_OK) st = alloc(ctx, q, NP);
-    if (st == GRTE_OK) st = alloc(ctx, &ctx->part, 2 * NP * P);
+    if (st == GRTE_OK) st = alloc(ctx, &ctx->part, (pred_direct(ctx->P, ctx->M) ? 2 : 1) * NP * P);
     if (st == GRTE_OK) st = alloc(ctx, &ctx->r, NP * P);
-    if (st == GRTE_OK && tiled_rows(ctx->N, ctx->P)) st = alloc(ctx, &ctx->fac, (size_t)(P + 1) * fac_doubles(TILE_MAX_M));
+    const int rows = tiled_rows(ctx->N, ctx->P);
+    if (st == GRTE_OK && rows) st = alloc(ctx, &ctx->fac, (P + 1) * fac_doubles(rows));
     for (double **q : cells)
         if (st == GRTE_OK) st = alloc(ctx, q, N);
     double **nodes[] = {&ctx->Aw, &ctx->Bc};
