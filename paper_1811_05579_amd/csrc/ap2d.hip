@@ -2910,7 +2910,7 @@ grte_status grte2d_step(grte2d_ctx *c, double dt, double eps, grte2d_step_info *
         A.S = Sp;
         A.n = c->nE;
         A.En = c->E;
-            rhs_norm(c, A);
+        rhs_norm(c, A);
     }
     if (hipMemcpyAsync(c->x, c->E, c->nE * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess)
         return GRTE_E_HIP;
@@ -2984,7 +2984,7 @@ grte_status grte2d_step(grte2d_ctx *c, double dt, double eps, grte2d_step_info *
         A.S = Sc;
         A.n = c->nE;
         A.En = c->E;
-            rhs_norm(c, A);
+        rhs_norm(c, A);
     }
     hipLaunchKernelGGL(xcorr0_kernel, dim3(nb), dim3(B2), 0, st, c->x, c->Es, c->acU, c->P, 1.0 / eps, c->nE);
     if (hipGetLastError() != hipSuccess) return GRTE_E_HIP;

@@ -234,7 +234,7 @@ constexpr int RHS_U = 4;
 template <bool F32>
 struct IView {
     BInst I;
-    int N, P, N1, NP;               // NP: pair stride of the pair scratch (the instance's tile, W M)
+    int N, P, N1, NP;               // NP: pair stride of the pair scratch (64 M)
     const double *Tn, *sg, *mu, *om, *bL, *bR;
     double *T2, *C, *Rt, *Et;
     int *st;
@@ -250,7 +250,7 @@ __device__ __forceinline__ IView<F32> iview(const BatchArgs &A, int i)
     V.N = I.N;
     V.P = I.P;
     V.N1 = I.N + 1;
-    V.NP = 64 * I.M;                           // rows per lane: wavefront M, work-group LMW
+    V.NP = 64 * I.M;
     V.Tn = A.T + I.oT;
     V.sg = A.sigma0 + I.oT;
     V.mu = A.mu + I.oP;
@@ -1107,7 +1107,7 @@ grte_status grte_batch_create(int n, const grte_instance *inst, const double *mu
         b->cost[i] = (double)I.N * I.P;
     }
     b->tot_E = oE; b->tot_O = oO; b->tot_cells = oT; b->tot_pairs = oP;
-    // blocks of the per-cell kernels: 256 consecutive cells of one instance each,
+    // blocks of the per-cell kernels: CB consecutive cells of one instance each,
     // the instances' blocks contiguous and in instance order
     std::vector<int2> cblk;
     for (int i = 0; i < n; ++i) {
@@ -1434,42 +1434,36 @@ grte_status grte_batch_tune(grte_batch *b, int trials, grte_batch_tuning *best)
     int nb = 0;
     const void *kfn = (const void *)solve_kernel<0>;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kfn, BNT, BATCH_LDS) != hipSuccess) nb = 1;
+    const int bg = std::max(1, nb) * b->ncu;
     const int waves[] = {0, 128, 256};
-    std::vector<int> grids;
-    for (int f = 1; f <= std::max(1, nb); f *= 2) grids.push_back(f * b->ncu);
     hipEvent_t e0, e1;
     BCHK(hipEventCreate(&e0));
     BCHK(hipEventCreate(&e1));
     double best_ms = 1e300;
-    int bw = b->wave_max_n, bg = b->grid;
+    int bw = b->wave_max_n;
     for (int wv : waves) {
-        for (int g : grids) {
-            b->wave_max_n = wv;
-            b->grid = g;
-            if ((st = assign_tiles(b)) != GRTE_OK) break;
-            if ((st = restore()) != GRTE_OK) break;
-            if ((st = enqueue_step(b, b->stream, b->cur)) != GRTE_OK) break;   // warm-up
-            if ((st = restore()) != GRTE_OK) break;
-            if (hipEventRecord(e0, b->stream) != hipSuccess) { st = GRTE_E_HIP; break; }
-            for (int r = 0; r < trials && st == GRTE_OK; ++r) {
-                if (r > 0) st = restore();
-                if (st == GRTE_OK) st = enqueue_step(b, b->stream, b->cur);
-            }
-            if (st != GRTE_OK) break;
-            float ms = 0.0f;
-            if (hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
-                st = GRTE_E_HIP;
-                break;
-            }
-            const double per = ms / trials;
-            if (per < best_ms) {
-                best_ms = per;
-                bw = wv;
-                bg = g;
-            }
+        b->wave_max_n = wv;
+        if ((st = assign_tiles(b)) != GRTE_OK) break;
+        if ((st = restore()) != GRTE_OK) break;
+        if ((st = enqueue_step(b, b->stream, b->cur)) != GRTE_OK) break;   // warm-up
+        if ((st = restore()) != GRTE_OK) break;
+        if (hipEventRecord(e0, b->stream) != hipSuccess) { st = GRTE_E_HIP; break; }
+        for (int r = 0; r < trials && st == GRTE_OK; ++r) {
+            if (r > 0) st = restore();
+            if (st == GRTE_OK) st = enqueue_step(b, b->stream, b->cur);
         }
         if (st != GRTE_OK) break;
+        float ms = 0.0f;
+        if (hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+            hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
+            st = GRTE_E_HIP;
+            break;
+        }
+        const double per = ms / trials;
+        if (per < best_ms) {
+            best_ms = per;
+            bw = wv;
+        }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -105,7 +105,7 @@ struct CoefArgs {
     int f32;
     double mu1, mu2;             // sum omega mu, sum omega mu^2 (diffusion operator)
     double *Ll, *Lu, *Lam, *LmG, *Gt, *Bd, *Aw, *Bc, *beta;
-    double *Dl, *Dd, *Du;        // diffusion operator (prediction only)
+    double *Dd;                  // diagonal of the diffusion operator (prediction only)
     double *rho_n;               // sum_p omega_p E^n_p (prediction only)
     double *r;                   // right-hand sides, pair-major cell order [p * NP + j]
     int NP;                      // padded rows of a pair
@@ -173,8 +173,6 @@ __device__ __forceinline__ void coef_body(const CoefArgs &A)
             A.beta[j] = beta;
             A.LmG[j] = lmg;
             A.Gt[j] = s0 * c * dt * (ac * beta) / opb;
-            A.Dl[j] = A.mu2 * (-fl);
-            A.Du[j] = A.mu2 * (-fr);
             A.Dd[j] = lmg + A.mu2 * (fl + fr) + A.mu1 * bd;
             src = s0 * c * dt * ac * Un / opb;
         } else {
@@ -1275,7 +1273,7 @@ struct grte_ctx {
     double *E = nullptr, *O = nullptr, *T = nullptr;       // current state
     double *E2 = nullptr, *O2 = nullptr, *T2 = nullptr;    // next state
     double *sigma0, *mu, *omega, *bL, *bR;
-    double *Ll, *Lu, *Lam, *LmG, *Gt, *Bd, *Aw, *Bc, *beta, *Dl, *Dd, *Du, *rho_n;
+    double *Ll, *Lu, *Lam, *LmG, *Gt, *Bd, *Aw, *Bc, *beta, *Dd, *rho_n;
     double *r, *part, *res, *estar, *rho;
     double *fac = nullptr;        // factorisations of the one-work-group prediction (small slabs)
     double *ustar, *Dv, *ostar, *rho1, *rstar;
@@ -1612,7 +1610,7 @@ grte_status grte_create(const grte_problem *pb, const double *mu, const double *
     const size_t N = ctx->N, P = ctx->P;
     grte_status st = GRTE_OK;
     double **cells[] = {&ctx->T, &ctx->T2, &ctx->sigma0, &ctx->Ll, &ctx->Lu, &ctx->Lam,
-                        &ctx->LmG, &ctx->Bd, &ctx->beta, &ctx->Dl, &ctx->Dd, &ctx->Du,
+                        &ctx->LmG, &ctx->Bd, &ctx->beta, &ctx->Dd,
                         &ctx->rho_n, &ctx->rho, &ctx->rho_b, &ctx->ustar, &ctx->Dv, &ctx->rho1, &ctx->rstar};
     const size_t NP = (size_t)NT * ctx->M;    // padded rows of the solvers
     double **padded[] = {&ctx->Gt, &ctx->res};
@@ -1856,7 +1854,7 @@ grte_status step_group(grte_ctx *const *ctxs, int n, const double *dts, const do
         ca.mu1 = ctx->mu1; ca.mu2 = ctx->mu2;
         ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.NP = NT * ctx->M;
         ca.Bd = ctx->Bd; ca.Aw = ctx->Aw; ca.Bc = ctx->Bc; ca.beta = ctx->beta;
-        ca.Dl = ctx->Dl; ca.Dd = ctx->Dd; ca.Du = ctx->Du; ca.rho_n = ctx->rho_n; ca.r = ctx->r;
+        ca.Dd = ctx->Dd; ca.rho_n = ctx->rho_n; ca.r = ctx->r;
         ca.stat = ctx->stat;
         ca.E32 = ctx->E32; ca.O32 = ctx->O32; ca.f32 = ctx->f32;
         // prediction: work-groups [grid, grid + P) belong to this context
@@ -2057,7 +2055,7 @@ grte_status grte_reference_step(grte_ctx *ctx, double dt, double eps, double tol
     ca.mu1 = ctx->mu1; ca.mu2 = ctx->mu2;
     ca.Ll = ctx->Ll; ca.Lu = ctx->Lu; ca.Lam = ctx->Lam; ca.LmG = ctx->LmG; ca.Gt = ctx->Gt; ca.NP = NT * M;
     ca.Bd = ctx->Bd; ca.Aw = ctx->Aw; ca.Bc = ctx->Bc; ca.beta = ctx->beta;
-    ca.Dl = ctx->Dl; ca.Dd = ctx->Dd; ca.Du = ctx->Du; ca.rho_n = ctx->rho_n; ca.r = ctx->r;
+    ca.Dd = ctx->Dd; ca.rho_n = ctx->rho_n; ca.r = ctx->r;
     ca.stat = ctx->stat;
     Group<PredArgs> gp{};
     gp.n = 1;

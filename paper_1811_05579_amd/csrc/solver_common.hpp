@@ -155,7 +155,7 @@ struct Int {
 // are eliminated, the last rows of a wavefront merged by blocks of 1, 2, .. 32 lanes
 // (merge_factor), and what a wavefront's first and last value answer to its neighbours'
 // goes through LDS as lanes 2 w, 2 w + 1 of one more such merge, which every wavefront
-// does on its own.  Two barriers (three for M > 1).
+// does on its own.  One barrier (two for M > 1).
 template <int NW, int M>
 __device__ __forceinline__ void tri_wg(const double (&a)[M], const double (&b)[M], const double (&c)[M], double (&x)[M])
 {
