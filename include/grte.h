@@ -613,7 +613,7 @@ enum {
 grte_status grte2d_circle_directions(int nv, double *mu, double *eta, double *omega);
 
 /* Create a context: copies the problem and the pairs (host arrays of P doubles)
- * and allocates device memory (about 16 binary64 arrays of nx*ny*P).  State
+ * and allocates device memory (about 18 binary64 arrays of nx*ny*P).  State
  * zero, opacity one, inflow zero until set.  GRTE_E_UNSUPPORTED for sizes or P
  * outside the limits above, GRTE_E_INVAL for bad values, GRTE_E_NOMEM. */
 grte_status grte2d_create(const grte2d_problem *pb, const double *mu, const double *eta,
@@ -672,9 +672,10 @@ grte_status grte2d_set_krylov_storage(grte2d_ctx *ctx, int narrow);
  * operator -- the mode that the angular coupling leaves nearly undamped in
  * optically thick cells (the diffusion limit of Section 3).  kind 0: none;
  * kind 1 (default): `steps` Chebyshev steps (default 19) on the Jacobi-scaled
- * operator, in launches over 32 x 32-cell tiles that take up to 9 stencil
- * steps each with a halo of as many cells (one launch up to 10 steps, two up
- * to 19); kind 2: one multigrid
+ * operator, in launches over regions of 64 x 16 to 96 cells that take up to 9
+ * stencil steps each with a halo of as many cells (one launch up to 10 steps,
+ * two up to 19; grids that one region covers: one launch up to 25 steps, no
+ * halo); kind 2: one multigrid
  * V-cycle (2 x 2 cell aggregates, coarse rows with the children's row sums and
  * half their couplings across each side, `steps` weighted-Jacobi sweeps before
  * and after each coarse correction); kind 3: kind 1's map with one launch per
