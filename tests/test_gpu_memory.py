@@ -2,6 +2,8 @@
 and O*, the right-hand sides and one buffer of partial sums are eight words per cell and
 pair; only slabs whose sums every work-group forms itself have a second such buffer.
 """
+import gc
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -16,6 +18,7 @@ def test_words_per_cell_and_pair(N, nv):
     """Nine words bound the eight, the per-cell arrays and the padding to the solvers' rows
     and to the allocator's granules."""
     mu, om = gauss_legendre(nv)
+    gc.collect()                                   # nothing of an earlier test is freed in between
     first = Grte(N, mu, om)                        # what the first context costs the process
     free = torch.cuda.mem_get_info()[0]
     gs = [Grte(N, mu, om) for _ in range(16)]
